@@ -29,11 +29,18 @@ UNITS = [
     ("mnufft.cpp", [], "mnufft.o"),
     ("host_common.cpp", [], "host_common.o"),
     ("batch.cpp", [], "batch.o"),
+    ("fft_plan.cpp", [], "fft_plan.o"),
     ("tune.cpp", [], "tune.o"),
     ("select.cpp", [], "select.o"),
     ("kernels_mlp.hip", [], "kernels_mlp.o"),
     ("kernels_sort.hip", [], "kernels_sort.o"),
     ("kernels_deconv.hip", [], "kernels_deconv.o"),
+    ("kernels_fft.hip", [], "kernels_fft.o"),
+    ("fft_inst.hip", ["-DMN_T=float", "-DMN_V=16", "-DMN_TAB=false"], "fft_f16.o"),
+    ("fft_inst.hip", ["-DMN_T=float", "-DMN_V=16", "-DMN_TAB=true"], "fft_f16t.o"),
+    ("fft_inst.hip", ["-DMN_T=float", "-DMN_V=24", "-DMN_TAB=false"], "fft_f24.o"),
+    ("fft_inst.hip", ["-DMN_T=double", "-DMN_V=16", "-DMN_TAB=false"], "fft_d16.o"),
+    ("fft_inst.hip", ["-DMN_T=double", "-DMN_V=16", "-DMN_TAB=true"], "fft_d16t.o"),
     ("kernels_type3.hip", [], "kernels_type3.o"),
     ("spread_dispatch.hip", [], "spread_dispatch.o"),
     ("spread_inst.hip", ["-DMN_T=float", "-DMN_D=1"], "spread_f1.o"),

@@ -63,6 +63,9 @@ struct mnufft_batch_s {
     uint32_t *hist = nullptr, *partials = nullptr;
     void *scratch = nullptr, *cmax = nullptr;
     int *flag = nullptr;
+    // FFTs: the library's own passes, one launch each over all transforms, or
+    // rocFFT plans per size where a dimension is too long for them
+    mn::host::FftBatch own;
     std::map<std::array<int, 3>, rocfft_plan> fft;
     // The transforms' FFTs are independent and mostly small: they run spread
     // over kFftStreams streams (default priority), forked from and joined
@@ -169,9 +172,42 @@ int sm_classes(mnufft_batch b, const mn::Pts &P, bool interp, const void *in, vo
     return MNUFFT_OK;
 }
 
-int run_ffts(mnufft_batch b, int sign)
+// rocFFT plans of every transform size, and their workspaces.
+int make_rocffts(mnufft_batch b, int iflag)
 {
-    (void)sign;  // plans were made for the batch's single direction
+    if (rocfft_setup() != rocfft_status_success) return MNUFFT_ERR_FFT;
+    for (int k = 0; k < mnufft_batch_s::kFftStreams; ++k)
+        if (rocfft_execution_info_create(&b->info[k]) != rocfft_status_success)
+            return MNUFFT_ERR_FFT;
+    b->fft_order.resize(b->T);
+    for (int t = 0; t < b->T; ++t) b->fft_order[t] = t;
+    std::stable_sort(b->fft_order.begin(), b->fft_order.end(), [&](int a, int c) {
+        const mn::TGeom &ga = b->geo[a], &gc = b->geo[c];
+        return (int64_t)ga.n[0] * ga.n[1] * ga.n[2] > (int64_t)gc.n[0] * gc.n[1] * gc.n[2];
+    });
+    size_t work = 0;
+    for (const mn::TGeom &tg : b->geo) {
+        const std::array<int, 3> key = {tg.n[0], tg.n[1], tg.n[2]};
+        if (b->fft.count(key)) continue;
+        void *pl = nullptr;
+        size_t wb = 0;
+        const int rc = mn::host::make_rocfft(b->prec, b->dim, tg.n, 1, iflag, &pl, &wb);
+        if (rc) return rc;
+        b->fft[key] = (rocfft_plan)pl;
+        work = std::max(work, wb);
+    }
+    if (work) {
+        work = (work + 255) / 256 * 256;
+        const int rc = balloc(b, &b->fftwork, work * mnufft_batch_s::kFftStreams);
+        if (rc) return rc;
+        b->fftwork_bytes = work;
+    }
+    return MNUFFT_OK;
+}
+
+// rocFFT of every transform's grid, in place.
+int run_rocffts(mnufft_batch b)
+{
     if (hipEventRecord(b->fork, b->stream) != hipSuccess) return MNUFFT_ERR_HIP;
     for (int k = 0; k < mnufft_batch_s::kFftStreams; ++k) {
         if (hipStreamWaitEvent(b->fstream[k], b->fork, 0) != hipSuccess) return MNUFFT_ERR_HIP;
@@ -392,8 +428,7 @@ int mnufft_batch_makeplan(int type, int dim, int ntr, const int64_t *nmodes, con
 
     // ---- device state ----
     int rc = MNUFFT_OK;
-    if (rocfft_setup() != rocfft_status_success) rc = MNUFFT_ERR_FFT;
-    if (!rc && b->device >= 0 && hipSetDevice(b->device) != hipSuccess) rc = MNUFFT_ERR_HIP;
+    if (b->device >= 0 && hipSetDevice(b->device) != hipSuccess) rc = MNUFFT_ERR_HIP;
     if (!rc) rc = balloc(b, (void **)&b->d_geo, sizeof(mn::TGeom) * ntr);
     if (!rc) rc = upload(b->d_geo, b->geo.data(), sizeof(mn::TGeom) * ntr);
     if (!rc) {
@@ -443,34 +478,15 @@ int mnufft_batch_makeplan(int type, int dim, int ntr, const int64_t *nmodes, con
     if (!rc && hipEventCreateWithFlags(&b->fork, hipEventDisableTiming) != hipSuccess)
         rc = MNUFFT_ERR_HIP;
     for (int k = 0; k < mnufft_batch_s::kFftStreams && !rc; ++k) {
-        if (rocfft_execution_info_create(&b->info[k]) != rocfft_status_success) rc = MNUFFT_ERR_FFT;
-        else if (hipStreamCreateWithFlags(&b->fstream[k], hipStreamNonBlocking) != hipSuccess ||
+        if (hipStreamCreateWithFlags(&b->fstream[k], hipStreamNonBlocking) != hipSuccess ||
                  hipEventCreateWithFlags(&b->join[k], hipEventDisableTiming) != hipSuccess)
             rc = MNUFFT_ERR_HIP;
     }
-    b->fft_order.resize(ntr);
-    for (int t = 0; t < ntr; ++t) b->fft_order[t] = t;
-    std::stable_sort(b->fft_order.begin(), b->fft_order.end(), [&](int a, int c) {
-        const mn::TGeom &ga = b->geo[a], &gc = b->geo[c];
-        return (int64_t)ga.n[0] * ga.n[1] * ga.n[2] > (int64_t)gc.n[0] * gc.n[1] * gc.n[2];
-    });
-    size_t work = 0;
-    for (int t = 0; t < ntr && !rc; ++t) {
-        const mn::TGeom &tg = b->geo[t];
-        const std::array<int, 3> key = {tg.n[0], tg.n[1], tg.n[2]};
-        if (b->fft.count(key)) continue;
-        void *pl = nullptr;
-        size_t wb = 0;
-        rc = mn::host::make_rocfft(prec, dim, tg.n, 1, iflag, &pl, &wb);
-        if (rc) break;
-        b->fft[key] = (rocfft_plan)pl;
-        work = std::max(work, wb);
-    }
-    if (!rc && work) {
-        work = (work + 255) / 256 * 256;
-        rc = balloc(b, &b->fftwork, work * mnufft_batch_s::kFftStreams);
-        b->fftwork_bytes = work;
-    }
+    if (!rc)
+        rc = b->own.make(type, dim, iflag, b->geo, prec, b->pfac,
+                         [b](void **ptr, size_t bytes) { return balloc(b, ptr, bytes); },
+                         b->stream);
+    if (!rc && !b->own.ok) rc = make_rocffts(b, iflag);
     if (rc) {
         mnufft_batch_destroy(b);
         return rc;
@@ -547,7 +563,8 @@ int mnufft_batch_execute(mnufft_batch b, void *c, void *f)
         }
         {
             StageTimer tm(b->tm, MNUFFT_STAGE_FFT, s);
-            rc = run_ffts(b, b->iflag);
+            if (b->own.ok) return b->own.run(b->grid, f, s);
+            rc = run_rocffts(b);
         }
         if (rc) return rc;
         StageTimer tm(b->tm, MNUFFT_STAGE_DECONV, s);
@@ -555,14 +572,14 @@ int mnufft_batch_execute(mnufft_batch b, void *c, void *f)
             return MNUFFT_ERR_HIP;
         return MNUFFT_OK;
     }
-    {
+    if (!b->own.ok) {
         StageTimer tm(b->tm, MNUFFT_STAGE_PRECORRECT, s);
         if (mn::launch_precorrect_batch(b->d_geo, b->T, b->cells, b->prec, f, b->pfac, b->grid, s))
             return MNUFFT_ERR_HIP;
     }
     {
         StageTimer tm(b->tm, MNUFFT_STAGE_FFT, s);
-        rc = run_ffts(b, b->iflag);
+        rc = b->own.ok ? b->own.run(b->grid, f, s) : run_rocffts(b);
     }
     if (rc) return rc;
     StageTimer tm(b->tm, MNUFFT_STAGE_INTERP, s);

@@ -5,6 +5,7 @@
 #include "internal.h"
 
 #include <stdint.h>
+#include <functional>
 #include <utility>
 #include <vector>
 
@@ -75,6 +76,40 @@ struct StageTimer {
     bool on;
     StageTimer(Timers &tt, int st, hipStream_t ss);
     ~StageTimer();
+};
+
+// Fine-grid FFT with truncation / zero padding and correction factors in its
+// passes.  `ok` is false when a dimension is too long for a block's LDS (or a
+// line's pass for its threads): those grids use rocFFT and the correction
+// kernels.
+enum FftBuf { kFftGrid = 0, kFftModes = 1, kFftWork = 2 };
+using FftAlloc = std::function<int(void **, size_t)>;
+struct FftStep {
+    FftPass p;
+    int V = 16, form = 0, src = 0, dst = 0;
+    long long tiles = 0;
+};
+struct FftPlan {
+    bool ok = false;
+    int prec = 0;
+    std::vector<FftStep> dir[2];   // type 1, type 2
+    int64_t work_cells = 0;        // workspace of type 2 (1D, two-pass), complex values
+    // Tables are allocated with `alloc` and filled on s (which is waited for).
+    int make(int dim, const int64_t *N, const int *n, int64_t nt, int prec_,
+             const void *const pf[3], const FftAlloc &alloc, hipStream_t s);
+    // type 1: grid (overwritten) -> modes; type 2: modes -> grid.
+    int run(int type, int sign, void *grid, void *modes, void *work, hipStream_t s) const;
+};
+// The same for every transform of a batch (2D / 3D), one launch per pass.
+struct FftBatch {
+    bool ok = false;
+    int prec = 0, steps = 0, ntab = 0;
+    const FftPass *table[3] = {};
+    int form[3] = {}, src[3] = {}, dst[3] = {}, threads[3] = {}, lds[3] = {};
+    long long tiles[3] = {};
+    int make(int type, int dim, int iflag, const std::vector<TGeom> &geo, int prec_,
+             const void *const pf[3], const FftAlloc &alloc, hipStream_t s);
+    int run(void *grid, void *modes, hipStream_t s) const;
 };
 
 // In-place C2C rocFFT plan of the given lengths (first fastest); `sign` is

@@ -329,6 +329,53 @@ hipError_t launch_deconv_batch(const TGeom *tg, int T, long long nmodes, int pre
 hipError_t launch_precorrect_batch(const TGeom *tg, int T, long long ncells, int prec,
                                    const void *f, const void *const p[3], void *grid,
                                    hipStream_t s);
+// ---- fine-grid FFT (kernels_fft.hip) ----------------------------------------
+// One pass: length-n transforms of the lines (a, b, t), a < na, b < nb, along
+// elements e.  Source element e of a line is at s0 + e s_e + a s_a + b s_b +
+// t s_t (complex values), destination likewise with d_*.  Form 0 moves every
+// element.  Otherwise element e stands for frequency l = e pe + a pa of full,
+// and form 1 writes, form 2 reads (zeros elsewhere) only the `cut` modes
+// around zero, mode i in the place of element i, scaled by fa[a] fb[b] fe[i]
+// when `scale` is set.
+constexpr int kFftStages = 8;
+struct FftPass {
+    int n, np, T, C, logC;   // length, radix stages, threads per line, lines per block
+    int R[kFftStages], Ns[kFftStages];
+    unsigned mNs[kFftStages];  // ceil(2^32 / Ns)
+    int pitch, lds, threads;   // LDS pitch of a line (values), bytes, block size
+    int col0, col1;          // thread order of the first load / of the rest: lines fastest
+    int inv;                 // exponent sign +1
+    int na, nb, ta;          // lines, tiles over a
+    int cut, scale;          // kept modes (forms 1, 2); multiply by the factors
+    int tw0[kFftStages], tw_len;  // each stage's factors in tw, their count
+    int pe, pa, full;
+    int tile0;               // batches: first tile of this entry
+    long long s0, s_e, s_a, s_b, s_t, d0, d_e, d_a, d_b, d_t;
+    const void *fe, *fa, *fb, *tw;
+    const void *tw4;         // scale outputs by exp(-2 pi i a e / full): kTw4 fine steps,
+                             // then the coarse ones (null: no)
+};
+constexpr int kTw4 = 2048;
+// Largest block of the line kernels: 128 registers a thread in single, 256 in
+// double precision (with 128 they spill: 2000 x 1998 forward rows 194 us
+// against 62 us).
+constexpr int fft_max_threads(int prec) { return prec != 0 ? 512 : 1024; }
+// Radix stages and threads per line for length n with V values per thread;
+// false when n does not factor into them.
+bool fft_line(int n, int prec, int V, FftPass &p);
+// Lines per block, LDS and block size of a pass whose n, na are set, over
+// `outer` groups of na lines; rows: the source line is contiguous.
+bool fft_tile(FftPass &p, int prec, bool rows, long long outer);
+// out[m] = exp(-2 pi i m step / n), m < cnt, complex of the precision.
+hipError_t launch_twiddle(int prec, int cnt, long long step, double n, void *out, hipStream_t s);
+// The stage factors of a pass (tw_len values).
+hipError_t launch_stage_twiddle(int prec, const FftPass &p, void *out, hipStream_t s);
+// Run a pass over `tiles` blocks (ta nb times the t count); with a table
+// (device, ntab entries by tile0), block -> entry.
+hipError_t launch_fft_lines(int prec, int V, int form, const FftPass &p, const FftPass *tab, int ntab,
+                            long long tiles, int threads, int lds, const void *src, void *dst,
+                            hipStream_t s);
+
 // ---- type 3 (kernels_type3.hip) -------------------------------------------
 // Per-dimension constants of the type 3 factors (see kernels_type3.hip): the
 // rescaled value of v is (v - off) * scale; the phases use mul.

@@ -79,7 +79,9 @@ struct mnufft_plan_s {
     void *cmax = nullptr;
     size_t cov_bytes[3] = {0, 0, 0};
     int kmax[3] = {1, 1, 1};
-    // FFT
+    // FFT: the library's own passes, or rocFFT where a dimension is too long
+    mn::host::FftPlan own;
+    void *owntab = nullptr;
     rocfft_plan fft[2] = {nullptr, nullptr};  // [0]: exponent sign -1, [1]: +1
     rocfft_execution_info fftinfo = nullptr;
     void *fftwork = nullptr;
@@ -214,39 +216,39 @@ int alloc_points(mnufft_plan p, int64_t M)
     return MNUFFT_OK;
 }
 
-int make_fft(mnufft_plan p, int which)
+// What running type `type` (1 or 2) with exponent sign `sign` needs: the
+// workspace of the two-pass 1D transform, or the rocFFT plan of that sign.
+int make_fft(mnufft_plan p, int type, int sign)
 {
-    if (p->fft[which]) return MNUFFT_OK;
-    size_t len[3];
-    for (int d = 0; d < p->dim; ++d) len[d] = (size_t)p->g.n[d];  // first dimension fastest
-    rocfft_status st = rocfft_plan_create(
-        &p->fft[which], rocfft_placement_inplace,
-        which == 0 ? rocfft_transform_type_complex_forward : rocfft_transform_type_complex_inverse,
-        p->prec == MNUFFT_F32 ? rocfft_precision_single : rocfft_precision_double,
-        (size_t)p->dim, len, (size_t)p->ntransf, nullptr);
-    if (st != rocfft_status_success) {
-        p->fft[which] = nullptr;
-        return MNUFFT_ERR_FFT;
-    }
     size_t wb = 0;
-    if (rocfft_plan_get_work_buffer_size(p->fft[which], &wb) != rocfft_status_success)
-        return MNUFFT_ERR_FFT;
+    if (p->own.ok) {
+        wb = type == 2 ? (size_t)p->own.work_cells * 2 * p->rsz : 0;
+    } else {
+        const int which = sign < 0 ? 0 : 1;
+        if (p->fft[which]) return MNUFFT_OK;
+        std::call_once(g_fft_once, [] { g_fft_setup = rocfft_setup(); });
+        if (g_fft_setup != rocfft_status_success) return MNUFFT_ERR_FFT;
+        if (!p->fftinfo && rocfft_execution_info_create(&p->fftinfo) != rocfft_status_success)
+            return MNUFFT_ERR_FFT;
+        void *pl = nullptr;
+        const int rc = mn::host::make_rocfft(p->prec, p->dim, p->g.n, (size_t)p->ntransf, sign,
+                                             &pl, &wb);
+        if (rc) return rc;
+        p->fft[which] = (rocfft_plan)pl;
+    }
     if (wb > p->fftwork_bytes) {
         dfree(p, &p->fftwork, p->fftwork_bytes);
         p->fftwork_bytes = 0;
-        int rc = dalloc(p, &p->fftwork, wb);
+        const int rc = dalloc(p, &p->fftwork, wb);
         if (rc) return rc;
         p->fftwork_bytes = wb;
     }
     return MNUFFT_OK;
 }
 
-// In-place unnormalised FFT of all ntransf grids with exponent sign `sign`.
-int run_fft(mnufft_plan p, int sign)
+// In-place unnormalised rocFFT of all ntransf grids with exponent sign `sign`.
+int run_rocfft(mnufft_plan p, int sign)
 {
-    const int which = sign < 0 ? 0 : 1;
-    int rc = make_fft(p, which);
-    if (rc) return rc;
     if (rocfft_execution_info_set_stream(p->fftinfo, p->stream) != rocfft_status_success)
         return MNUFFT_ERR_FFT;
     if (p->fftwork_bytes &&
@@ -254,9 +256,43 @@ int run_fft(mnufft_plan p, int sign)
             rocfft_status_success)
         return MNUFFT_ERR_FFT;
     void *buf[1] = {p->grid};
-    if (rocfft_execute(p->fft[which], buf, nullptr, p->fftinfo) != rocfft_status_success)
+    if (rocfft_execute(p->fft[sign < 0 ? 0 : 1], buf, nullptr, p->fftinfo) !=
+        rocfft_status_success)
         return MNUFFT_ERR_FFT;
     return MNUFFT_OK;
+}
+
+// Steps 2 and 3 of type 1: FFT of the grids, modes f scaled and truncated.
+int grid_to_modes(mnufft_plan p, int sign, void *f)
+{
+    int rc = make_fft(p, 1, sign);
+    if (rc) return rc;
+    {
+        StageTimer tm(p->tm, MNUFFT_STAGE_FFT, p->stream);
+        if (p->own.ok) return p->own.run(1, sign, p->grid, f, p->fftwork, p->stream);
+        rc = run_rocfft(p, sign);
+    }
+    if (rc) return rc;
+    StageTimer tm(p->tm, MNUFFT_STAGE_DECONV, p->stream);
+    MN_HIP(mn::launch_deconv(p->dim, p->N, p->g.n, p->prec, (int)p->ntransf, p->grid, p->pfac, f,
+                             p->stream));
+    return MNUFFT_OK;
+}
+
+// Steps 1 and 2 of type 2: modes f scaled and zero-padded, FFT of the grids.
+int modes_to_grid(mnufft_plan p, int sign, const void *f)
+{
+    int rc = make_fft(p, 2, sign);
+    if (rc) return rc;
+    if (!p->own.ok) {
+        StageTimer tm(p->tm, MNUFFT_STAGE_PRECORRECT, p->stream);
+        MN_HIP(mn::launch_precorrect(p->dim, p->N, p->g.n, p->prec, (int)p->ntransf, f, p->pfac,
+                                     p->grid, p->stream));
+    }
+    StageTimer tm(p->tm, MNUFFT_STAGE_FFT, p->stream);
+    if (p->own.ok)
+        return p->own.run(2, sign, p->grid, const_cast<void *>(f), p->fftwork, p->stream);
+    return run_rocfft(p, sign);
 }
 
 mn::Pts points_of(mnufft_plan p)
@@ -354,15 +390,7 @@ int exec_type1(mnufft_plan p, int sign, const void *c, void *f, bool sorted = fa
 {
     int rc = spread_all(p, c, sorted);
     if (rc) return rc;
-    {
-        StageTimer tm(p->tm, MNUFFT_STAGE_FFT, p->stream);
-        rc = run_fft(p, sign);
-    }
-    if (rc) return rc;
-    StageTimer tm(p->tm, MNUFFT_STAGE_DECONV, p->stream);
-    MN_HIP(mn::launch_deconv(p->dim, p->N, p->g.n, p->prec, (int)p->ntransf, p->grid,
-                             p->pfac, f, p->stream));
-    return MNUFFT_OK;
+    return grid_to_modes(p, sign, f);
 }
 
 // Type 2 with exponent sign `sign`: f (ntransf x N) -> c (ntransf x M); c in
@@ -370,16 +398,7 @@ int exec_type1(mnufft_plan p, int sign, const void *c, void *f, bool sorted = fa
 int exec_type2(mnufft_plan p, int sign, const void *f, void *c, bool sorted = false)
 {
     mn::Pts P = kernel_points(p, sorted);
-    {
-        StageTimer tm(p->tm, MNUFFT_STAGE_PRECORRECT, p->stream);
-        MN_HIP(mn::launch_precorrect(p->dim, p->N, p->g.n, p->prec, (int)p->ntransf, f,
-                                     p->pfac, p->grid, p->stream));
-    }
-    int rc;
-    {
-        StageTimer tm(p->tm, MNUFFT_STAGE_FFT, p->stream);
-        rc = run_fft(p, sign);
-    }
+    int rc = modes_to_grid(p, sign, f);
     if (rc) return rc;
     for (int64_t t = 0; t < p->ntransf; ++t) {
         char *ct = (char *)c + (size_t)t * p->M * 2 * p->rsz;
@@ -632,10 +651,7 @@ int plan_device(mnufft_plan p, bool with_fft)
 {
     const int dim = p->dim;
     const mn::Geom &g = p->g;
-    std::call_once(g_fft_once, [] { g_fft_setup = rocfft_setup(); });
-    int rc = MNUFFT_OK;
-    if (g_fft_setup != rocfft_status_success) rc = MNUFFT_ERR_FFT;
-    if (!rc) rc = use_device(p);
+    int rc = use_device(p);
     if (!rc) rc = dalloc(p, &p->grid, p->grid_elems * 2 * p->rsz * p->ntransf);
     for (int d = 0; d < 3 && !rc && with_fft; ++d) {
         std::vector<double> fac;
@@ -655,9 +671,13 @@ int plan_device(mnufft_plan p, bool with_fft)
     if (!rc) rc = dalloc(p, (void **)&p->flag, 16);
     if (!rc) rc = plan_bins_device(p);
     if (with_fft) {
-        if (!rc && rocfft_execution_info_create(&p->fftinfo) != rocfft_status_success)
-            rc = MNUFFT_ERR_FFT;
-        if (!rc) rc = make_fft(p, p->iflag < 0 ? 0 : 1);
+        const mn::host::FftAlloc alloc = [p](void **ptr, size_t bytes) {
+            const int r = dalloc(p, ptr, bytes);
+            p->owntab = *ptr;
+            return r;
+        };
+        if (!rc) rc = p->own.make(dim, p->N, g.n, p->ntransf, p->prec, p->pfac, alloc, p->stream);
+        if (!rc) rc = make_fft(p, p->type, p->iflag);
     }
     return rc;
 }
@@ -1140,9 +1160,7 @@ int mnufft_interp_grad(mnufft_plan p, const void *modes, const void *wts, void *
     if ((rc = use_device(p))) return rc;
     // field = type 2 of `modes` with the sign of the plan's type 2 direction
     const int sign = p->type == 2 ? p->iflag : -p->iflag;
-    MN_HIP(mn::launch_precorrect(p->dim, p->N, p->g.n, p->prec, (int)p->ntransf, modes,
-                                 p->pfac, p->grid, p->stream));
-    if ((rc = run_fft(p, sign))) return rc;
+    if ((rc = modes_to_grid(p, sign, modes))) return rc;
     void *out[3] = {gx, p->dim >= 2 ? gy : nullptr, p->dim == 3 ? gz : nullptr};
     MN_HIP(mn::launch_interp_grad(p->g, p->prec, points_of(p), (int)p->ntransf, p->grid, wts,
                                   out, p->stream));
@@ -1182,11 +1200,13 @@ int mnufft_set_stream(mnufft_plan p, void *stream)
     if (!p) return MNUFFT_ERR_ARG;
     int rc = use_device(p);
     if (rc) return rc;
-    // both FFT directions exist from here on, so execute / execute_adjoint
-    // allocate nothing and can be captured into a graph
+    // what both FFT directions need exists from here on, so execute /
+    // execute_adjoint allocate nothing and can be captured into a graph
     for (mnufft_plan q : {p, p->t3inner}) {
-        if (!q || !q->fftinfo) continue;
-        if ((rc = make_fft(q, 0)) || (rc = make_fft(q, 1))) return rc;
+        if (!q || q->type == 3) continue;
+        const int other = -q->iflag;
+        if ((rc = make_fft(q, q->type, q->iflag)) || (rc = make_fft(q, 3 - q->type, other)))
+            return rc;
     }
     for (mnufft_plan q : {p, p->t3spr, p->t3inner}) {
         if (!q) continue;
@@ -1282,6 +1302,7 @@ int mnufft_destroy(mnufft_plan p)
     dfree(p, (void **)&p->t3quad, 0);
     free_points(p);
     dfree(p, &p->fftwork, p->fftwork_bytes);
+    dfree(p, &p->owntab, 0);
     dfree(p, &p->grid, p->grid_elems * 2 * p->rsz * p->ntransf);
     for (int d = 0; d < 3; ++d) dfree(p, &p->pfac[d], 0);
     dfree(p, (void **)&p->binstart, 0);
