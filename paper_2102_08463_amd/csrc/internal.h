@@ -177,6 +177,10 @@ struct Pts {
     int kmax[3];
     void *cmax;               // 1024 partial maxima of |Re c|, |Im c| of the vector being spread
     int msub;                 // maximum points per subproblem
+    int mf;                   // start cells per window group of the matrix-core kernels
+                              // (the points are in their order; 0: tap by tap)
+    int *work;                // their work counters (spreading, interpolation), zero
+                              // between launches
     // batches: per-transform geometry (device) and count; nullptr / 1 for a plain plan
     const TGeom *tg;
     int T;
@@ -264,6 +268,21 @@ hipError_t launch_balance(const Geom &g, int prec, int nsub_max, const int32_t *
                           const int32_t *nsub, const void *const u[3], const int32_t *perm,
                           void *const v[3], int32_t *vperm, int32_t *spos, uint16_t *hslot,
                           hipStream_t s);
+
+// Matrix-core kernels (mfma_kernels.h): start cells per dimension of a window
+// group, or 0 when a plan's SM kernels work tap by tap.  Double precision 3D
+// of widths 8 to 14: below, the window's 16^3 cells per point cost more than
+// its w^3 taps (2 w^3 atomics at 3.6 a cycle and CU against 128 cycles of
+// products: even near w = 7), above, a group holds too few start cells.
+// Subproblems must fit the grouping pass, the tile and the staged kernel
+// values the LDS.
+int mf_span(const Geom &g, int prec, int msub);
+// Dynamic LDS bytes of the matrix-core spreading kernel.
+size_t mf_lds_bytes(const Geom &g);
+// The processing order of those kernels (k_group), as launch_balance.
+hipError_t launch_group(const Geom &g, int prec, int span, int nsub_max, const int32_t *sub,
+                        const int32_t *nsub, const void *const u[3], const int32_t *perm,
+                        void *const v[3], int32_t *vperm, int32_t *spos, hipStream_t st);
 
 // Exclusive prefix sum of n uint32 values (in and out may alias).
 hipError_t scan_exclusive(const uint32_t *in, uint32_t *out, size_t n, uint32_t *partials,

@@ -749,6 +749,104 @@ k_balance(Geom g, const int32_t *__restrict__ sub, const int32_t *__restrict__ n
     }
 }
 
+// Processing order of the matrix-core kernels (mfma_kernels.h): the points of
+// a subproblem by window group, groups in x-fastest order, points of a group
+// in sorted order.  A group is the start cells (start / s) per dimension.  A
+// stable counting sort: each wave ranks a contiguous share of the points by
+// ballots over the group's bits, so the order (and the sums that follow it)
+// is the same in every run.  Bound by its traffic, as k_balance is.
+constexpr int kGroupMax = 256;
+template <typename T, int DIM, int ITEMS>
+__global__ void __launch_bounds__(kBalThreads)
+k_group(Geom g, int s, int3 ng, int bits, const int32_t *__restrict__ sub,
+        const int32_t *__restrict__ nsubp, const T *__restrict__ u0, const T *__restrict__ u1,
+        const T *__restrict__ u2, const int32_t *__restrict__ perm, T *__restrict__ v0,
+        T *__restrict__ v1, T *__restrict__ v2, int32_t *__restrict__ vperm,
+        int32_t *__restrict__ spos)
+{
+    constexpr int kLo = ITEMS == 8 ? 0 : 8 * kBalThreads;
+    constexpr int kHi = ITEMS == 8 ? 8 * kBalThreads : 16 * kBalThreads;
+    constexpr int kWaves = kBalThreads / 64;
+    __shared__ uint32_t cnt[kWaves][kGroupMax];
+    __shared__ uint32_t first[kGroupMax];
+    __shared__ __align__(16) unsigned char stage_raw[ITEMS * kBalThreads * sizeof(T)];
+    T *sT = reinterpret_cast<T *>(stage_raw);
+    int32_t *sI = reinterpret_cast<int32_t *>(stage_raw);
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+    const int nsub = *nsubp;
+    for (int q = blockIdx.x; q < nsub; q += gridDim.x) {
+        const int4 rec = reinterpret_cast<const int4 *>(sub)[q];
+        const int n = rec.z;
+        if (n <= kLo || n > kHi) continue;  // the other instantiation's subproblem
+        for (int e = tid; e < kWaves * kGroupMax; e += kBalThreads) (&cnt[0][0])[e] = 0u;
+        __syncthreads();
+        // wave w takes points w share .. (w + 1) share, 64 at a time
+        const int share = (n + kBalThreads - 1) / kBalThreads * 64;
+        T a[ITEMS], b[ITEMS], c[ITEMS];
+        int pm[ITEMS], pos[ITEMS], grp[ITEMS];
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it) {
+            const int i = rec.y + min(wave * share + it * 64 + lane, n - 1);
+            a[it] = u0[i];
+            b[it] = DIM >= 2 ? u1[i] : (T)0;
+            c[it] = DIM == 3 ? u2[i] : (T)0;
+            pm[it] = perm[i];
+        }
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it) {
+            const int j = wave * share + it * 64 + lane;
+            const bool valid = it * 64 < share && j < n;
+            int gr = start_cell_rt<T>(a[it], g.w) / s;
+            if (DIM >= 2) gr += ng.x * (start_cell_rt<T>(b[it], g.w) / s);
+            if (DIM == 3) gr += ng.x * ng.y * (start_cell_rt<T>(c[it], g.w) / s);
+            gr = min(max(gr, 0), kGroupMax - 1);
+            uint64_t mask = __ballot(valid);
+            for (int k = 0; k < bits; ++k) {
+                const bool bit = (gr >> k) & 1;
+                const uint64_t bb = __ballot(bit);
+                mask &= bit ? bb : ~bb;
+            }
+            const uint32_t rank = (uint32_t)__popcll(mask & lt);
+            uint32_t old = 0;
+            if (valid) {
+                old = cnt[wave][gr];
+                if (rank == 0) cnt[wave][gr] = old + (uint32_t)__popcll(mask);
+            }
+            grp[it] = gr;
+            pos[it] = (int)(old + rank);
+        }
+        __syncthreads();
+        if (tid < kGroupMax) {  // (kBalThreads == kGroupMax)
+            uint32_t run = 0;
+            for (int w = 0; w < kWaves; ++w) {
+                const uint32_t t = cnt[w][tid];
+                cnt[w][tid] = run;
+                run += t;
+            }
+            uint32_t ex;
+            block_excl_scan(run, ex);
+            first[tid] = ex;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it) pos[it] += (int)(first[grp[it]] + cnt[wave][grp[it]]);
+        const auto emit = [&](auto *stage, auto *dst, auto value) {
+#pragma unroll
+            for (int it = 0; it < ITEMS; ++it)
+                if (it * 64 < share && wave * share + it * 64 + lane < n) stage[pos[it]] = value(it);
+            __syncthreads();
+            for (int j = tid; j < n; j += kBalThreads) dst[rec.y + j] = stage[j];
+            __syncthreads();
+        };
+        emit(sT, v0, [&](int it) { return a[it]; });
+        if constexpr (DIM >= 2) emit(sT, v1, [&](int it) { return b[it]; });
+        if constexpr (DIM == 3) emit(sT, v2, [&](int it) { return c[it]; });
+        emit(sI, vperm, [&](int it) { return pm[it]; });
+        emit(sI, spos, [&](int it) { return rec.y + wave * share + it * 64 + lane; });
+    }
+}
+
 namespace {
 __global__ void k_iota(int n, int32_t *__restrict__ out)
 {
@@ -791,6 +889,31 @@ hipError_t launch_balance(const Geom &g, int prec, int nsub_max, const int32_t *
     }
 #undef MN_BAL
 #undef MN_BAL1
+    return hipGetLastError();
+}
+
+hipError_t launch_group(const Geom &g, int prec, int span, int nsub_max, const int32_t *sub,
+                        const int32_t *nsub, const void *const u[3], const int32_t *perm,
+                        void *const v[3], int32_t *vperm, int32_t *spos, hipStream_t st)
+{
+    if (nsub_max <= 0) return hipSuccess;
+    int ng[3];
+    int total = 1, bits = 0;
+    for (int d = 0; d < 3; ++d) {
+        ng[d] = d < g.dim ? (g.m[d] + 1) / span + 1 : 1;  // start cells 0 .. m + 1
+        total *= ng[d];
+    }
+    if (total > kGroupMax || g.dim != 3 || prec == 0) return hipErrorInvalidValue;
+    while ((1 << bits) < total) ++bits;
+    const dim3 grid(std::max(1, std::min(nsub_max, 256 * 8)));
+#define MN_GRP(II)                                                                           \
+    hipLaunchKernelGGL((k_group<double, 3, II>), grid, dim3(kBalThreads), 0, st, g, span,    \
+                       make_int3(ng[0], ng[1], ng[2]), bits, sub, nsub, (const double *)u[0], \
+                       (const double *)u[1], (const double *)u[2], perm, (double *)v[0],     \
+                       (double *)v[1], (double *)v[2], vperm, spos)
+    MN_GRP(8);
+    MN_GRP(16);
+#undef MN_GRP
     return hipGetLastError();
 }
 

@@ -74,6 +74,7 @@ struct mnufft_plan_s {
     void *scratch = nullptr;
     size_t scratch_bytes = 0;
     int ts2 = 0;
+    int mf = 0;                 // start cells per window group (matrix-core kernels), or 0
     int32_t *mergelist = nullptr, *nmerge = nullptr;
     int2 *cov[3] = {nullptr, nullptr, nullptr};
     void *cmax = nullptr;
@@ -171,8 +172,9 @@ void free_points(mnufft_plan p)
 }
 
 // SM plans in 2D and 3D process each subproblem's points in the bank-
-// balanced order of k_balance (kept in the *_proc arrays); 1D tiles are a
-// single row, where the sorted order does as well.
+// balanced order of k_balance, or for the matrix-core kernels the grouped
+// one of k_group (kept in the *_proc arrays); 1D tiles are a single row,
+// where the sorted order does as well.
 bool balanced(const mnufft_plan_s *p) { return p->method == MNUFFT_METHOD_SM && p->dim >= 2; }
 
 int alloc_points(mnufft_plan p, int64_t M)
@@ -200,7 +202,7 @@ int alloc_points(mnufft_plan p, int64_t M)
             for (int d = 0; d < p->dim; ++d)
                 if ((rc = dalloc(p, &p->su_proc[d], Ma * p->rsz))) return rc;
             if ((rc = dalloc(p, (void **)&p->perm_proc, Ma * 4))) return rc;
-            if ((rc = dalloc(p, (void **)&p->hslot_proc, Ma * 2))) return rc;
+            if (!p->mf && (rc = dalloc(p, (void **)&p->hslot_proc, Ma * 2))) return rc;
         }
         p->scratch_bytes = (size_t)std::max(p->nsub_cap, 1) * p->ts2 * p->rsz;
         if ((rc = dalloc(p, &p->scratch, p->scratch_bytes))) return rc;
@@ -342,6 +344,8 @@ mn::Pts kernel_points(mnufft_plan p, bool sorted)
         for (int d = 0; d < 3; ++d) P.u[d] = p->su_proc[d];
         P.perm = p->perm_proc;
         P.hslot = p->hslot_proc;
+        P.mf = p->mf;
+        P.work = p->nmerge + 2;
     }
     if (sorted && p->method == MNUFFT_METHOD_SM) P.spos = p->spos_proc;
     if (sorted) P.perm = nullptr;
@@ -352,7 +356,8 @@ size_t grid_bytes(mnufft_plan p) { return p->grid_elems * 2 * p->rsz; }
 
 // SM spreading with the two-word accumulator (double precision, and single
 // precision in 1D) needs max |c| before the tile kernel.
-bool needs_cmax(mnufft_plan p) { return p->prec == MNUFFT_F64 || p->dim == 1; }
+// (The matrix-core kernels accumulate in floating point.)
+bool needs_cmax(mnufft_plan p) { return (p->prec == MNUFFT_F64 || p->dim == 1) && !p->mf; }
 
 // Step 1 of type 1 for all ntransf vectors: c (ntransf x M) -> p->grid; c in
 // bin-sorted order when `sorted`.
@@ -476,8 +481,12 @@ int enqueue_setpts(mnufft_plan p, int64_t M, const void *x, const void *y, const
         MN_HIP(mn::launch_iota(p->spos_proc, (int)M, s));
     if (balanced(p)) {
         const void *su[3] = {p->su[0], p->su[1], p->su[2]};
-        MN_HIP(mn::launch_balance(g, p->prec, p->nsub_max, p->sub, p->nsub, su, p->perm,
-                                  p->su_proc, p->perm_proc, p->spos_proc, p->hslot_proc, s));
+        if (p->mf)
+            MN_HIP(mn::launch_group(g, p->prec, p->mf, p->nsub_max, p->sub, p->nsub, su, p->perm,
+                                    p->su_proc, p->perm_proc, p->spos_proc, s));
+        else
+            MN_HIP(mn::launch_balance(g, p->prec, p->nsub_max, p->sub, p->nsub, su, p->perm,
+                                      p->su_proc, p->perm_proc, p->spos_proc, p->hslot_proc, s));
     }
     return MNUFFT_OK;
 }
@@ -624,6 +633,7 @@ int plan_geometry(mnufft_plan p, const int64_t nf[3], int w, double beta, const 
     else
         p->method = o.method;
     if (p->method == MNUFFT_METHOD_SM && lds > kLdsMax) return MNUFFT_ERR_ARG;
+    p->mf = p->method == MNUFFT_METHOD_SM ? mn::mf_span(g, p->prec, p->msub) : 0;
     return MNUFFT_OK;
 }
 
@@ -637,7 +647,15 @@ int plan_bins_device(mnufft_plan p)
     // subproblem offsets (nbins + 1), then the add-back's list of bins (nbins)
     if (!rc) rc = dalloc(p, (void **)&p->subcount, (2 * (size_t)g.nbins + 1) * 4);
     if (!rc && p->method == MNUFFT_METHOD_SM) {
-        if (!p->nmerge) rc = dalloc(p, (void **)&p->nmerge, 16);
+        // [0] tiles to merge, [1] bins of the add-back's second pass, [2] and [3]
+        // work counters of the matrix-core kernels (zero between launches)
+        if (!p->nmerge) {
+            rc = dalloc(p, (void **)&p->nmerge, 16);
+            // (waited for: the plan may be moved to another stream)
+            if (!rc && (mn::launch_zero(p->nmerge, 16, p->stream) != hipSuccess ||
+                        hipStreamSynchronize(p->stream) != hipSuccess))
+                rc = MNUFFT_ERR_HIP;
+        }
         if (!rc && !p->cmax) rc = dalloc(p, &p->cmax, 1024 * 8);  // partial maxima, see k_maxabs
         for (int d = 0; d < p->dim && !rc; ++d) rc = build_cover(p, d);
     }

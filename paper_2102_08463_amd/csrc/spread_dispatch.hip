@@ -78,6 +78,25 @@ size_t sm_lds_bytes(const Geom &g, int prec, bool interp, int msub)
     return cells * 2 * rsz;
 }
 
+size_t mf_lds_bytes(const Geom &g)
+{
+    // the tile, then 32 staged points: 4 x 16 products of kernel values and
+    // strength and the window's origin each
+    return (size_t)sm_tile_stride(g) * 8 + 32 * (64 * 8 + 4);
+}
+
+int mf_span(const Geom &g, int prec, int msub)
+{
+    if (prec == 0 || g.dim != 3 || g.w < 8 || g.w > 14 || msub > 4096) return 0;
+    const int s = 17 - g.w;
+    int64_t groups = 1;
+    for (int d = 0; d < 3; ++d) {
+        if (g.m[d] + 2 * ((g.w + 1) / 2) > 255) return 0;  // origins are packed in bytes
+        groups *= (g.m[d] + 1) / s + 1;
+    }
+    return groups <= 256 && mf_lds_bytes(g) <= 160 * 1024 ? s : 0;
+}
+
 namespace {
 __global__ void k_merge_list(int nsub_max, const int32_t *__restrict__ nsubp,
                              const int32_t *__restrict__ sub, const int32_t *__restrict__ suboff,

@@ -64,10 +64,38 @@ __device__ __forceinline__ float es_val(float z, float bk)
     const float t = fmaxf(1.0f - z * z, 0.0f);
     return __builtin_amdgcn_exp2f(bk * (__builtin_amdgcn_sqrtf(t) - 1.0f));
 }
+// Double precision without the library calls' special cases, half their
+// instructions: the root by two Goldschmidt steps from the hardware's 24-bit
+// reciprocal root (1e-300 stands for a zero argument), the exponential of an
+// argument in [-60, 0] by its Taylor series about the nearest multiple of
+// ln 2 (r^14 / 14! < 5e-18 at |r| <= 0.347).
 __device__ __forceinline__ double es_val(double z, double bk)
 {
-    const double t = fmax(1.0 - z * z, 0.0);
-    return exp(bk * (sqrt(t) - 1.0));
+    const double t = fmax(fma(-z, z, 1.0), 1e-300);
+    const double y = __builtin_amdgcn_rsq(t);
+    double g = t * y, h = 0.5 * y;
+    const double r0 = fma(-h, g, 0.5);
+    g = fma(g, r0, g);
+    h = fma(h, r0, h);
+    g = fma(fma(-g, g, t), h, g);
+    const double x = fma(bk, g, -bk);
+    const double n = rint(x * 1.4426950408889634);
+    const double r = fma(-n, 1.90821492927058770002e-10, fma(-n, 6.93147180369123816490e-01, x));
+    double p = 1.0 / 6227020800.0;
+    p = fma(p, r, 1.0 / 479001600.0);
+    p = fma(p, r, 1.0 / 39916800.0);
+    p = fma(p, r, 1.0 / 3628800.0);
+    p = fma(p, r, 1.0 / 362880.0);
+    p = fma(p, r, 1.0 / 40320.0);
+    p = fma(p, r, 1.0 / 5040.0);
+    p = fma(p, r, 1.0 / 720.0);
+    p = fma(p, r, 1.0 / 120.0);
+    p = fma(p, r, 1.0 / 24.0);
+    p = fma(p, r, 1.0 / 6.0);
+    p = fma(p, r, 0.5);
+    p = fma(p, r, 1.0);
+    p = fma(p, r, 1.0);
+    return ldexp(p, (int)n);
 }
 
 // First tap index (as an integer) and the W kernel weights of a point at
@@ -1503,6 +1531,12 @@ hipError_t grad_dim(const Geom &g, const Pts &P, int ntransf, const void *grid, 
     return hipErrorInvalidValue;
 }
 
+// Double precision 3D on the matrix cores (mfma_kernels.h).
+template <int W>
+hipError_t spread_mf(const Geom &g, const Pts &P, const void *c, hipStream_t s);
+template <int W>
+hipError_t interp_mf(const Geom &g, const Pts &P, const void *grid, void *c, hipStream_t s);
+
 // part: bit 0 = accumulate (all methods), bit 1 = SM add-back (merge + gather),
 // bit 2 = SM max|c| pre-pass.  P.tg != nullptr selects the batched kernels.
 template <typename T, int DIM, int W, bool BATCH>
@@ -1515,11 +1549,20 @@ hipError_t spread_wb(const Geom &g, int method, const Pts &P, const void *c, voi
         // the packed single-precision kernel (2D / 3D) scales per subproblem
         // and needs no max|c|
         constexpr bool packed = std::is_same<T, float>::value && DIM >= 2;
-        if ((part & 4) && !packed) {
+        constexpr bool mf = std::is_same<T, double>::value && DIM == 3 && W >= 8 && W <= 14;
+        if ((part & 4) && !packed && !P.mf) {
             hipLaunchKernelGGL(k_maxabs<T>, dim3(std::max(1, std::min(cdiv(P.M, kThreads), kMaxParts))),
                                dim3(kThreads), 0, s, (const C *)c, P.M, (T *)P.cmax);
         }
-        if (part & 1) {
+        bool done = false;
+        if constexpr (mf && !BATCH) {
+            if ((part & 1) && P.mf) {
+                const hipError_t e = spread_mf<W>(g, P, c, s);
+                if (e != hipSuccess) return e;
+                done = true;
+            }
+        }
+        if ((part & 1) && !done) {
             if constexpr (packed) {
                 auto pk = k_spread_smp<T, DIM, W, BATCH>;
                 if (lds > 65536)
@@ -1607,6 +1650,9 @@ hipError_t interp_wb(const Geom &g, int method, const Pts &P, const void *grid, 
 {
     using C = typename Cplx<T>::type;
     const T bk = kernel_param<T>(g.beta);
+    if constexpr (std::is_same<T, double>::value && DIM == 3 && W >= 8 && W <= 14 && !BATCH) {
+        if (method == 3 && P.mf) return interp_mf<W>(g, P, grid, c, s);
+    }
     if (method == 3) {
         auto kern = k_interp_sm<T, DIM, W, BATCH>;
         if (lds > 65536)
