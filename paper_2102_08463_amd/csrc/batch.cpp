@@ -136,6 +136,7 @@ mn::Pts batch_points(mnufft_batch b)
     P.T = b->T;
     P.ncells = b->cells;
     P.bin_t = b->bin_t;
+    P.nt = 1;
     return P;
 }
 

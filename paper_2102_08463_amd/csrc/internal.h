@@ -181,6 +181,8 @@ struct Pts {
                               // (the points are in their order; 0: tap by tap)
     int *work;                // their work counters (spreading, interpolation), zero
                               // between launches
+    int nt;                   // stacked transforms of this launch (SM; at least 1)
+    size_t tile_stride;       // reals between their tiles in scratch
     // batches: per-transform geometry (device) and count; nullptr / 1 for a plain plan
     const TGeom *tg;
     int T;
@@ -289,13 +291,13 @@ hipError_t scan_exclusive(const uint32_t *in, uint32_t *out, size_t n, uint32_t 
                           hipStream_t s);
 
 // ---- spreading / interpolation (kernels_spread.hip) -----------------------
-// Spreading of c (one vector) with the given method.  part bit 0 runs the
+// Spreading of c (one vector, or P.nt stacked ones with method SM).  part bit 0 runs the
 // accumulation (GM / GMSORT: atomics into a zeroed grid; SM: per-subproblem
 // tiles), bit 1 the SM add-back that writes every grid cell, bit 2 the SM
 // pre-pass computing partial maxima of |c| into P.cmax (zeroed before it).
 hipError_t launch_spread(const Geom &g, int prec, int method, const Pts &P, const void *c,
                          void *grid, hipStream_t s, int part = 7);
-// c = interpolation of grid (one vector) with the given method.
+// c = interpolation of grid (one vector, or P.nt stacked ones with method SM).
 hipError_t launch_interp(const Geom &g, int prec, int method, const Pts &P, const void *grid,
                          void *c, hipStream_t s);
 // out_i[j] = sum_t Re(conj(wts[t][j]) d/dx_i (interpolation of grid t at x_j)),

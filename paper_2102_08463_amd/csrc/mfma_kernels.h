@@ -84,7 +84,7 @@ k_spread_mf(Geom g, const int32_t *__restrict__ sub, const int32_t *__restrict__
             const double *__restrict__ u0, const double *__restrict__ u1,
             const double *__restrict__ u2, const int32_t *__restrict__ idx,
             const double2 *__restrict__ c, double2 *__restrict__ scratch, int tcells, double bk,
-            int *__restrict__ work)
+            int *__restrict__ work, int nt, TStride tst)
 {
     __shared__ int next_item;
     const WorkQueue queue{work, &next_item};
@@ -98,15 +98,17 @@ k_spread_mf(Geom g, const int32_t *__restrict__ sub, const int32_t *__restrict__
     const int sl = lane & 15, kp = lane >> 4;
     const int p1 = g.m[0] + 2 * P, p2 = g.m[1] + 2 * P, p3 = g.m[2] + 2 * P;
     const int nsub = *nsubp;
-    for (int q = queue.next(nsub); q < nsub; q = queue.next(nsub)) {
+    for (int it = queue.next(nsub * nt); it < nsub * nt; it = queue.next(nsub * nt)) {
+        const int tr = it / nsub, q = it - tr * nsub;  // stacked transform, subproblem
         const int4 rec = reinterpret_cast<const int4 *>(sub)[q];
+        const double2 *ct = c + tr * tst.c;
         const int end = rec.y + rec.z;
         for (int e = tid; e < tcells; e += kMfThreads) tile[e] = make_double2(0.0, 0.0);
         // this thread's point of a chunk, clamped to the subproblem
         const auto at = [&](int i0) { return min(i0 + (tid >> 4), end - 1); };
         int ci = idx[at(rec.y)];
         double nu0 = u0[at(rec.y)], nu1 = u1[at(rec.y)], nu2 = u2[at(rec.y)];
-        double2 nc = c[ci];
+        double2 nc = ct[ci];
         ci = idx[at(rec.y + kMfPts)];
         d4 ar0 = {0, 0, 0, 0}, ai0 = {0, 0, 0, 0}, ar1 = {0, 0, 0, 0}, ai1 = {0, 0, 0, 0};
         int cur = -1, z0a = 0, z0b = 0;
@@ -151,7 +153,7 @@ k_spread_mf(Geom g, const int32_t *__restrict__ sub, const int32_t *__restrict__
             nu0 = u0[at(i0 + kMfPts)];
             nu1 = u1[at(i0 + kMfPts)];
             nu2 = u2[at(i0 + kMfPts)];
-            nc = c[ci];
+            nc = ct[ci];
             ci = idx[at(i0 + 2 * kMfPts)];
             __syncthreads();
             const int nv = min(kMfPts, end - i0);
@@ -194,7 +196,7 @@ k_spread_mf(Geom g, const int32_t *__restrict__ sub, const int32_t *__restrict__
         }
         flush();
         __syncthreads();
-        double2 *dst = scratch + (size_t)q * tcells;
+        double2 *dst = scratch + tr * (tst.tiles / 2) + (size_t)q * tcells;
         for (int e = tid; e < tcells; e += kMfThreads) dst[e] = tile[e];
     }
 }
@@ -211,7 +213,7 @@ k_interp_mf(Geom g, const int32_t *__restrict__ sub, const int32_t *__restrict__
             const double *__restrict__ u0, const double *__restrict__ u1,
             const double *__restrict__ u2, const int32_t *__restrict__ idx,
             const double2 *__restrict__ grid, double2 *__restrict__ c, double bk,
-            int *__restrict__ work)
+            int *__restrict__ work, int nt, TStride tst)
 {
     __shared__ int next_item;
     const WorkQueue queue{work, &next_item};
@@ -224,10 +226,12 @@ k_interp_mf(Geom g, const int32_t *__restrict__ sub, const int32_t *__restrict__
     const int nsub = *nsubp;
     // work item = kMfPart points of a subproblem (at most 4096 points, so most
     // of the later parts are empty)
-    const int items = 4096 / kMfPart * nsub;
+    const int items = 4096 / kMfPart * nsub * nt;
     for (int it = queue.next(items); it < items; it = queue.next(items)) {
-        const int part = it / nsub;
-        int4 rec = reinterpret_cast<const int4 *>(sub)[it - part * nsub];
+        const int pt = it / nsub, part = pt / nt, tr = pt - part * nt;
+        const double2 *gt = grid + tr * tst.grid;
+        double2 *ct = c + tr * tst.c;
+        int4 rec = reinterpret_cast<const int4 *>(sub)[it - pt * nsub];
         rec.y += part * kMfPart;
         rec.z = min(rec.z - part * kMfPart, kMfPart);
         if (rec.z <= 0) continue;
@@ -244,7 +248,7 @@ k_interp_mf(Geom g, const int32_t *__restrict__ sub, const int32_t *__restrict__
 #pragma unroll
                 for (int k = 0; k < kRows; ++k) {
                     const int r = min(r0 + k * kStep, rows - 1), s3 = r / p2, s2 = r - s3 * p2;
-                    v[k] = grid[((size_t)wrapmod(o3 + s3, g.n[2]) * g.n[1] +
+                    v[k] = gt[((size_t)wrapmod(o3 + s3, g.n[2]) * g.n[1] +
                                  wrapmod(o2 + s2, g.n[1])) * g.n[0] + l1];
                 }
 #pragma unroll
@@ -315,7 +319,7 @@ k_interp_mf(Geom g, const int32_t *__restrict__ sub, const int32_t *__restrict__
                 }
                 const int row = a + 4 * sl + kp;  // (sl < 4) the point of res
                 const int dst = __shfl(pj, min(row, 63), 64);
-                if (sl < 4 && row < b) c[dst] = res;
+                if (sl < 4 && row < b) ct[dst] = res;
                 a = b;
             }
         }
@@ -328,10 +332,11 @@ hipError_t spread_mf(const Geom &g, const Pts &P, const void *c, hipStream_t s)
     auto k = k_spread_mf<W>;
     const size_t lds = mf_lds_bytes(g);
     (void)hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL(k, dim3(std::max(1, std::min(P.nsub_max, kMfBlocks))), dim3(kMfThreads), lds, s, g, P.sub, P.nsub,
+    hipLaunchKernelGGL(k, dim3(kMfBlocks), dim3(kMfThreads), lds, s, g, P.sub, P.nsub,
                        (const double *)P.u[0], (const double *)P.u[1], (const double *)P.u[2],
                        sm_index(P), (const double2 *)c, (double2 *)P.scratch, P.ts2 / 2,
-                       kernel_param<double>(g.beta), P.work);
+                       kernel_param<double>(g.beta), P.work, P.nt,
+                       TStride{(size_t)P.M, (size_t)P.ncells, P.tile_stride});
     return hipGetLastError();
 }
 
@@ -344,7 +349,8 @@ hipError_t interp_mf(const Geom &g, const Pts &P, const void *grid, void *c, hip
     hipLaunchKernelGGL(k, dim3(kMfBlocks), dim3(kMfInterp), lds, s, g, P.sub, P.nsub,
                        (const double *)P.u[0], (const double *)P.u[1], (const double *)P.u[2],
                        sm_index(P), (const double2 *)grid, (double2 *)c,
-                       kernel_param<double>(g.beta), P.work + 1);
+                       kernel_param<double>(g.beta), P.work + 1, P.nt,
+                       TStride{(size_t)P.M, (size_t)P.ncells, 0});
     return hipGetLastError();
 }
 

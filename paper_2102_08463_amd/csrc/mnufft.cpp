@@ -21,6 +21,8 @@ namespace {
 
 constexpr double kPi = mn::host::kPi;
 constexpr size_t kLdsMax = 160 * 1024;  // LDS per workgroup on gfx950
+constexpr int64_t kMaxStack = 1024;     // stacked transforms per launch
+constexpr size_t kTileBytes = (size_t)256 << 20;  // tile scratch for several of them
 constexpr int kMergeGroup = 32;         // tiles summed per leader in heavy bins
 
 using mn::host::bits_for;
@@ -73,6 +75,7 @@ struct mnufft_plan_s {
     // SM spreading: tile slots, merge list and cover tables
     void *scratch = nullptr;
     size_t scratch_bytes = 0;
+    int nt_chunk = 1;           // stacked transforms whose tiles the scratch holds
     int ts2 = 0;
     int mf = 0;                 // start cells per window group (matrix-core kernels), or 0
     int32_t *mergelist = nullptr, *nmerge = nullptr;
@@ -204,7 +207,11 @@ int alloc_points(mnufft_plan p, int64_t M)
             if ((rc = dalloc(p, (void **)&p->perm_proc, Ma * 4))) return rc;
             if (!p->mf && (rc = dalloc(p, (void **)&p->hslot_proc, Ma * 2))) return rc;
         }
-        p->scratch_bytes = (size_t)std::max(p->nsub_cap, 1) * p->ts2 * p->rsz;
+        // tiles of as many stacked transforms as kTileBytes hold, at least one
+        const size_t one = (size_t)std::max(p->nsub_cap, 1) * p->ts2 * p->rsz;
+        p->nt_chunk = (int)std::max<size_t>(
+            1, std::min<size_t>(std::min<int64_t>(p->ntransf, kMaxStack), kTileBytes / one));
+        p->scratch_bytes = one * p->nt_chunk;
         if ((rc = dalloc(p, &p->scratch, p->scratch_bytes))) return rc;
         if ((rc = dalloc(p, (void **)&p->mergelist, (size_t)std::max(p->nsub_cap, 1) * 4)))
             return rc;
@@ -323,6 +330,8 @@ mn::Pts points_of(mnufft_plan p)
     P.heavy = p->method == MNUFFT_METHOD_SM ? p->subcount + p->g.nbins + 1 : nullptr;
     P.cmax = p->cmax;
     P.msub = p->msub;
+    P.nt = 1;
+    P.tile_stride = (size_t)std::max(p->nsub_cap, 1) * p->ts2;
     P.tg = nullptr;
     P.T = 1;
     P.ncells = (long long)p->grid_elems;
@@ -368,14 +377,17 @@ int spread_all(mnufft_plan p, const void *c, bool sorted = false)
         StageTimer tm(p->tm, MNUFFT_STAGE_ZERO, p->stream);
         MN_HIP(mn::launch_zero(p->grid, grid_bytes(p) * p->ntransf, p->stream));
     }
-    for (int64_t t = 0; t < p->ntransf; ++t) {
+    // method SM takes nt_chunk transforms per launch, the others one
+    const int64_t chunk = p->method == MNUFFT_METHOD_SM ? p->nt_chunk : 1;
+    for (int64_t t = 0; t < p->ntransf; t += chunk) {
         const char *ct = (const char *)c + (size_t)t * p->M * 2 * p->rsz;
         char *gt = (char *)p->grid + (size_t)t * grid_bytes(p);
+        P.nt = (int)std::min<int64_t>(chunk, p->ntransf - t);
         if (p->method == MNUFFT_METHOD_SM && needs_cmax(p)) {
             // max |c| for the two-word fixed-point scale (2D / 3D single
             // precision scales each subproblem inside the spreading kernel)
             StageTimer tm(p->tm, MNUFFT_STAGE_SCALE, p->stream);
-            MN_HIP(mn::launch_zero(p->cmax, 1024 * 8, p->stream));
+            MN_HIP(mn::launch_zero(p->cmax, (size_t)P.nt * 1024 * p->rsz, p->stream));
             MN_HIP(mn::launch_spread(p->g, p->prec, p->method, P, ct, gt, p->stream, 4));
         }
         {
@@ -405,9 +417,13 @@ int exec_type2(mnufft_plan p, int sign, const void *f, void *c, bool sorted = fa
     mn::Pts P = kernel_points(p, sorted);
     int rc = modes_to_grid(p, sign, f);
     if (rc) return rc;
-    for (int64_t t = 0; t < p->ntransf; ++t) {
+    // (their work items are counted in 32 bits)
+    const int64_t fit = std::max<int64_t>(1, ((int64_t)1 << 28) / std::max(p->nsub_max, 1));
+    const int64_t chunk = p->method == MNUFFT_METHOD_SM ? std::min(kMaxStack, fit) : 1;
+    for (int64_t t = 0; t < p->ntransf; t += chunk) {
         char *ct = (char *)c + (size_t)t * p->M * 2 * p->rsz;
         const char *gt = (const char *)p->grid + (size_t)t * grid_bytes(p);
+        P.nt = (int)std::min<int64_t>(chunk, p->ntransf - t);
         StageTimer tm(p->tm, MNUFFT_STAGE_INTERP, p->stream);
         MN_HIP(mn::launch_interp(p->g, p->prec, p->method, P, gt, ct, p->stream));
     }
@@ -656,7 +672,8 @@ int plan_bins_device(mnufft_plan p)
                         hipStreamSynchronize(p->stream) != hipSuccess))
                 rc = MNUFFT_ERR_HIP;
         }
-        if (!rc && !p->cmax) rc = dalloc(p, &p->cmax, 1024 * 8);  // partial maxima, see k_maxabs
+        if (!rc && !p->cmax)  // partial maxima, see k_maxabs
+            rc = dalloc(p, &p->cmax, (size_t)std::min<int64_t>(p->ntransf, kMaxStack) * 1024 * p->rsz);
         for (int d = 0; d < p->dim && !rc; ++d) rc = build_cover(p, d);
     }
     return rc;
@@ -1151,7 +1168,7 @@ int mnufft_spread(mnufft_plan p, const void *c, void *grid)
     if (!grid || (p->M > 0 && !c)) return MNUFFT_ERR_ARG;
     if ((rc = use_device(p))) return rc;
     if (p->method != MNUFFT_METHOD_SM) MN_HIP(mn::launch_zero(grid, grid_bytes(p), p->stream));
-    else if (needs_cmax(p)) MN_HIP(mn::launch_zero(p->cmax, 1024 * 8, p->stream));
+    else if (needs_cmax(p)) MN_HIP(mn::launch_zero(p->cmax, 1024 * p->rsz, p->stream));
     MN_HIP(mn::launch_spread(p->g, p->prec, p->method, kernel_points(p, false), c, grid, p->stream));
     return MNUFFT_OK;
 }

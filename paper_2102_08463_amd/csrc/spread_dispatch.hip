@@ -126,7 +126,7 @@ hipError_t launch_spread(const Geom &g, int prec, int method, const Pts &P, cons
     if (P.M == 0) {
         // nothing to accumulate; the SM add-back alone owns writing the grid
         if (method != 3 || !(part & 2)) return hipSuccess;
-        return launch_zero(grid, (size_t)P.ncells * 2 * (prec == 0 ? sizeof(float) : sizeof(double)),
+        return launch_zero(grid, (size_t)P.ncells * P.nt * 2 * (prec == 0 ? sizeof(float) : sizeof(double)),
                            s);
     }
     // the SM kernels reach every strength through an index array

@@ -275,6 +275,13 @@ k_interp_gm(Geom g, int M, const uint32_t *__restrict__ key, const T *__restrict
     c[perm ? perm[i] : i] = out;
 }
 
+// Distances between the vectors, grids and tiles (in reals) of stacked
+// transforms: the SM kernels take them over blockIdx.y (one launch, so that
+// one transform's last blocks run beside the next one's).
+struct TStride {
+    size_t c, grid, tiles;
+};
+
 // Partial maxima of max(|Re c_j|, |Im c_j|) for the fixed-point scale of
 // k_spread_sm: block b writes out[b]; the consumer takes the max over the
 // kMaxParts entries (blocks beyond the launch leave theirs at zero).
@@ -284,6 +291,8 @@ template <typename T>
 __global__ void __launch_bounds__(kThreads)
 k_maxabs(const typename Cplx<T>::type *__restrict__ c, int M, T *__restrict__ out)
 {
+    c += (size_t)blockIdx.y * M;  // transform
+    out += blockIdx.y * kMaxParts;
     T m = 0;
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < M; i += gridDim.x * blockDim.x) {
         const auto v = c[i];
@@ -483,11 +492,14 @@ k_spread_sm(Geom g, const int32_t *__restrict__ sub, const int32_t *__restrict__
             const typename Cplx<T>::type *__restrict__ c,
             const T *__restrict__ cmaxp, T *__restrict__ scratch, int ts2, int lts, T bk,
             int stage_cap, const TGeom *__restrict__ tg, const int32_t *__restrict__ bin_t,
-            const int32_t *__restrict__ q0p)
+            const int32_t *__restrict__ q0p, TStride tst)
 {
     using V = typename Vec16<T>::type;
     using C = typename Cplx<T>::type;
     constexpr int NV = 16 / sizeof(T);
+    c += blockIdx.y * tst.c;
+    scratch += blockIdx.y * tst.tiles;
+    cmaxp += blockIdx.y * kMaxParts;
     // LDS: the tile (lts words, the launch's largest), then the first
     // stage_cap strengths of the subproblem, gathered once by the histogram
     // pass and read again by the accumulation pass
@@ -645,8 +657,10 @@ k_spread_smp(Geom g, const int32_t *__restrict__ sub, const int32_t *__restrict_
              const uint16_t *__restrict__ hslot, const float2 *__restrict__ c,
              float *__restrict__ scratch, int ts2, int lts, float bk, int stage_cap,
              const TGeom *__restrict__ tg, const int32_t *__restrict__ bin_t,
-             const int32_t *__restrict__ q0p)
+             const int32_t *__restrict__ q0p, TStride tst)
 {
+    c += blockIdx.y * tst.c;
+    scratch += blockIdx.y * tst.tiles;
     static_assert(std::is_same<T, float>::value && DIM >= 2, "2D / 3D single precision only");
     constexpr int P = (W + 1) / 2;
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -856,10 +870,11 @@ template <typename T>
 __global__ void __launch_bounds__(kThreads)
 k_tile_merge(int32_t *__restrict__ nmergep, const int32_t *__restrict__ mergelist,
              const int32_t *__restrict__ sub, const int32_t *__restrict__ suboff,
-             T *__restrict__ scratch, int ts2, int G)
+             T *__restrict__ scratch, int ts2, int G, TStride tst)
 {
+    scratch += blockIdx.y * tst.tiles;
     // (nmergep[1] counts the bins the bin-wise add-back lists after this launch)
-    if (blockIdx.x == 0 && threadIdx.x == 0) nmergep[1] = 0;
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) nmergep[1] = 0;
     using V = typename Vec16<T>::type;
     constexpr int NV = 16 / sizeof(T);
     const int nvec = ts2 / NV;
@@ -890,8 +905,10 @@ k_tile_gather(Geom g, const int32_t *__restrict__ suboff, const T *__restrict__ 
               int ts2, int G, const int2 *__restrict__ cov0_, const int2 *__restrict__ cov1_,
               const int2 *__restrict__ cov2_, int k0_, int k1_, int k2_, int P,
               typename Cplx<T>::type *__restrict__ grid, long long ncell_all,
-              const TGeom *__restrict__ tg, int T_)
+              const TGeom *__restrict__ tg, int T_, TStride tst)
 {
+    scratch += blockIdx.y * tst.tiles;
+    grid += blockIdx.y * tst.grid;
     __shared__ long long soff[BATCH ? kTCache : 1];
     const auto fld = [](const TGeom &a) { return a.grid_off; };
     bool cached = false;
@@ -966,8 +983,10 @@ k_tile_gather2(Geom g, const int32_t *__restrict__ suboff, const T *__restrict__
                int ts2, int G, const int2 *__restrict__ cov0_, const int2 *__restrict__ cov1_,
                const int2 *__restrict__ cov2_, int k0_, int k1_, int k2_, int P,
                typename Cplx<T>::type *__restrict__ grid, long long ncell,
-               const TGeom *__restrict__ tg, int T_)
+               const TGeom *__restrict__ tg, int T_, TStride tst)
 {
+    scratch += blockIdx.y * tst.tiles;
+    grid += blockIdx.y * tst.grid;
     constexpr int NY = DIM >= 2 ? 2 : 1, NZ = DIM == 3 ? 2 : 1, NC = 2 * NY * NZ;
     __shared__ long long soff[BATCH ? kTCache : 1];
     const auto fld = [](const TGeom &a) { return a.grid_off; };
@@ -1072,8 +1091,10 @@ template <typename T, int DIM, bool HEAVY>
 __global__ void __launch_bounds__(kThreads)
 k_tile_sum(Geom g, const int32_t *__restrict__ suboff, const T *__restrict__ scratch, int ts2,
            int G, int P, typename Cplx<T>::type *__restrict__ grid, int32_t *__restrict__ heavy,
-           int32_t *__restrict__ cnt)
+           int32_t *__restrict__ cnt, TStride tst)
 {
+    scratch += blockIdx.y * tst.tiles;
+    grid += blockIdx.y * tst.grid;
     using C = typename Cplx<T>::type;
     constexpr int NB = DIM == 3 ? 27 : 9;
     constexpr int NC = DIM == 3 ? 8 : 4;   // tile combinations per cell, at most
@@ -1115,7 +1136,8 @@ k_tile_sum(Geom g, const int32_t *__restrict__ suboff, const T *__restrict__ scr
 #pragma unroll
             for (int l = 0; l < NB; ++l) several = several || scnt[l] > 1;
             if (several) {  // the same for the whole workgroup
-                if (threadIdx.x == 0) heavy[atomicAdd(&cnt[1], 1)] = b;
+                // (one list serves every transform)
+                if (threadIdx.x == 0 && blockIdx.y == 0) heavy[atomicAdd(&cnt[1], 1)] = b;
                 continue;
             }
         }
@@ -1231,8 +1253,10 @@ k_interp_sm(Geom g, const int32_t *__restrict__ sub, const int32_t *__restrict__
             const T *__restrict__ u0, const T *__restrict__ u1, const T *__restrict__ u2,
             const int32_t *__restrict__ idx, const typename Cplx<T>::type *__restrict__ grid_,
             typename Cplx<T>::type *__restrict__ c, T bk, const TGeom *__restrict__ tg,
-            const int32_t *__restrict__ bin_t, const int32_t *__restrict__ q0p)
+            const int32_t *__restrict__ bin_t, const int32_t *__restrict__ q0p, TStride tst)
 {
+    grid_ += blockIdx.y * tst.grid;
+    c += blockIdx.y * tst.c;
     using C = typename Cplx<T>::type;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     C *tile = reinterpret_cast<C *>(smem_raw);
@@ -1545,13 +1569,14 @@ hipError_t spread_wb(const Geom &g, int method, const Pts &P, const void *c, voi
 {
     using C = typename Cplx<T>::type;
     const T bk = kernel_param<T>(g.beta);
+    const TStride tst{(size_t)P.M, (size_t)P.ncells, P.tile_stride};
     if (method == 3) {
         // the packed single-precision kernel (2D / 3D) scales per subproblem
         // and needs no max|c|
         constexpr bool packed = std::is_same<T, float>::value && DIM >= 2;
         constexpr bool mf = std::is_same<T, double>::value && DIM == 3 && W >= 8 && W <= 14;
         if ((part & 4) && !packed && !P.mf) {
-            hipLaunchKernelGGL(k_maxabs<T>, dim3(std::max(1, std::min(cdiv(P.M, kThreads), kMaxParts))),
+            hipLaunchKernelGGL(k_maxabs<T>, dim3(std::max(1, std::min(cdiv(P.M, kThreads), kMaxParts)), P.nt),
                                dim3(kThreads), 0, s, (const C *)c, P.M, (T *)P.cmax);
         }
         bool done = false;
@@ -1568,30 +1593,30 @@ hipError_t spread_wb(const Geom &g, int method, const Pts &P, const void *c, voi
                 if (lds > 65536)
                     (void)hipFuncSetAttribute((const void *)pk,
                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-                hipLaunchKernelGGL(pk, dim3(sm_grid(P)), dim3(kThreads), lds, s, g, P.sub,
+                hipLaunchKernelGGL(pk, dim3(sm_grid(P), P.nt), dim3(kThreads), lds, s, g, P.sub,
                                    P.nsub, (const float *)P.u[0], (const float *)P.u[1],
                                    (const float *)P.u[2], sm_index(P), P.hslot, (const float2 *)c,
                                    (float *)P.scratch, P.ts2, sm_tile_stride(g), (float)bk,
-                                   smp_stage(DIM, P.msub), P.tg, P.bin_t, P.q0);
+                                   smp_stage(DIM, P.msub), P.tg, P.bin_t, P.q0, tst);
             } else {
                 auto kern = k_spread_sm<T, DIM, W, BATCH>;
                 if (lds > 65536)
                     (void)hipFuncSetAttribute((const void *)kern,
                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-                hipLaunchKernelGGL(kern, dim3(sm_grid(P)), dim3(kThreads), lds, s, g, P.sub,
-                                   P.nsub, (const T *)P.u[0], (const T *)P.u[1], (const T *)P.u[2],
+                hipLaunchKernelGGL(kern, dim3(sm_grid(P), P.nt), dim3(kThreads), lds, s, g,
+                                   P.sub, P.nsub, (const T *)P.u[0], (const T *)P.u[1], (const T *)P.u[2],
                                    sm_index(P), P.hslot, (const C *)c, (const T *)P.cmax,
                                    (T *)P.scratch, P.ts2, sm_tile_stride(g), bk,
                                    sm2_stage(DIM, sizeof(T) == 4 ? 0 : 1, P.msub), P.tg,
-                                   P.bin_t, P.q0);
+                                   P.bin_t, P.q0, tst);
             }
         }
         if (!(part & 2)) return hipGetLastError();
         const int nvec = P.ts2 / (16 / (int)sizeof(T));
         const int nchunk = (nvec + kThreads - 1) / kThreads;
         const int mgrid = std::max(1, std::min(P.nsub_max / std::max(P.G, 1) * nchunk + nchunk, 8192));
-        hipLaunchKernelGGL(k_tile_merge<T>, dim3(mgrid), dim3(kThreads), 0, s, P.nmerge,
-                           P.mergelist, P.sub, P.suboff, (T *)P.scratch, P.ts2, P.G);
+        hipLaunchKernelGGL(k_tile_merge<T>, dim3(mgrid, P.nt), dim3(kThreads), 0, s, P.nmerge,
+                           P.mergelist, P.sub, P.suboff, (T *)P.scratch, P.ts2, P.G, tst);
         if constexpr (!BATCH && DIM >= 2) {
             bool wide = true;  // every bin, the last one included, two halos wide
             for (int d = 0; d < DIM; ++d) {
@@ -1600,13 +1625,13 @@ hipError_t spread_wb(const Geom &g, int method, const Pts &P, const void *c, voi
             }
             if (wide && P.heavy) {
                 // bins of one tile per neighbourhood, then the listed others
-                hipLaunchKernelGGL((k_tile_sum<T, DIM, false>), dim3(std::min(g.nbins, 1 << 20)),
+                hipLaunchKernelGGL((k_tile_sum<T, DIM, false>), dim3(std::min(g.nbins, 1 << 20), P.nt),
                                    dim3(kThreads), 0, s, g, P.suboff, (const T *)P.scratch,
-                                   P.ts2, P.G, (W + 1) / 2, (C *)grid, P.heavy, P.nmerge);
+                                   P.ts2, P.G, (W + 1) / 2, (C *)grid, P.heavy, P.nmerge, tst);
                 hipLaunchKernelGGL((k_tile_sum<T, DIM, true>),
-                                   dim3(std::min(g.nbins * kSlices, 2048)), dim3(kThreads), 0, s,
+                                   dim3(std::min(g.nbins * kSlices, 2048), P.nt), dim3(kThreads), 0, s,
                                    g, P.suboff, (const T *)P.scratch, P.ts2, P.G, (W + 1) / 2,
-                                   (C *)grid, P.heavy, P.nmerge);
+                                   (C *)grid, P.heavy, P.nmerge, tst);
                 return hipGetLastError();
             }
         }
@@ -1614,16 +1639,16 @@ hipError_t spread_wb(const Geom &g, int method, const Pts &P, const void *c, voi
         const int ggrid = (int)std::min<long long>((ncell + kThreads - 1) / kThreads, 16384);
         // (for a batch, P.kmax holds the largest table width over its transforms)
         if (P.kmax[0] <= 2 && (DIM == 1 || P.kmax[1] <= 2) && (DIM <= 2 || P.kmax[2] <= 2)) {
-            hipLaunchKernelGGL((k_tile_gather2<T, DIM, BATCH>), dim3(std::max(ggrid, 1)),
+            hipLaunchKernelGGL((k_tile_gather2<T, DIM, BATCH>), dim3(std::max(ggrid, 1), P.nt),
                                dim3(kThreads), 0, s, g, P.suboff, (const T *)P.scratch, P.ts2,
                                P.G, P.cov[0], P.cov[1], P.cov[2], P.kmax[0], P.kmax[1],
-                               P.kmax[2], (W + 1) / 2, (C *)grid, ncell, P.tg, P.T);
+                               P.kmax[2], (W + 1) / 2, (C *)grid, ncell, P.tg, P.T, tst);
             return hipGetLastError();
         }
-        hipLaunchKernelGGL((k_tile_gather<T, DIM, BATCH>), dim3(std::max(ggrid, 1)), dim3(kThreads),
+        hipLaunchKernelGGL((k_tile_gather<T, DIM, BATCH>), dim3(std::max(ggrid, 1), P.nt), dim3(kThreads),
                            0, s, g, P.suboff, (const T *)P.scratch, P.ts2, P.G, P.cov[0], P.cov[1],
                            P.cov[2], P.kmax[0], P.kmax[1], P.kmax[2], (W + 1) / 2, (C *)grid, ncell,
-                           P.tg, P.T);
+                           P.tg, P.T, tst);
     } else if (part & 1) {
         const bool gm = method == 1;
         hipLaunchKernelGGL((k_spread_gm<T, DIM, W>), dim3(cdiv(P.M, kThreads)), dim3(kThreads),
@@ -1658,9 +1683,10 @@ hipError_t interp_wb(const Geom &g, int method, const Pts &P, const void *grid, 
         if (lds > 65536)
             (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
                                       (int)lds);
-        hipLaunchKernelGGL(kern, dim3(sm_grid(P)), dim3(kThreads), lds, s, g, P.sub, P.nsub,
-                           (const T *)P.u[0], (const T *)P.u[1], (const T *)P.u[2], sm_index(P),
-                           (const C *)grid, (C *)c, bk, P.tg, P.bin_t, P.q0);
+        hipLaunchKernelGGL(kern, dim3(sm_grid(P), P.nt), dim3(kThreads), lds, s, g, P.sub,
+                           P.nsub, (const T *)P.u[0], (const T *)P.u[1], (const T *)P.u[2],
+                           sm_index(P), (const C *)grid, (C *)c, bk, P.tg, P.bin_t, P.q0,
+                           TStride{(size_t)P.M, (size_t)P.ncells, 0});
     } else {
         const bool gm = method == 1;
         hipLaunchKernelGGL((k_interp_gm<T, DIM, W>), dim3(cdiv(P.M, kThreads)), dim3(kThreads),
