@@ -29,6 +29,7 @@ UNITS = [
     ("mnufft.cpp", [], "mnufft.o"),
     ("host_common.cpp", [], "host_common.o"),
     ("batch.cpp", [], "batch.o"),
+    ("pool.cpp", [], "pool.o"),
     ("fft_plan.cpp", [], "fft_plan.o"),
     ("tune.cpp", [], "tune.o"),
     ("select.cpp", [], "select.o"),

@@ -89,10 +89,8 @@ int balloc(mnufft_batch b, void **p, size_t bytes)
 {
     *p = nullptr;
     if (bytes == 0) bytes = 16;
-    hipError_t e = hipMalloc(p, bytes);
+    const hipError_t e = mn::host::pool_alloc(p, bytes);
     if (e != hipSuccess) {
-        *p = nullptr;
-        (void)hipGetLastError();
         return e == hipErrorOutOfMemory ? MNUFFT_ERR_ALLOC : MNUFFT_ERR_HIP;
     }
     b->allocs.push_back(*p);
@@ -260,7 +258,8 @@ int mnufft_batch_destroy(mnufft_batch b)
     }
     if (b->fork) (void)hipEventDestroy(b->fork);
     b->tm.destroy();
-    for (void *p : b->allocs) (void)hipFree(p);
+    if (rc != MNUFFT_OK) (void)hipDeviceSynchronize();  // nothing in use goes to the pool
+    for (void *p : b->allocs) mn::host::pool_free(p);
     delete b;
     return rc;
 }
@@ -316,7 +315,7 @@ int mnufft_batch_makeplan(int type, int dim, int ntr, const int64_t *nmodes, con
     b->g.pad = (w + 1) / 2;
     const int P = b->g.pad;
     b->geo.resize(ntr);
-    std::vector<double> pf[3];
+    int64_t pf[3] = {0, 0, 0};  // correction factors per dimension
     std::vector<int2> cv[3];
     int64_t bin_off = 0, pt_off = 0, grid_off = 0, mode_off = 0, nsub_max = 0;
     int mmax[3] = {1, 1, 1};
@@ -347,11 +346,8 @@ int mnufft_batch_makeplan(int type, int dim, int ntr, const int64_t *nmodes, con
             nb *= tg.B[d];
             mmax[d] = std::max(mmax[d], m);
             // correction factors (third dimension of a 2D batch: a single 1)
-            std::vector<double> fac;
-            if (d < dim) mn::host::correction(N, n, w, beta, fac);
-            else fac.assign(1, 1.0);
-            tg.p_off[d] = (int)pf[d].size();
-            pf[d].insert(pf[d].end(), fac.begin(), fac.end());
+            tg.p_off[d] = (int)pf[d];
+            pf[d] += N;
             std::vector<int2> tab;
             int km = 1;
             if (d < dim) mn::host::cover_table((int)n, m, tg.B[d], P, tab, km);
@@ -441,13 +437,13 @@ int mnufft_batch_makeplan(int type, int dim, int ntr, const int64_t *nmodes, con
     }
     if (!rc) rc = balloc(b, &b->grid, (size_t)b->cells * 2 * b->rsz);
     for (int d = 0; d < 3 && !rc; ++d) {
-        rc = balloc(b, &b->pfac[d], pf[d].size() * b->rsz);
-        if (rc) break;
-        if (prec == MNUFFT_F32) {
-            std::vector<float> ff(pf[d].begin(), pf[d].end());
-            rc = upload(b->pfac[d], ff.data(), ff.size() * 4);
-        } else {
-            rc = upload(b->pfac[d], pf[d].data(), pf[d].size() * 8);
+        rc = balloc(b, &b->pfac[d], (size_t)pf[d] * b->rsz);
+        for (int t = 0; t < ntr && !rc; ++t) {
+            const mn::TGeom &tg = b->geo[t];
+            if (mn::launch_correction(prec, tg.N[d], d < dim ? tg.n[d] : 0, w, beta,
+                                      (char *)b->pfac[d] + (size_t)tg.p_off[d] * b->rsz,
+                                      b->stream) != hipSuccess)
+                rc = MNUFFT_ERR_HIP;
         }
         if (!rc) rc = balloc(b, (void **)&b->cov[d], cv[d].size() * sizeof(int2));
         if (!rc) rc = upload(b->cov[d], cv[d].data(), cv[d].size() * sizeof(int2));

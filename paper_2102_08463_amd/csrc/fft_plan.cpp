@@ -256,8 +256,6 @@ int FftPlan::make(int dim, const int64_t *N, const int *n, int64_t nt, int prec_
             for (FftStep &st : d)
                 if (st.p.tw4) st.p.tw4 = t;
     }
-    // the tables are used on whatever stream the plan is moved to
-    if (hipStreamSynchronize(s) != hipSuccess) return MNUFFT_ERR_HIP;
     work_cells = fourA ? n[0] * nt : 0;
     ok = true;
     return MNUFFT_OK;

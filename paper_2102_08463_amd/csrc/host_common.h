@@ -58,6 +58,11 @@ int bits_for(int64_t nbins);
 // periodic wrapping; rows padded to the largest count kmax with bin -1.
 void cover_table(int n, int m, int B, int P, std::vector<int2> &tab, int &kmax);
 
+// Device memory from and to the pool (pool.cpp), on the current device.  The
+// device must no longer use a block that is freed.
+hipError_t pool_alloc(void **ptr, size_t bytes);
+void pool_free(void *ptr);
+
 // Per-stage HIP-event timers on one stream.
 struct Timers {
     bool on = false;
@@ -94,7 +99,7 @@ struct FftPlan {
     int prec = 0;
     std::vector<FftStep> dir[2];   // type 1, type 2
     int64_t work_cells = 0;        // workspace of type 2 (1D, two-pass), complex values
-    // Tables are allocated with `alloc` and filled on s (which is waited for).
+    // Tables are allocated with `alloc` and filled on s (the caller waits).
     int make(int dim, const int64_t *N, const int *n, int64_t nt, int prec_,
              const void *const pf[3], const FftAlloc &alloc, hipStream_t s);
     // type 1: grid (overwritten) -> modes; type 2: modes -> grid.

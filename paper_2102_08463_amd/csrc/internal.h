@@ -330,6 +330,17 @@ inline int sm2_stage(int dim, int prec, int msub)
 }
 // Reals per scratch tile slot of SM spreading.
 int sm_tile_stride(const Geom &g);
+// Whether the SM add-back goes bin by bin: 2D and 3D grids whose bins, the
+// narrower last one of a dimension included, are all at least two halos wide.
+// (Others gather per cell through the cover tables.)
+inline bool wide_bins(const Geom &g)
+{
+    for (int d = 0; d < g.dim; ++d) {
+        const int last = g.n[d] - (g.B[d] - 1) * g.m[d];
+        if ((g.m[d] < last ? g.m[d] : last) < 2 * g.pad) return false;
+    }
+    return g.dim >= 2;
+}
 // Leaders of tile groups to merge: subproblems q with (q - suboff[bin]) % G == 0
 // in bins with more than G subproblems (*nmerge must be zero on entry).
 hipError_t launch_merge_list(int nsub_max, const int32_t *nsub, const int32_t *sub,
@@ -337,6 +348,9 @@ hipError_t launch_merge_list(int nsub_max, const int32_t *nsub, const int32_t *s
                              hipStream_t s);
 
 // ---- correction (kernels_deconv.hip) --------------------------------------
+// out[i] = factor of mode i - floor(N/2) for i < N (ones when n = 0), plan precision.
+hipError_t launch_correction(int prec, int64_t N, int n, int w, double beta, void *out,
+                             hipStream_t s);
 // f[t] = p1 p2 p3 * grid[t][k mod n] over the modes, for ntransf transforms.
 hipError_t launch_deconv(int dim, const int64_t N[3], const int n[3], int prec, int ntransf,
                          const void *grid, const void *const p[3], void *f, hipStream_t s);

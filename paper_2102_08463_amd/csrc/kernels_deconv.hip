@@ -159,6 +159,43 @@ k_precorrect_batch(const TGeom *__restrict__ tg, int T_, long long ncells,
     }
 }
 
+// Correction factors p_k = (2/w) / phi_hat(alpha k) (-1)^k of one dimension
+// (Sec. II-A step 3), by the quadrature of host::es_fourier (tanh-sinh, 513
+// nodes), a wave per mode; n = 0 (an absent dimension) gives ones.  On the
+// host the cosines took most of a plan's creation (64^3: 0.7 ms, 2^20: 4 s).
+constexpr int kNodes = 513;
+template <typename T>
+__global__ void __launch_bounds__(kThreads)
+k_correction(int N, int n, int w, double beta, T *__restrict__ out)
+{
+    __shared__ double zz[kNodes], ww[kNodes];
+    const double pi = 3.141592653589793;
+    for (int q = threadIdx.x; q < kNodes; q += kThreads) {
+        const double t = (q - kNodes / 2) / 64.0, u = 0.5 * pi * sinh(t);
+        const double one_minus_z = 1.0 / (1.0 + exp(2.0 * u)), z = 1.0 - one_minus_z;
+        const double ch = cosh(u), dz = 0.25 * pi * cosh(t) / (ch * ch);
+        const double s = one_minus_z * (1.0 + z);  // 1 - z^2 without cancellation
+        zz[q] = z;
+        ww[q] = dz / 64.0 * exp(beta * (sqrt(fmax(s, 0.0)) - 1.0));
+    }
+    __syncthreads();
+    const int lane = threadIdx.x & 63;
+    for (int i = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6); i < N;
+         i += gridDim.x * (kThreads / 64)) {
+        if (n == 0) {
+            if (lane == 0) out[i] = (T)1;
+            continue;
+        }
+        const int k = i - N / 2;
+        const double xi = w * pi / (double)n * (double)k;
+        double acc = 0.0;
+        for (int q = lane; q < kNodes; q += 64) acc += ww[q] * cos(xi * zz[q]);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
+        if (lane == 0) out[i] = (T)((2.0 / w) / (2.0 * acc) * (k % 2 == 0 ? 1.0 : -1.0));
+    }
+}
+
 template <typename V>
 __global__ void k_zero(V *__restrict__ p, size_t nv, unsigned char *__restrict__ tail, int ntail)
 {
@@ -240,6 +277,18 @@ hipError_t launch_precorrect_batch(const TGeom *tg, int T, long long ncells, int
         hipLaunchKernelGGL(k_precorrect_batch<double>, dim3(blocks), dim3(kThreads), 0, s, tg, T,
                            ncells, (const double2 *)f, (const double *)p[0], (const double *)p[1],
                            (const double *)p[2], (double2 *)grid);
+    return hipGetLastError();
+}
+
+hipError_t launch_correction(int prec, int64_t N, int n, int w, double beta, void *out,
+                             hipStream_t s)
+{
+    const dim3 grd((unsigned)std::min<int64_t>((N + 3) / 4, 16384)), blk(kThreads);
+    if (prec == 0)
+        hipLaunchKernelGGL(k_correction<float>, grd, blk, 0, s, (int)N, n, w, beta, (float *)out);
+    else
+        hipLaunchKernelGGL(k_correction<double>, grd, blk, 0, s, (int)N, n, w, beta,
+                           (double *)out);
     return hipGetLastError();
 }
 

@@ -48,6 +48,7 @@ struct mnufft_plan_s {
     int device = -1;
     int validate = 0;
     hipStream_t stream = nullptr;
+    bool moved = false;         // work may also be pending on an earlier stream
     size_t rsz = 4;             // bytes per real of the plan precision
     size_t grid_elems = 0;      // complex cells per transform
     void *grid = nullptr;       // ntransf fine grids
@@ -119,20 +120,24 @@ int dalloc(mnufft_plan p, void **ptr, size_t bytes)
 {
     *ptr = nullptr;
     if (bytes == 0) return MNUFFT_OK;
-    hipError_t e = hipMalloc(ptr, bytes);
-    if (e != hipSuccess) {
-        *ptr = nullptr;
-        (void)hipGetLastError();
-        return e == hipErrorOutOfMemory ? MNUFFT_ERR_ALLOC : MNUFFT_ERR_HIP;
-    }
+    const hipError_t e = mn::host::pool_alloc(ptr, bytes);
+    if (e != hipSuccess) return e == hipErrorOutOfMemory ? MNUFFT_ERR_ALLOC : MNUFFT_ERR_HIP;
     p->devbytes += (int64_t)bytes;
     return MNUFFT_OK;
+}
+
+// Waits until the device is done with the plan's buffers, before any goes
+// back to the pool.
+int quiesce(mnufft_plan p)
+{
+    if (!p->moved && hipStreamSynchronize(p->stream) == hipSuccess) return MNUFFT_OK;
+    return hipDeviceSynchronize() == hipSuccess ? MNUFFT_OK : MNUFFT_ERR_HIP;
 }
 
 void dfree(mnufft_plan p, void **ptr, size_t bytes)
 {
     if (*ptr) {
-        (void)hipFree(*ptr);
+        mn::host::pool_free(*ptr);
         p->devbytes -= (int64_t)bytes;
     }
     *ptr = nullptr;
@@ -147,6 +152,7 @@ int use_device(mnufft_plan p)
 void free_points(mnufft_plan p)
 {
     if (p->Mcap < 0) return;
+    (void)quiesce(p);
     const size_t M = (size_t)std::max<int64_t>(p->Mcap, 1);
     for (int d = 0; d < 3; ++d) {
         dfree(p, &p->su[d], M * p->rsz);
@@ -246,6 +252,7 @@ int make_fft(mnufft_plan p, int type, int sign)
         p->fft[which] = (rocfft_plan)pl;
     }
     if (wb > p->fftwork_bytes) {
+        if (p->fftwork) (void)quiesce(p);
         dfree(p, &p->fftwork, p->fftwork_bytes);
         p->fftwork_bytes = 0;
         const int rc = dalloc(p, &p->fftwork, wb);
@@ -515,6 +522,7 @@ int plan_bins_device(mnufft_plan p);
 // tables and makes them again for the new bins.
 int replan(mnufft_plan p, const mnufft_opts &c)
 {
+    (void)quiesce(p);
     free_points(p);
     dfree(p, (void **)&p->binstart, ((size_t)p->g.nbins + 1) * 4);
     dfree(p, (void **)&p->subcount, (2 * (size_t)p->g.nbins + 1) * 4);
@@ -655,7 +663,7 @@ int plan_geometry(mnufft_plan p, const int64_t nf[3], int w, double beta, const 
 
 // The device state that depends on the bins: bin starts, per-bin subproblem
 // offsets and, for method SM, the merge counter, the max |c| partials and
-// the cover tables of the add-back.
+// the cover tables of the cell-wise add-back.
 int plan_bins_device(mnufft_plan p)
 {
     const mn::Geom &g = p->g;
@@ -667,14 +675,11 @@ int plan_bins_device(mnufft_plan p)
         // work counters of the matrix-core kernels (zero between launches)
         if (!p->nmerge) {
             rc = dalloc(p, (void **)&p->nmerge, 16);
-            // (waited for: the plan may be moved to another stream)
-            if (!rc && (mn::launch_zero(p->nmerge, 16, p->stream) != hipSuccess ||
-                        hipStreamSynchronize(p->stream) != hipSuccess))
-                rc = MNUFFT_ERR_HIP;
+            if (!rc && mn::launch_zero(p->nmerge, 16, p->stream) != hipSuccess) rc = MNUFFT_ERR_HIP;
         }
         if (!rc && !p->cmax)  // partial maxima, see k_maxabs
             rc = dalloc(p, &p->cmax, (size_t)std::min<int64_t>(p->ntransf, kMaxStack) * 1024 * p->rsz);
-        for (int d = 0; d < p->dim && !rc; ++d) rc = build_cover(p, d);
+        for (int d = 0; d < p->dim && !rc && !mn::wide_bins(g); ++d) rc = build_cover(p, d);
     }
     return rc;
 }
@@ -689,18 +694,10 @@ int plan_device(mnufft_plan p, bool with_fft)
     int rc = use_device(p);
     if (!rc) rc = dalloc(p, &p->grid, p->grid_elems * 2 * p->rsz * p->ntransf);
     for (int d = 0; d < 3 && !rc && with_fft; ++d) {
-        std::vector<double> fac;
-        if (d < dim) correction(p->N[d], g.n[d], g.w, g.beta, fac);
-        else fac.assign(1, 1.0);
-        rc = dalloc(p, &p->pfac[d], fac.size() * p->rsz);
-        if (rc) break;
-        if (p->prec == MNUFFT_F32) {
-            std::vector<float> ff(fac.begin(), fac.end());
-            if (hipMemcpy(p->pfac[d], ff.data(), ff.size() * 4, hipMemcpyHostToDevice))
-                rc = MNUFFT_ERR_HIP;
-        } else if (hipMemcpy(p->pfac[d], fac.data(), fac.size() * 8, hipMemcpyHostToDevice)) {
+        rc = dalloc(p, &p->pfac[d], (size_t)p->N[d] * p->rsz);
+        if (!rc && mn::launch_correction(p->prec, p->N[d], d < dim ? g.n[d] : 0, g.w, g.beta,
+                                         p->pfac[d], p->stream) != hipSuccess)
             rc = MNUFFT_ERR_HIP;
-        }
     }
     if (!rc) rc = dalloc(p, (void **)&p->nsub, 16);
     if (!rc) rc = dalloc(p, (void **)&p->flag, 16);
@@ -714,6 +711,8 @@ int plan_device(mnufft_plan p, bool with_fft)
         if (!rc) rc = p->own.make(dim, p->N, g.n, p->ntransf, p->prec, p->pfac, alloc, p->stream);
         if (!rc) rc = make_fft(p, p->type, p->iflag);
     }
+    // the tables filled above serve whatever stream the plan is moved to
+    if (!rc && hipStreamSynchronize(p->stream) != hipSuccess) rc = MNUFFT_ERR_HIP;
     return rc;
 }
 
@@ -808,6 +807,7 @@ bool reduce_bounds(const double *part, int nb, int dim, int n, double lo[3], dou
 
 void free_t3_points(mnufft_plan p)
 {
+    if (p->t3Mcap >= 0 || p->t3Kcap >= 0) (void)quiesce(p);
     const size_t cz = 2 * p->rsz;
     if (p->t3Mcap >= 0) {
         const size_t M = (size_t)std::max<int64_t>(p->t3Mcap, 1);
@@ -1245,6 +1245,7 @@ int mnufft_set_stream(mnufft_plan p, void *stream)
     }
     for (mnufft_plan q : {p, p->t3spr, p->t3inner}) {
         if (!q) continue;
+        q->moved = q->moved || q->stream != (hipStream_t)stream;
         q->stream = (hipStream_t)stream;
         q->opts.stream = stream;
     }
@@ -1327,6 +1328,7 @@ int mnufft_destroy(mnufft_plan p)
     int rc = MNUFFT_OK;
     if (p->device >= 0 && hipSetDevice(p->device) != hipSuccess) rc = MNUFFT_ERR_HIP;
     if (hipStreamSynchronize(p->stream) != hipSuccess) rc = MNUFFT_ERR_HIP;
+    if (quiesce(p)) rc = MNUFFT_ERR_HIP;
     for (int k = 0; k < 2; ++k)
         if (p->fft[k]) rocfft_plan_destroy(p->fft[k]);
     if (p->fftinfo) rocfft_execution_info_destroy(p->fftinfo);

@@ -1618,12 +1618,7 @@ hipError_t spread_wb(const Geom &g, int method, const Pts &P, const void *c, voi
         hipLaunchKernelGGL(k_tile_merge<T>, dim3(mgrid, P.nt), dim3(kThreads), 0, s, P.nmerge,
                            P.mergelist, P.sub, P.suboff, (T *)P.scratch, P.ts2, P.G, tst);
         if constexpr (!BATCH && DIM >= 2) {
-            bool wide = true;  // every bin, the last one included, two halos wide
-            for (int d = 0; d < DIM; ++d) {
-                const int last = g.n[d] - (g.B[d] - 1) * g.m[d];
-                wide = wide && std::min(g.m[d], last) >= 2 * ((W + 1) / 2);
-            }
-            if (wide && P.heavy) {
+            if (wide_bins(g) && P.heavy) {
                 // bins of one tile per neighbourhood, then the listed others
                 hipLaunchKernelGGL((k_tile_sum<T, DIM, false>), dim3(std::min(g.nbins, 1 << 20), P.nt),
                                    dim3(kThreads), 0, s, g, P.suboff, (const T *)P.scratch,
