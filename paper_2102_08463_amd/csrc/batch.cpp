@@ -521,11 +521,8 @@ int mnufft_batch_setpts(mnufft_batch b, const void *x, const void *y, const void
         b->perm = reinterpret_cast<int32_t *>(sv);
         if (mn::launch_binstart(M, b->nbins, b->skey, b->binstart, s)) return MNUFFT_ERR_HIP;
         if (mn::launch_subproblems(b->nbins, b->msub_max, b->nsub_max, b->binstart, b->subcount,
-                                   b->partials, b->sub, b->nsub, s, b->d_geo, b->T, b->bin_t))
-            return MNUFFT_ERR_HIP;
-        if (mn::launch_zero(b->nmerge, 4, s)) return MNUFFT_ERR_HIP;
-        if (mn::launch_merge_list(b->nsub_max, b->nsub, b->sub, b->subcount, kMergeGroup,
-                                  b->mergelist, b->nmerge, s))
+                                   b->partials, b->sub, b->nsub, kMergeGroup, b->mergelist,
+                                   b->nmerge, s, b->d_geo, b->T, b->bin_t))
             return MNUFFT_ERR_HIP;
     }
     b->pts_set = true;

@@ -254,10 +254,14 @@ hipError_t launch_binstart(int M, int nbins, const uint32_t *skey, int32_t *bins
                            hipStream_t s);
 
 // Subproblem list from bin starts; nsub_max = nbins + ceil(M / msub).
-// With a batch table, each bin uses its transform's msub.
+// With a batch table, each bin uses its transform's msub.  With a merge list
+// (method SM), *nmerge and mergelist receive the leaders of tile groups to
+// merge: subproblems q with (q - suboff[bin]) % G == 0 in bins with more than
+// G subproblems.
 hipError_t launch_subproblems(int nbins, int msub, int nsub_max, const int32_t *binstart,
                               int32_t *subcount, uint32_t *partials, int32_t *sub,
-                              int32_t *nsub, hipStream_t s, const TGeom *tg = nullptr, int T = 1,
+                              int32_t *nsub, int G, int32_t *mergelist, int32_t *nmerge,
+                              hipStream_t s, const TGeom *tg = nullptr, int T = 1,
                               const int32_t *bin_t = nullptr);
 
 // Processing order of the SM kernels within each subproblem (see k_balance):
@@ -341,11 +345,6 @@ inline bool wide_bins(const Geom &g)
     }
     return g.dim >= 2;
 }
-// Leaders of tile groups to merge: subproblems q with (q - suboff[bin]) % G == 0
-// in bins with more than G subproblems (*nmerge must be zero on entry).
-hipError_t launch_merge_list(int nsub_max, const int32_t *nsub, const int32_t *sub,
-                             const int32_t *suboff, int G, int32_t *mergelist, int32_t *nmerge,
-                             hipStream_t s);
 
 // ---- correction (kernels_deconv.hip) --------------------------------------
 // out[i] = factor of mode i - floor(N/2) for i < N (ones when n = 0), plan precision.

@@ -17,6 +17,7 @@
 #include "internal.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace mn {
 namespace {
@@ -25,6 +26,14 @@ constexpr double kPi = 3.141592653589793;
 constexpr int kThreads = 256;
 constexpr int kItems = 16;
 constexpr int kTile = kThreads * kItems;  // keys per radix block
+constexpr int kTileSmall = 1024;          // the same for at most kSmallKeys keys, which
+constexpr int kSmallKeys = 1 << 20;       // would fill too few large blocks
+// Up to this many blocks each scatter block sums the digit counts it needs
+// itself (M = 1e5: the two scan launches took 9 us of a 55 us sort).
+constexpr int kFusedBlocks = 256;
+inline int tile_of(int M) { return M <= kSmallKeys ? kTileSmall : kTile; }
+// Distance between the digits' rows of counts.
+inline int hist_pitch(int nblk) { return nblk <= kFusedBlocks ? (nblk + 3) / 4 * 4 : nblk; }
 
 // Folded grid coordinate in [0, n).  `bad` is set when one period shift does
 // not bring the value into range (non-finite or beyond about [-3pi, 3pi)).
@@ -111,17 +120,38 @@ k_binkey(Geom g, int M, const T *__restrict__ x, const T *__restrict__ y,
     if (bad) atomicOr(flag, 1);
 }
 
+__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v, int lane)
+{
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t t = __shfl_up(v, o, 64);
+        if (lane >= o) v += t;
+    }
+    return v;
+}
+
+// A block's digit counts to column blockIdx.x; the last block also clears the
+// columns up to the row pitch.
+__device__ __forceinline__ void store_counts(const uint32_t *h, int pitch, uint32_t *hist)
+{
+    if (threadIdx.x >= 256) return;
+    uint32_t *row = hist + (int64_t)threadIdx.x * pitch;
+    row[blockIdx.x] = h[threadIdx.x];
+    if (blockIdx.x == gridDim.x - 1)
+        for (int k = gridDim.x; k < pitch; ++k) row[k] = 0u;
+}
+
 // Digit histogram of the first radix pass straight from the points (keys
 // computed as point_key does; the validation flag set as k_binkey sets it).
 // (1024 threads, kTile / 1024 points each: the key arithmetic is long, so
 // more points are in flight per tile than with k_radix_hist's layout)
 constexpr int kSrcThreads = 1024;
-constexpr int kSrcItems = kTile / kSrcThreads;
-template <typename T, bool BATCH>
+template <typename T, bool BATCH, int TILE>
 __global__ void __launch_bounds__(kSrcThreads)
-k_radix_hist_src(KeySrc src, int M, int shift, uint32_t dmask, int nblk,
+k_radix_hist_src(KeySrc src, int M, int shift, uint32_t dmask, int pitch,
                  uint32_t *__restrict__ hist)
 {
+    constexpr int kSrcItems = TILE / kSrcThreads;
     __shared__ uint32_t h[256];
     __shared__ long long soff[BATCH ? kTCache : 1];
     const int tid = threadIdx.x;
@@ -133,7 +163,7 @@ k_radix_hist_src(KeySrc src, int M, int shift, uint32_t dmask, int nblk,
         __syncthreads();
     const T *x = (const T *)src.x, *y = (const T *)src.y, *z = (const T *)src.z;
     const int dim = src.g.dim;
-    const int64_t base = (int64_t)blockIdx.x * kTile;
+    const int64_t base = (int64_t)blockIdx.x * TILE;
     int bad = 0;
     // every coordinate load first, so that their latencies overlap
     T xc[kSrcItems][3];
@@ -166,20 +196,22 @@ k_radix_hist_src(KeySrc src, int M, int shift, uint32_t dmask, int nblk,
     }
     if (bad) atomicOr(src.flag, 1);
     __syncthreads();
-    if (tid < 256) hist[(int64_t)tid * nblk + blockIdx.x] = h[tid];
+    store_counts(h, pitch, hist);
 }
 
-// Per-tile digit histogram, stored digit-major: hist[d * nblk + blk]; the
+// Per-tile digit histogram, stored digit-major: hist[d * pitch + blk]; the
 // digit is (key >> shift) & dmask with dmask + 1 <= 256.
+template <int TILE>
 __global__ void __launch_bounds__(kThreads)
-k_radix_hist(const uint32_t *__restrict__ keys, int M, int shift, uint32_t dmask, int nblk,
+k_radix_hist(const uint32_t *__restrict__ keys, int M, int shift, uint32_t dmask, int pitch,
              uint32_t *__restrict__ hist)
 {
+    constexpr int kItems = TILE / kThreads;
     __shared__ uint32_t h[256];
     const int tid = threadIdx.x;
     h[tid] = 0;
     __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * kTile;
+    const int64_t base = (int64_t)blockIdx.x * TILE;
     // every key load first, so that their latencies overlap
     uint32_t kv[kItems];
 #pragma unroll
@@ -203,7 +235,7 @@ k_radix_hist(const uint32_t *__restrict__ keys, int M, int shift, uint32_t dmask
         }
     }
     __syncthreads();
-    hist[(int64_t)tid * nblk + blockIdx.x] = h[tid];
+    store_counts(h, pitch, hist);
 }
 
 // Stable scatter of one radix pass over a tile of kTile keys, with NT
@@ -216,28 +248,30 @@ k_radix_hist(const uint32_t *__restrict__ keys, int M, int shift, uint32_t dmask
 // LDS (3D, or double precision) one workgroup fills a CU, and 1024 threads
 // hide its memory latency better than 512 (measured: 3D setpts 0.93 ->
 // 0.74 ms at M = 2^24).
-template <typename T, int ND>
+template <typename T, int ND, int TILE>
 constexpr int scatter_threads()
 {
-    return kTile * (8 + ND * (int)sizeof(T)) > 65536 ? 1024 : 512;
+    return TILE < kTile ? 256 : (TILE * (8 + ND * (int)sizeof(T)) > 65536 ? 1024 : 512);
 }
 
 // SRC: 0 reads keys and payload; 1 computes them from the points (src, a
 // plain plan); 2 the same for a batch (transform by binary search of pt_off).
-template <typename T, int ND, int SRC = 0, int NT = scatter_threads<T, ND>()>
+// offs holds the scanned counts or, with `sums`, the counts themselves.
+template <typename T, int ND, int SRC, int TILE, int NT = scatter_threads<T, ND, TILE>()>
 __global__ void __launch_bounds__(NT)
 k_radix_scatter(const uint32_t *__restrict__ kin, const uint32_t *__restrict__ vin, int M,
-                int shift, int dbits, int nblk, const uint32_t *__restrict__ offs,
+                int shift, int dbits, int pitch, bool sums, const uint32_t *__restrict__ offs,
                 uint32_t *__restrict__ kout, uint32_t *__restrict__ vout, Payload pl, KeySrc src)
 {
-    constexpr int kSWaves = NT / 64, kSItems = kTile / NT;
+    constexpr int kSWaves = NT / 64, kSItems = TILE / NT;
     __shared__ uint32_t cnt[kSWaves][256];   // running per-wave digit counts, then prefixes
     __shared__ uint32_t tstart[256];         // tile-local start of each digit run
     __shared__ uint32_t gbase[256];          // global start of each digit run
+    __shared__ uint32_t wsum[4], asum[4];
     extern __shared__ __align__(16) unsigned char stage_raw[];
     uint32_t *skey = reinterpret_cast<uint32_t *>(stage_raw);
-    uint32_t *sval = skey + kTile;
-    T *spay = reinterpret_cast<T *>(sval + kTile);
+    uint32_t *sval = skey + TILE;
+    T *spay = reinterpret_cast<T *>(sval + TILE);
 
     const int tid = threadIdx.x;
     const int wave = tid >> 6;
@@ -245,9 +279,9 @@ k_radix_scatter(const uint32_t *__restrict__ kin, const uint32_t *__restrict__ v
     for (int e = tid; e < kSWaves * 256; e += NT) (&cnt[0][0])[e] = 0;
     __syncthreads();
 
-    const int64_t tbase = (int64_t)blockIdx.x * kTile;
+    const int64_t tbase = (int64_t)blockIdx.x * TILE;
     const int64_t base = tbase + (int64_t)wave * (64 * kSItems);
-    const int tcount = (int)std::min<int64_t>(kTile, (int64_t)M - tbase);
+    const int tcount = (int)std::min<int64_t>(TILE, (int64_t)M - tbase);
     const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     const uint32_t dmask = (1u << dbits) - 1u;
     uint32_t kk[kSItems], vv[kSItems], rk[kSItems];
@@ -309,17 +343,38 @@ k_radix_scatter(const uint32_t *__restrict__ kin, const uint32_t *__restrict__ v
             cnt[w][d] = run;
             run += c;
         }
-        tstart[d] = run;  // digit total, scanned below
-        gbase[d] = offs[(int64_t)d * nblk + blockIdx.x];
+        const uint32_t inc = wave_incl_scan(run, lane);
+        uint32_t base = 0, all = 0;
+        if (sums) {
+            // this digit's points in earlier blocks, and in all of them
+            const uint4 *row = reinterpret_cast<const uint4 *>(offs + (int64_t)d * pitch);
+            const uint32_t me = blockIdx.x;
+#pragma unroll 16
+            for (uint32_t q = 0; q < (uint32_t)pitch / 4; ++q) {
+                const uint4 v = row[q];
+                base += (4 * q < me ? v.x : 0u) + (4 * q + 1 < me ? v.y : 0u) +
+                        (4 * q + 2 < me ? v.z : 0u) + (4 * q + 3 < me ? v.w : 0u);
+                all += v.x + v.y + v.z + v.w;
+            }
+        } else {
+            base = offs[(int64_t)d * pitch + blockIdx.x];
+        }
+        const uint32_t ainc = wave_incl_scan(all, lane);
+        if (lane == 63) {
+            wsum[wave] = inc;
+            asum[wave] = ainc;
+        }
+        tstart[d] = inc;  // within the wave's digits; completed below
+        gbase[d] = base + (sums ? ainc - all : 0u);
     }
     __syncthreads();
-    for (int o = 1; o < 256; o <<= 1) {
-        uint32_t v = 0;
-        if (tid < 256 && tid >= o) v = tstart[tid - o];
-        __syncthreads();
-        if (tid < 256) tstart[tid] += v;
-        __syncthreads();
+    if (tid < 256) {
+        for (int w = 0; w < wave; ++w) {
+            tstart[tid] += wsum[w];
+            gbase[tid] += sums ? asum[w] : 0u;
+        }
     }
+    __syncthreads();
     // tstart[d] now holds the inclusive sum of the digit totals, so digit d's
     // run in the tile starts at tstart[d - 1] (0 for d = 0).
 #pragma unroll
@@ -329,13 +384,13 @@ k_radix_scatter(const uint32_t *__restrict__ kin, const uint32_t *__restrict__ v
             const uint32_t d = (kk[r] >> shift) & dmask;
             const uint32_t start = d == 0 ? 0u : tstart[d - 1];
             const uint32_t lpos = start + cnt[wave][d] + rk[r];
-            if (lpos >= (uint32_t)kTile) continue;  // cannot happen when the counts agree
+            if (lpos >= (uint32_t)TILE) continue;  // cannot happen when the counts agree
             skey[lpos] = kk[r];
             sval[lpos] = vv[r];
 #pragma unroll
             for (int q = 0; q < ND; ++q) {
-                if constexpr (SRC) spay[q * kTile + lpos] = pu[r][q];
-                else spay[q * kTile + lpos] = static_cast<const T *>(pl.in[q])[idx];
+                if constexpr (SRC) spay[q * TILE + lpos] = pu[r][q];
+                else spay[q * TILE + lpos] = static_cast<const T *>(pl.in[q])[idx];
             }
         }
     }
@@ -349,22 +404,12 @@ k_radix_scatter(const uint32_t *__restrict__ kin, const uint32_t *__restrict__ v
         kout[gpos] = key;
         vout[gpos] = sval[e];
 #pragma unroll
-        for (int q = 0; q < ND; ++q) static_cast<T *>(pl.out[q])[gpos] = spay[q * kTile + e];
+        for (int q = 0; q < ND; ++q) static_cast<T *>(pl.out[q])[gpos] = spay[q * TILE + e];
     }
 }
 
 // ---- generic exclusive scan (chunk totals; down-sweep adds earlier ones) ----
 constexpr int kScanChunk = kThreads * kItems;
-
-__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v, int lane)
-{
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t t = __shfl_up(v, o, 64);
-        if (lane >= o) v += t;
-    }
-    return v;
-}
 
 // Exclusive scan of one value per thread over the block; returns the block total.
 __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t &excl)
@@ -435,6 +480,37 @@ k_scan_down(const uint32_t *__restrict__ in, uint32_t *__restrict__ out, size_t 
     }
 }
 
+// binstart[b] = first sorted position with key >= b: a wave per bin narrows
+// the range 64-fold a step, four dependent loads for 1.6e7 points against 24
+// of a binary search per thread (1e7 points in 4096 bins 12 -> 9 us, 1e5 in
+// 256 bins 5.5 -> 3.8 us); above kWaveBins bins a thread per bin, which then
+// fill the GPU.
+constexpr int kWaveBins = 32768;
+__global__ void __launch_bounds__(256)
+k_binstart_wave(int M, int nbins, const uint32_t *__restrict__ skey,
+                int32_t *__restrict__ binstart)
+{
+    const int b = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (b > nbins) return;
+    int64_t lo = 0, hi = M;  // the answer lies in [lo, hi]
+    while (lo < hi) {
+        const int64_t len = hi - lo;
+        // 64 probes, each the end of a sixty-fourth of [lo, hi), or all of it
+        const auto probe = [&](int k) { return len <= 64 ? lo + k : lo + ((len * (k + 1)) >> 6) - 1; };
+        const int64_t p = probe(lane);
+        const bool below = p < hi && skey[p] < (uint32_t)b;
+        const int n = (int)__popcll(__ballot(below));  // the first n probes are below
+        if (len <= 64) {
+            lo += n;
+            break;
+        }
+        const int64_t nlo = n > 0 ? probe(n - 1) + 1 : lo;
+        hi = n < 64 ? probe(n) : hi;
+        lo = nlo;
+    }
+    if (lane == 0) binstart[b] = (int32_t)lo;
+}
+
 __global__ void k_binstart(int M, int nbins, const uint32_t *__restrict__ skey,
                            int32_t *__restrict__ binstart)
 {
@@ -466,10 +542,43 @@ __global__ void k_subcount(int nbins, int msub, const int32_t *__restrict__ bins
     cnt[b] = (uint32_t)((c + ms - 1) / ms);
 }
 
+// k_subcount and the scan of its counts in one block, for up to kWaveBins
+// bins; also clears the merge list's count.
+__global__ void __launch_bounds__(1024)
+k_subscan(int nbins, int msub, const int32_t *__restrict__ binstart, uint32_t *__restrict__ off,
+          const TGeom *__restrict__ tg, const int32_t *__restrict__ bin_t,
+          int32_t *__restrict__ nmerge)
+{
+    __shared__ uint32_t wsum[16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (nmerge && tid == 0) *nmerge = 0;
+    const int per = (nbins + 1023) / 1024, b0 = min(tid * per, nbins), b1 = min(b0 + per, nbins);
+    const auto count = [&](int b) {
+        const int c = binstart[b + 1] - binstart[b], ms = msub_of(b, msub, tg, bin_t);
+        return (uint32_t)((c + ms - 1) / ms);
+    };
+    uint32_t mine = 0;
+    for (int b = b0; b < b1; ++b) mine += count(b);
+    const uint32_t inc = wave_incl_scan(mine, lane);
+    if (lane == 63) wsum[wave] = inc;
+    __syncthreads();
+    uint32_t run = inc - mine;
+    for (int w = 0; w < wave; ++w) run += wsum[w];
+    for (int b = b0; b < b1; ++b) {
+        off[b] = run;
+        run += count(b);
+    }
+    if (tid == 1023) off[nbins] = run;
+}
+
+// Subproblem records; with a merge list, also the leaders of tile groups to
+// merge: subproblems q with (q - off[bin]) % G == 0 in bins with more than G
+// of them (*nmerge is zero on entry).
 __global__ void k_subfill(int nbins, int msub, int nsub_max, const int32_t *__restrict__ binstart,
                           const uint32_t *__restrict__ off, int32_t *__restrict__ sub,
                           int32_t *__restrict__ nsub, const TGeom *__restrict__ tg,
-                          const int32_t *__restrict__ bin_t)
+                          const int32_t *__restrict__ bin_t, int G,
+                          int32_t *__restrict__ mergelist, int32_t *__restrict__ nmerge)
 {
     const int q = blockIdx.x * blockDim.x + threadIdx.x;
     // the count is clamped to the list's capacity so that no consumer can
@@ -484,19 +593,23 @@ __global__ void k_subfill(int nbins, int msub, int nsub_max, const int32_t *__re
     }
     const int b = lo;
     const int ms = msub_of(b, msub, tg, bin_t);
-    const int s = q - (int)off[b];
+    const int first = (int)off[b], s = q - first;
     const int start = binstart[b] + s * ms;
     const int len = std::min(ms, binstart[b + 1] - start);
     int4 rec;
     rec.x = b; rec.y = start; rec.z = len; rec.w = 0;
     reinterpret_cast<int4 *>(sub)[q] = rec;
+    if (mergelist && (int)off[b + 1] - first > G && s % G == 0) mergelist[atomicAdd(nmerge, 1)] = q;
 }
 
 inline int nblocks(int64_t n, int t) { return (int)((n + t - 1) / t); }
 
 }  // namespace
 
-size_t radix_hist_elems(int M) { return (size_t)256 * std::max(1, nblocks(M, kTile)); }
+size_t radix_hist_elems(int M)
+{
+    return (size_t)256 * hist_pitch(std::max(1, nblocks(M, tile_of(M))));
+}
 
 size_t scan_partial_elems(size_t n) { return (n + kScanChunk - 1) / kScanChunk + 1; }
 
@@ -549,7 +662,9 @@ hipError_t radix_sort(int M, int bits, int prec, int dim, uint32_t *keysA, uint3
     const int passes = radix_passes(bits);
     const int dbits = std::max(1, (bits + passes - 1) / passes);
     const uint32_t dmask = (1u << dbits) - 1u;
-    const int nblk = std::max(1, nblocks(M, kTile));
+    const int tile = tile_of(M), nblk = std::max(1, nblocks(M, tile));
+    const int pitch = hist_pitch(nblk);
+    const bool sums = nblk <= kFusedBlocks;  // the scatter sums the counts itself
     uint32_t *kb[2] = {keysA, keysB}, *vb[2] = {valsA, valsB};
     int cur = 0;
     for (int p = 0; p < passes; ++p) {
@@ -558,37 +673,36 @@ hipError_t radix_sort(int M, int bits, int prec, int dim, uint32_t *keysA, uint3
             // pass 0 from the points themselves when a source is given
             const int from = (p == 0 && src) ? (src->tg ? 2 : 1) : 0;
             const KeySrc ks = src ? *src : KeySrc{};
-            if (from) {
-#define MN_HSRC(TT)                                                                           \
-    do {                                                                                      \
-        if (from == 2)                                                                        \
-            hipLaunchKernelGGL((k_radix_hist_src<TT, true>), dim3(nblk), dim3(kSrcThreads), 0, \
-                               s, ks, M, shift, dmask, nblk, hist);                           \
-        else                                                                                  \
-            hipLaunchKernelGGL((k_radix_hist_src<TT, false>), dim3(nblk), dim3(kSrcThreads),   \
-                               0, s, ks, M, shift, dmask, nblk, hist);                        \
-    } while (0)
-                if (prec == 0) MN_HSRC(float);
-                else MN_HSRC(double);
-#undef MN_HSRC
-            } else {
-                hipLaunchKernelGGL(k_radix_hist, dim3(nblk), dim3(kThreads), 0, s,
-                                   (const uint32_t *)kb[cur], M, shift, dmask, nblk, hist);
-            }
-            // digits above dmask are empty: only the first dmask + 1 rows are scanned
-            hipError_t e = scan_exclusive(hist, hist, (size_t)(dmask + 1) * nblk, partials, s);
-            if (e != hipSuccess) return e;
             const uint32_t *vin = p == 0 ? nullptr : (const uint32_t *)vb[cur];
+            const auto pass = [&](auto tag) -> hipError_t {
+                constexpr int TILE = decltype(tag)::value;
+#define MN_HSRC(TT, BB)                                                                       \
+    hipLaunchKernelGGL((k_radix_hist_src<TT, BB, TILE>), dim3(nblk), dim3(kSrcThreads), 0, s,  \
+                       ks, M, shift, dmask, pitch, hist)
+                if (from == 0)
+                    hipLaunchKernelGGL((k_radix_hist<TILE>), dim3(nblk), dim3(kThreads), 0, s,
+                                       (const uint32_t *)kb[cur], M, shift, dmask, pitch, hist);
+                else if (prec == 0 && from == 2) MN_HSRC(float, true);
+                else if (prec == 0) MN_HSRC(float, false);
+                else if (from == 2) MN_HSRC(double, true);
+                else MN_HSRC(double, false);
+#undef MN_HSRC
+                // digits above dmask are empty: only the first dmask + 1 rows are scanned
+                if (!sums) {
+                    const hipError_t e =
+                        scan_exclusive(hist, hist, (size_t)(dmask + 1) * pitch, partials, s);
+                    if (e != hipSuccess) return e;
+                }
 #define MN_SCATTER1(TT, DD, SS)                                                             \
     do {                                                                                    \
-        const size_t lds = (size_t)kTile * (8 + DD * sizeof(TT));                           \
+        const size_t lds = (size_t)TILE * (8 + DD * sizeof(TT));                            \
         if (lds > 65536)                                                                    \
-            (void)hipFuncSetAttribute((const void *)k_radix_scatter<TT, DD, SS>,            \
+            (void)hipFuncSetAttribute((const void *)k_radix_scatter<TT, DD, SS, TILE>,      \
                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); \
-        hipLaunchKernelGGL((k_radix_scatter<TT, DD, SS>), dim3(nblk),                       \
-                           dim3(scatter_threads<TT, DD>()), lds, s,                        \
-                           (const uint32_t *)kb[cur], vin, M, shift, dbits, nblk,           \
-                           (const uint32_t *)hist, kb[1 - cur], vb[1 - cur], pays[p], ks); \
+        hipLaunchKernelGGL((k_radix_scatter<TT, DD, SS, TILE>), dim3(nblk),                 \
+                           dim3(scatter_threads<TT, DD, TILE>()), lds, s,                   \
+                           (const uint32_t *)kb[cur], vin, M, shift, dbits, pitch, sums,    \
+                           (const uint32_t *)hist, kb[1 - cur], vb[1 - cur], pays[p], ks);  \
     } while (0)
 #define MN_SCATTER(TT, DD)                                                                  \
     do {                                                                                    \
@@ -596,17 +710,22 @@ hipError_t radix_sort(int M, int bits, int prec, int dim, uint32_t *keysA, uint3
         else if (from == 1) MN_SCATTER1(TT, DD, 1);                                         \
         else MN_SCATTER1(TT, DD, 0);                                                        \
     } while (0)
-            if (prec == 0) {
-                if (dim == 1) MN_SCATTER(float, 1);
-                else if (dim == 2) MN_SCATTER(float, 2);
-                else MN_SCATTER(float, 3);
-            } else {
-                if (dim == 1) MN_SCATTER(double, 1);
-                else if (dim == 2) MN_SCATTER(double, 2);
-                else MN_SCATTER(double, 3);
-            }
+                if (prec == 0) {
+                    if (dim == 1) MN_SCATTER(float, 1);
+                    else if (dim == 2) MN_SCATTER(float, 2);
+                    else MN_SCATTER(float, 3);
+                } else {
+                    if (dim == 1) MN_SCATTER(double, 1);
+                    else if (dim == 2) MN_SCATTER(double, 2);
+                    else MN_SCATTER(double, 3);
+                }
 #undef MN_SCATTER
 #undef MN_SCATTER1
+                return hipSuccess;
+            };
+            const hipError_t e = tile == kTile ? pass(std::integral_constant<int, kTile>())
+                                               : pass(std::integral_constant<int, kTileSmall>());
+            if (e != hipSuccess) return e;
         }
         cur = 1 - cur;
     }
@@ -618,8 +737,12 @@ hipError_t radix_sort(int M, int bits, int prec, int dim, uint32_t *keysA, uint3
 hipError_t launch_binstart(int M, int nbins, const uint32_t *skey, int32_t *binstart,
                            hipStream_t s)
 {
-    hipLaunchKernelGGL(k_binstart, dim3(nblocks(nbins + 1, 256)), dim3(256), 0, s, M, nbins,
-                       skey, binstart);
+    if (nbins <= kWaveBins)
+        hipLaunchKernelGGL(k_binstart_wave, dim3(nblocks(nbins + 1, 4)), dim3(256), 0, s, M,
+                           nbins, skey, binstart);
+    else
+        hipLaunchKernelGGL(k_binstart, dim3(nblocks(nbins + 1, 256)), dim3(256), 0, s, M, nbins,
+                           skey, binstart);
     return hipGetLastError();
 }
 
@@ -919,19 +1042,28 @@ hipError_t launch_group(const Geom &g, int prec, int span, int nsub_max, const i
 
 hipError_t launch_subproblems(int nbins, int msub, int nsub_max, const int32_t *binstart,
                               int32_t *subcount, uint32_t *partials, int32_t *sub,
-                              int32_t *nsub, hipStream_t s, const TGeom *tg, int T,
-                              const int32_t *bin_t)
+                              int32_t *nsub, int G, int32_t *mergelist, int32_t *nmerge,
+                              hipStream_t s, const TGeom *tg, int T, const int32_t *bin_t)
 {
     if (tg && !bin_t) return hipErrorInvalidValue;
     (void)T;
     uint32_t *cnt = reinterpret_cast<uint32_t *>(subcount);
-    hipLaunchKernelGGL(k_subcount, dim3(nblocks(nbins + 1, 256)), dim3(256), 0, s, nbins, msub,
-                       binstart, cnt, tg, bin_t);
-    hipError_t e = scan_exclusive(cnt, cnt, (size_t)nbins + 1, partials, s);
-    if (e != hipSuccess) return e;
+    if (nbins <= kWaveBins) {
+        hipLaunchKernelGGL(k_subscan, dim3(1), dim3(1024), 0, s, nbins, msub, binstart, cnt, tg,
+                           bin_t, nmerge);
+    } else {
+        if (nmerge) {
+            const hipError_t e = launch_zero(nmerge, 4, s);
+            if (e != hipSuccess) return e;
+        }
+        hipLaunchKernelGGL(k_subcount, dim3(nblocks(nbins + 1, 256)), dim3(256), 0, s, nbins,
+                           msub, binstart, cnt, tg, bin_t);
+        const hipError_t e = scan_exclusive(cnt, cnt, (size_t)nbins + 1, partials, s);
+        if (e != hipSuccess) return e;
+    }
     hipLaunchKernelGGL(k_subfill, dim3(nblocks(std::max(nsub_max, 1), 256)), dim3(256), 0, s,
                        nbins, msub, nsub_max, binstart, (const uint32_t *)cnt, sub, nsub, tg,
-                       bin_t);
+                       bin_t, G, mergelist, nmerge);
     return hipGetLastError();
 }
 

@@ -493,13 +493,10 @@ int enqueue_setpts(mnufft_plan p, int64_t M, const void *x, const void *y, const
     p->skey = sk;
     p->perm = reinterpret_cast<int32_t *>(sv);
     MN_HIP(mn::launch_binstart((int)M, g.nbins, p->skey, p->binstart, s));
+    const bool sm = p->method == MNUFFT_METHOD_SM;
     MN_HIP(mn::launch_subproblems(g.nbins, p->msub, p->nsub_max, p->binstart, p->subcount,
-                                  p->partials, p->sub, p->nsub, s));
-    if (p->method == MNUFFT_METHOD_SM) {
-        MN_HIP(mn::launch_zero(p->nmerge, 4, s));
-        MN_HIP(mn::launch_merge_list(p->nsub_max, p->nsub, p->sub, p->subcount, kMergeGroup,
-                                     p->mergelist, p->nmerge, s));
-    }
+                                  p->partials, p->sub, p->nsub, kMergeGroup,
+                                  sm ? p->mergelist : nullptr, sm ? p->nmerge : nullptr, s));
     if (p->method == MNUFFT_METHOD_SM && !balanced(p))
         MN_HIP(mn::launch_iota(p->spos_proc, (int)M, s));
     if (balanced(p)) {

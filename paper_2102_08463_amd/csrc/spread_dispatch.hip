@@ -97,29 +97,6 @@ int mf_span(const Geom &g, int prec, int msub)
     return groups <= 256 && mf_lds_bytes(g) <= 160 * 1024 ? s : 0;
 }
 
-namespace {
-__global__ void k_merge_list(int nsub_max, const int32_t *__restrict__ nsubp,
-                             const int32_t *__restrict__ sub, const int32_t *__restrict__ suboff,
-                             int G, int32_t *__restrict__ mergelist, int32_t *__restrict__ nmerge)
-{
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= nsub_max || q >= *nsubp) return;
-    const int b = reinterpret_cast<const int4 *>(sub)[q].x;
-    const int first = suboff[b], k = suboff[b + 1] - first;
-    if (k > G && (q - first) % G == 0) mergelist[atomicAdd(nmerge, 1)] = q;
-}
-}  // namespace
-
-hipError_t launch_merge_list(int nsub_max, const int32_t *nsub, const int32_t *sub,
-                             const int32_t *suboff, int G, int32_t *mergelist, int32_t *nmerge,
-                             hipStream_t s)
-{
-    if (nsub_max <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_merge_list, dim3((nsub_max + 255) / 256), dim3(256), 0, s, nsub_max,
-                       nsub, sub, suboff, G, mergelist, nmerge);
-    return hipGetLastError();
-}
-
 hipError_t launch_spread(const Geom &g, int prec, int method, const Pts &P, const void *c,
                          void *grid, hipStream_t s, int part)
 {

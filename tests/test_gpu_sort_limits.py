@@ -1,0 +1,29 @@
+"""Bin-sort at the sizes where its kernels change: small blocks with summed
+counts up to 262144 points, small blocks with scanned counts up to 2^20, large
+blocks above; one bin, some, and more bins than the wave search takes."""
+import numpy as np
+import pytest
+
+from oracle import binsort
+from tests.gpu_helpers import make_points, note
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("M", [1, 63, 1023, 1024, 1025, 262144, 262145, 1 << 20, (1 << 20) + 1])
+def test_permutation_bins_and_subproblems(M):
+    from paper_2102_08463_amd import Plan
+    note(f"sort limits {M}")
+    pts64, pts = make_points("gaussian", M, 2, "f32", seed=5)
+    for N, bs, method in (((20, 24), None, "auto"), ((600, 640), (6, 4), "gmsort"),
+                          ((8, 8), (64, 64), "auto")):
+        with Plan(1, N, eps=1e-4, binsize=bs, method=method) as p:
+            p.setpts(*pts)
+            inf = p.info()
+            perm, start = p.get_sort()
+            sub, _ = p.get_subproblems()
+        keys = binsort.bin_keys(pts64, inf["nfine"][:2], inf["binsize"][:2])
+        assert np.array_equal(perm.cpu().numpy(), binsort.permutation(keys))
+        assert np.array_equal(start.cpu().numpy(), binsort.bin_starts(keys, inf["nbins"]))
+        assert np.array_equal(sub[:, :3].cpu().numpy(),
+                              binsort.subproblems(keys, inf["nbins"], inf["msub"]))
