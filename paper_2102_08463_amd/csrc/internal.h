@@ -181,6 +181,7 @@ struct Pts {
                               // (the points are in their order; 0: tap by tap)
     int *work;                // their work counters (spreading, interpolation), zero
                               // between launches
+    int sm;                   // method SM: sub, nsub and the kernels' order are set
     int nt;                   // stacked transforms of this launch (SM; at least 1)
     size_t tile_stride;       // reals between their tiles in scratch
     // batches: per-transform geometry (device) and count; nullptr / 1 for a plain plan

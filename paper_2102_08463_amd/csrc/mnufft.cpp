@@ -337,6 +337,7 @@ mn::Pts points_of(mnufft_plan p)
     P.heavy = p->method == MNUFFT_METHOD_SM ? p->subcount + p->g.nbins + 1 : nullptr;
     P.cmax = p->cmax;
     P.msub = p->msub;
+    P.sm = p->method == MNUFFT_METHOD_SM;
     P.nt = 1;
     P.tile_stride = (size_t)std::max(p->nsub_cap, 1) * p->ts2;
     P.tg = nullptr;
@@ -1194,7 +1195,7 @@ int mnufft_interp_grad(mnufft_plan p, const void *modes, const void *wts, void *
     const int sign = p->type == 2 ? p->iflag : -p->iflag;
     if ((rc = modes_to_grid(p, sign, modes))) return rc;
     void *out[3] = {gx, p->dim >= 2 ? gy : nullptr, p->dim == 3 ? gz : nullptr};
-    MN_HIP(mn::launch_interp_grad(p->g, p->prec, points_of(p), (int)p->ntransf, p->grid, wts,
+    MN_HIP(mn::launch_interp_grad(p->g, p->prec, kernel_points(p, false), (int)p->ntransf, p->grid, wts,
                                   out, p->stream));
     return MNUFFT_OK;
 }

@@ -1529,11 +1529,138 @@ k_interp_grad(Geom g, int M, int ntransf, const uint32_t *__restrict__ key,
     for (int d = 0; d < DIM; ++d) outs[d][j] = acc[d] * (-(T)g.n[d] / ((T)3.141592653589793 * (T)W));
 }
 
+// The same for method SM plans: the padded bin staged in LDS as k_interp_sm
+// stages it, points in the SM kernels' order.  From global memory a point
+// reads its w^d cells through L1 and L2 (3D, w = 6, 4e6 points in spirals:
+// 854 us; staged 314 us); transforms after the first (add) accumulate into out.
+template <typename T, int DIM, int W>
+__global__ void __launch_bounds__(kThreads)
+k_grad_sm(Geom g, const int32_t *__restrict__ sub, const int32_t *__restrict__ nsubp,
+          const T *__restrict__ u0, const T *__restrict__ u1, const T *__restrict__ u2,
+          const int32_t *__restrict__ idx, const typename Cplx<T>::type *__restrict__ grid,
+          const typename Cplx<T>::type *__restrict__ wts, T *__restrict__ o0,
+          T *__restrict__ o1, T *__restrict__ o2, int add, T bk, T beta)
+{
+    using C = typename Cplx<T>::type;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    C *tile = reinterpret_cast<C *>(smem_raw);
+    constexpr int P = (W + 1) / 2;
+    const int p1 = g.m[0] + 2 * P, p2 = DIM >= 2 ? g.m[1] + 2 * P : 1;
+    const int p3 = DIM == 3 ? g.m[2] + 2 * P : 1, rows = p2 * p3;
+    const int nsub = *nsubp;
+    for (int q = blockIdx.x; q < nsub; q += gridDim.x) {
+        const int4 rec = reinterpret_cast<const int4 *>(sub)[q];
+        const int b1 = rec.x % g.B[0], b23 = rec.x / g.B[0];
+        const int b2 = DIM >= 2 ? b23 % g.B[1] : 0, b3 = DIM == 3 ? b23 / g.B[1] : 0;
+        const int f1 = b1 * g.m[0] - P, f2 = DIM >= 2 ? b2 * g.m[1] - P : 0;
+        const int f3 = DIM == 3 ? b3 * g.m[2] - P : 0;
+        // rows of the padded bin, 32 lanes each, four rows' loads in flight
+        constexpr int kRows = 4, kStep = kThreads / 32;
+        for (int s1 = threadIdx.x & 31; s1 < p1; s1 += 32) {
+            const int l1 = wrapmod(f1 + s1, g.n[0]);
+            for (int r0 = threadIdx.x >> 5; r0 < rows; r0 += kRows * kStep) {
+                C v[kRows];
+#pragma unroll
+                for (int k = 0; k < kRows; ++k) {
+                    const int r = min(r0 + k * kStep, rows - 1), s3 = r / p2, s2 = r - s3 * p2;
+                    const int l2 = DIM >= 2 ? wrapmod(f2 + s2, g.n[1]) : 0;
+                    const int l3 = DIM == 3 ? wrapmod(f3 + s3, g.n[2]) : 0;
+                    v[k] = grid[((size_t)l3 * g.n[1] + l2) * g.n[0] + l1];
+                }
+#pragma unroll
+                for (int k = 0; k < kRows; ++k)
+                    if (r0 + k * kStep < rows) tile[(r0 + k * kStep) * p1 + s1] = v[k];
+            }
+        }
+        __syncthreads();
+        const int end = rec.y + rec.z;
+        for (int i = rec.y + threadIdx.x; i < end; i += kThreads) {
+            T kx[W], ky[W], dkx[W], dky[W];
+            const int sx = taps_der<T, W>(u0[i] + (T)P, bk, beta, kx, dkx);
+            int sy = 0;
+            if constexpr (DIM >= 2) {
+                sy = taps_der<T, W>(u1[i] + (T)P, bk, beta, ky, dky);
+            } else {
+                ky[0] = 1;  // one row, weight one
+                dky[0] = 0;
+            }
+            const int j = idx[i];
+            const C w = wts[j];
+            T z0 = 0;
+            int sz = 0;
+            if constexpr (DIM == 3) sz = tap_start<T, W>(u2[i] + (T)P, z0);
+            T dr[3] = {0, 0, 0}, di[3] = {0, 0, 0};
+#pragma unroll 1
+            for (int a3 = 0; a3 < (DIM == 3 ? W : 1); ++a3) {
+                T wz = 1, dwz = 0;
+                if constexpr (DIM == 3)
+                    es_val_der(z0 + (T)a3 * (T)(2.0 / W), bk, beta, wz, dwz);
+                // sums over the plane with the x-derivative, the y-derivative, none
+                T xr = 0, xi = 0, yr = 0, yi = 0, pr = 0, pi = 0;
+#pragma unroll
+                for (int a2 = 0; a2 < (DIM >= 2 ? W : 1); ++a2) {
+                    const C *row = tile + ((sz + a3) * p2 + sy + a2) * p1 + sx;
+                    T sr = 0, si = 0, er = 0, ei = 0;
+#pragma unroll
+                    for (int a1 = 0; a1 < W; ++a1) {
+                        const C v = row[a1];
+                        sr += v.x * kx[a1];
+                        si += v.y * kx[a1];
+                        er += v.x * dkx[a1];
+                        ei += v.y * dkx[a1];
+                    }
+                    xr += er * ky[a2];
+                    xi += ei * ky[a2];
+                    if constexpr (DIM >= 2) {
+                        yr += sr * dky[a2];
+                        yi += si * dky[a2];
+                    }
+                    if constexpr (DIM == 3) {
+                        pr += sr * ky[a2];
+                        pi += si * ky[a2];
+                    }
+                }
+                dr[0] += xr * wz;
+                di[0] += xi * wz;
+                dr[1] += yr * wz;
+                di[1] += yi * wz;
+                dr[2] += pr * dwz;
+                di[2] += pi * dwz;
+            }
+            T *outs[3] = {o0, o1, o2};
+#pragma unroll
+            for (int d = 0; d < DIM; ++d) {
+                // Re(conj(w) D_d)
+                T v = (w.x * dr[d] + w.y * di[d]) *
+                      (-(T)g.n[d] / ((T)3.141592653589793 * (T)W));
+                if (add) v += outs[d][j];
+                outs[d][j] = v;
+            }
+        }
+        __syncthreads();
+    }
+}
+
 template <typename T, int DIM, int W>
 hipError_t grad_w(const Geom &g, const Pts &P, int ntransf, const void *grid, const void *wts,
                   void *const out[3], hipStream_t s)
 {
     using C = typename Cplx<T>::type;
+    const size_t lds = sm_lds_bytes(g, sizeof(T) == 4 ? 0 : 1, true, P.msub);
+    if (P.sm) {
+        auto kern = k_grad_sm<T, DIM, W>;
+        if (lds > 65536)
+            (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                      (int)lds);
+        for (int t = 0; t < ntransf; ++t) {
+            hipLaunchKernelGGL(kern, dim3(sm_grid(P)), dim3(kThreads), lds, s, g, P.sub, P.nsub,
+                               (const T *)P.u[0], (const T *)P.u[1], (const T *)P.u[2], P.perm,
+                               (const C *)grid + (size_t)t * P.ncells,
+                               (const C *)wts + (size_t)t * P.M, (T *)out[0], (T *)out[1],
+                               (T *)out[2], t > 0, kernel_param<T>(g.beta), (T)g.beta);
+        }
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL((k_interp_grad<T, DIM, W>), dim3(cdiv(P.M, kThreads)), dim3(kThreads), 0,
                        s, g, P.M, ntransf, P.key, (const T *)P.u[0], (const T *)P.u[1],
                        (const T *)P.u[2], P.perm, (const C *)grid, (const C *)wts, (T *)out[0],
