@@ -40,8 +40,8 @@ UNITS = [
     ("fft_inst.hip", ["-DMN_T=float", "-DMN_V=16", "-DMN_TAB=false"], "fft_f16.o"),
     ("fft_inst.hip", ["-DMN_T=float", "-DMN_V=16", "-DMN_TAB=true"], "fft_f16t.o"),
     ("fft_inst.hip", ["-DMN_T=float", "-DMN_V=24", "-DMN_TAB=false"], "fft_f24.o"),
-    ("fft_inst.hip", ["-DMN_T=double", "-DMN_V=16", "-DMN_TAB=false"], "fft_d16.o"),
-    ("fft_inst.hip", ["-DMN_T=double", "-DMN_V=16", "-DMN_TAB=true"], "fft_d16t.o"),
+    ("fft_inst.hip", ["-DMN_T=double", "-DMN_V=8", "-DMN_TAB=false"], "fft_d8.o"),
+    ("fft_inst.hip", ["-DMN_T=double", "-DMN_V=8", "-DMN_TAB=true"], "fft_d8t.o"),
     ("kernels_type3.hip", [], "kernels_type3.o"),
     ("spread_dispatch.hip", [], "spread_dispatch.o"),
     ("spread_inst.hip", ["-DMN_T=float", "-DMN_D=1"], "spread_f1.o"),

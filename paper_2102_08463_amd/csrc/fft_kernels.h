@@ -201,7 +201,7 @@ __device__ __forceinline__ int mode_of(int l, int N, int n)
 }
 
 // Radices up to this one (the larger ones spill registers in double precision).
-template <typename T> constexpr int max_radix() { return sizeof(T) == 4 ? 16 : 10; }
+template <typename T> constexpr int max_radix() { return sizeof(T) == 4 ? 16 : 8; }
 
 // The lines a block works on and where this thread stands in them.
 struct Where {
@@ -354,7 +354,7 @@ struct Stage {
 
 // Lines of one pass; with TAB, block -> entry of a table (a batch), else p0.
 template <typename T, int V, int FORM, bool TAB>
-__global__ void __launch_bounds__(fft_max_threads(sizeof(T) == 4 ? 0 : 1))
+__global__ void __launch_bounds__(kFftThreads)
 k_fft_lines(FftPass p0, const FftPass *__restrict__ tab, int ntab,
             const typename Cplx<T>::type *src, typename Cplx<T>::type *dst)
 {

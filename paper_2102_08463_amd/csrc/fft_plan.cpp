@@ -189,8 +189,8 @@ void add_length(std::vector<FftPass> &lens, const FftPass &p, size_t &vals)
 // holds too few lines.
 bool shape(Pass &q, int prec, bool table, int &V)
 {
-    for (int v : {16, 24}) {
-        if (v != 16 && (prec != 0 || table)) break;
+    for (int v : {fft_values(prec), 24}) {
+        if (v == 24 && (prec != 0 || table)) break;
         if (!fft_line(q.p.n, prec, v, q.p)) return false;
         if (fft_tile(q.p, prec, q.rows, (long long)q.p.nb * q.nt)) {
             V = v;
@@ -340,7 +340,7 @@ int FftBatch::run(void *grid, void *modes, hipStream_t s) const
 {
     void *buf[2] = {grid, modes};
     for (int k = 0; k < steps; ++k)
-        if (launch_fft_lines(prec, 16, form[k], FftPass{}, table[k], ntab, tiles[k], threads[k], lds[k],
+        if (launch_fft_lines(prec, fft_values(prec), form[k], FftPass{}, table[k], ntab, tiles[k], threads[k], lds[k],
                              buf[src[k]], buf[dst[k]], s) != hipSuccess)
             return MNUFFT_ERR_HIP;
     return MNUFFT_OK;

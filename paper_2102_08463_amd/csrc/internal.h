@@ -391,10 +391,12 @@ struct FftPass {
                              // then the coarse ones (null: no)
 };
 constexpr int kTw4 = 2048;
-// Largest block of the line kernels: 128 registers a thread in single, 256 in
-// double precision (with 128 they spill: 2000 x 1998 forward rows 194 us
-// against 62 us).
-constexpr int fft_max_threads(int prec) { return prec != 0 ? 512 : 1024; }
+// Largest block of the line kernels (128 registers a thread).
+constexpr int kFftThreads = 1024;
+// Values per thread: 16 in single precision; in double precision 8, with
+// radices up to 8 (16 values and radix 10 took 256 registers, half the waves:
+// 162^3 forward passes 117 -> 71 us, 2000 x 1998 98 -> 82 us).
+constexpr int fft_values(int prec) { return prec == 0 ? 16 : 8; }
 // Radix stages and threads per line for length n with V values per thread;
 // false when n does not factor into them.
 bool fft_line(int n, int prec, int V, FftPass &p);

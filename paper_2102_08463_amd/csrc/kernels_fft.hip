@@ -14,7 +14,7 @@ hipError_t launch(int form, const FftPass &p, const FftPass *tab, int ntab, long
                                                   long long, int, int, const void *, void *,  \
                                                   hipStream_t);
 MN_EXTERN(float, 16, false) MN_EXTERN(float, 16, true) MN_EXTERN(float, 24, false)
-MN_EXTERN(double, 16, false) MN_EXTERN(double, 16, true)
+MN_EXTERN(double, 8, false) MN_EXTERN(double, 8, true)
 #undef MN_EXTERN
 }  // namespace fft
 
@@ -96,7 +96,7 @@ bool fft_line(int n, int prec, int V, FftPass &p)
 {
     int R[kFftStages] = {}, best[kFftStages] = {}, np = 0, T = 0;
     if (n < 2) return false;
-    search(n, n, prec == 0 ? 16 : 10, 0, R, V, best, np, T);
+    search(n, n, prec == 0 ? 16 : 8, 0, R, V, best, np, T);
     if (np == 0) return false;
     p.n = n;
     p.np = np;
@@ -122,7 +122,6 @@ bool fft_line(int n, int prec, int V, FftPass &p)
 bool fft_tile(FftPass &p, int prec, bool rows, long long outer)
 {
     const size_t csz = prec == 0 ? 8 : 16;
-    const int most = fft_max_threads(prec);
     const int unit = (int)(32 / csz);  // lines of a 32 B piece
     const auto bytes = [&](int C) {
         int pitch = p.n + p.n / 16 + 1;
@@ -142,10 +141,10 @@ bool fft_tile(FftPass &p, int prec, bool rows, long long outer)
         C = std::min(4 * unit, na2);
         while (C > 2 * unit && bytes(C) > 80 * 1024) C /= 2;
     }
-    while (C > 1 && (C * p.T > most || bytes(C) > 160 * 1024)) C /= 2;
+    while (C > 1 && (C * p.T > kFftThreads || bytes(C) > 160 * 1024)) C /= 2;
     const int least = rows ? std::max(1, 64 / p.T) : std::min(unit, na2);
     while (C / 2 >= least && (long long)((p.na + C - 1) / C) * outer < 512) C /= 2;
-    if (C * p.T > most || bytes(C) > 160 * 1024) return false;
+    if (C * p.T > kFftThreads || bytes(C) > 160 * 1024) return false;
     if (!rows && C < std::min(unit, na2)) return false;
     p.C = C;
     p.logC = 0;
@@ -183,14 +182,14 @@ hipError_t launch_fft_lines(int prec, int V, int form, const FftPass &p, const F
                             hipStream_t s)
 {
     if (tiles <= 0) return hipSuccess;
-    if (tiles > 2147483647LL || threads > fft_max_threads(prec) ||
-        (tab && V != 16)) return hipErrorInvalidValue;
+    if (tiles > 2147483647LL || threads > kFftThreads ||
+        (tab && V != fft_values(prec))) return hipErrorInvalidValue;
 #define MN_GO(TT, VV, BB) fft::launch<TT, VV, BB>(form, p, tab, ntab, tiles, threads, lds, src, dst, s)
     if (prec == 0) {
         if (V == 24) return MN_GO(float, 24, false);
         return tab ? MN_GO(float, 16, true) : MN_GO(float, 16, false);
     }
-    return tab ? MN_GO(double, 16, true) : MN_GO(double, 16, false);
+    return tab ? MN_GO(double, 8, true) : MN_GO(double, 8, false);
 #undef MN_GO
 }
 
