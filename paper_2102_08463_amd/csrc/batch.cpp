@@ -341,6 +341,7 @@ int mnufft_batch_makeplan(int type, int dim, int ntr, const int64_t *nmodes, con
             tg.m[d] = m;
             tg.B[d] = (int)((n + m - 1) / m);
             tg.S[d] = (double)n / (2.0 * mn::host::kPi);
+            tg.im[d] = 1.0 / (double)m;
             cells *= n;
             nm *= N;
             nb *= tg.B[d];

@@ -15,6 +15,7 @@ struct Geom {
     int B[3];        // bins per dimension ceil(n_i / m_i)
     int nbins;
     double S[3];     // n_i / (2 pi), rounded once in double
+    double im[3];    // 1 / m_i
     int w;           // kernel width
     double beta;     // ES shape parameter
     int pad;         // ceil(w / 2): halo of a padded bin (Sec. III-A, SM step 2)
@@ -35,7 +36,7 @@ struct TGeom {
     int kmax[3];
     long long grid_off;
     long long mode_off;
-    double S[3];
+    double S[3], im[3];
 };
 
 // Index t of the last table entry whose `field` is <= v (entries sorted by field).
@@ -95,6 +96,7 @@ __device__ __forceinline__ Geom geom_of(const Geom &g, const TGeom &t)
         r.m[d] = t.m[d];
         r.B[d] = t.B[d];
         r.S[d] = t.S[d];
+        r.im[d] = t.im[d];
     }
     r.nbins = t.nbins;
     return r;
@@ -426,6 +428,10 @@ struct T3Affine {
 int t3_bounds_blocks(int n);
 hipError_t launch_t3_bounds(int prec, int n, int dim, const void *const a[3], double *part,
                             hipStream_t s);
+// The partials of the points (na blocks at pa) and the frequencies reduced to
+// (min, max, flag) per dimension at out and out + 9.
+hipError_t launch_t3_final(int dim, const double *pa, int na, const double *pb, int nb,
+                           double *out, hipStream_t s);
 // pre[j] = exp(i sg sum_d mul_d (x_jd - off_d)), complex of the plan precision.
 hipError_t launch_t3_prephase(int prec, int n, int dim, const void *const x[3],
                               const T3Affine &af, int sg, void *pre, hipStream_t s);

@@ -31,7 +31,15 @@ constexpr int kSmallKeys = 1 << 20;       // would fill too few large blocks
 // Up to this many blocks each scatter block sums the digit counts it needs
 // itself (M = 1e5: the two scan launches took 9 us of a 55 us sort).
 constexpr int kFusedBlocks = 256;
-inline int tile_of(int M) { return M <= kSmallKeys ? kTileSmall : kTile; }
+// Passes that move three single-precision planes of a sorted order take twice
+// the tile: its longer digit runs write fewer partial lines (1.7e7 points, 128
+// digits: 243 -> 203 us; the passes from the points and those of one or two
+// planes got 10 to 20% slower with it).
+constexpr int kTileWide = 2 * kTile;
+inline int tile_of(int M, bool wide = false)
+{
+    return M <= kSmallKeys ? kTileSmall : (wide ? kTileWide : kTile);
+}
 // Distance between the digits' rows of counts.
 inline int hist_pitch(int nblk) { return nblk <= kFusedBlocks ? (nblk + 3) / 4 * 4 : nblk; }
 
@@ -79,7 +87,8 @@ __device__ __forceinline__ uint32_t point_key_of(const Geom &g, const T xc[3], c
         if (map.on) xv = __dmul_rn(__dsub_rn(xv, map.off[d]), map.mul[d]);
         const double gc = grid_coord(xv, gg.S[d], gg.n[d], bad);
         const int l = (int)gc;  // gc >= 0, so truncation is floor; l <= n - 1
-        const int b = l / gg.m[d];
+        // l / m, exactly: (l + 1/2) / m is at least 1 / (2 m) from an integer
+        const int b = (int)(((double)l + 0.5) * gg.im[d]);
         k += (uint32_t)b * stride;
         stride *= (uint32_t)gg.B[d];
         u[d] = (T)(gc - (double)b * (double)gg.m[d]);
@@ -130,6 +139,17 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v, int lane)
     return v;
 }
 
+// The transforms that points [j0, j1] of a batch belong to, as a table and
+// its length: the points of a tile then search a few entries, not all.
+__device__ __forceinline__ const TGeom *tile_transforms(const TGeom *tg, int &T_, int64_t j0,
+                                                        int64_t j1)
+{
+    const auto fld = [](const TGeom &a) { return a.pt_off; };
+    const int a = find_transform(tg, T_, j0, fld), b = find_transform(tg, T_, j1, fld);
+    T_ = b - a + 1;
+    return tg + a;
+}
+
 // A block's digit counts to column blockIdx.x; the last block also clears the
 // columns up to the row pitch.
 __device__ __forceinline__ void store_counts(const uint32_t *h, int pitch, uint32_t *hist)
@@ -153,14 +173,12 @@ k_radix_hist_src(KeySrc src, int M, int shift, uint32_t dmask, int pitch,
 {
     constexpr int kSrcItems = TILE / kSrcThreads;
     __shared__ uint32_t h[256];
-    __shared__ long long soff[BATCH ? kTCache : 1];
     const int tid = threadIdx.x;
     if (tid < 256) h[tid] = 0;
-    bool cached = false;
     if constexpr (BATCH)
-        cached = cache_offsets(soff, src.tg, src.T, [](const TGeom &a) { return a.pt_off; });
-    else
-        __syncthreads();
+        src.tg = tile_transforms(src.tg, src.T, (int64_t)blockIdx.x * TILE,
+                                 std::min<int64_t>((int64_t)(blockIdx.x + 1) * TILE, M) - 1);
+    __syncthreads();
     const T *x = (const T *)src.x, *y = (const T *)src.y, *z = (const T *)src.z;
     const int dim = src.g.dim;
     const int64_t base = (int64_t)blockIdx.x * TILE;
@@ -182,7 +200,7 @@ k_radix_hist_src(KeySrc src, int M, int shift, uint32_t dmask, int pitch,
         uint32_t d = 0;
         if (valid) {
             T u[3];
-            d = (point_key_of<T, BATCH>(src.g, xc[r], src.map, src.tg, src.T, soff, cached,
+            d = (point_key_of<T, BATCH>(src.g, xc[r], src.map, src.tg, src.T, nullptr, false,
                                         (int)idx, u, bad) >> shift) & dmask;
         }
         const uint32_t d0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)d);
@@ -238,26 +256,27 @@ k_radix_hist(const uint32_t *__restrict__ keys, int M, int shift, uint32_t dmask
     store_counts(h, pitch, hist);
 }
 
-// Stable scatter of one radix pass over a tile of kTile keys, with NT
-// threads: wave w owns keys [blk*kTile + w*items*64, +items*64), items =
-// kTile / NT, and walks them in rounds of 64 consecutive keys, so ranks grow
-// with the input index.  The tile is first rearranged in LDS into digit order
-// (key, value and ND payload planes of T, the bin-relative coordinates), then
-// each digit's run is written to its global range with consecutive threads
-// on consecutive addresses.  When the staged tile takes more than 64 KB of
-// LDS (3D, or double precision) one workgroup fills a CU, and 1024 threads
-// hide its memory latency better than 512 (measured: 3D setpts 0.93 ->
-// 0.74 ms at M = 2^24).
-template <typename T, int ND, int TILE>
-constexpr int scatter_threads()
+// Stable scatter of one radix pass over a tile of TILE keys, with NT threads:
+// wave w owns keys [blk*TILE + w*items*64, +items*64), items = TILE / NT, and
+// walks them in rounds of 64 consecutive keys, so ranks grow with the input
+// index.  Every array of the tile (key, value and ND payload planes of T, the
+// bin-relative coordinates) is then rearranged in LDS into digit order and
+// each digit's run written to its global range with consecutive threads on
+// consecutive addresses.  Bound by latencies between its phases, not by
+// bandwidth, so blocks have to overlap: all loads are issued before the
+// ranking, and the arrays take turns in one stage of TILE values instead of
+// filling the LDS together (one or two blocks a CU).  1e7 points in 2D 81 and
+// 109 -> 80 and 78 us for the two passes, 1.7e7 in 3D 246 and 248 -> 170 and
+// 240; 1024 threads with half the items each: 101 and 97, 205 and 231.
+template <int TILE> constexpr int scatter_threads()
 {
-    return TILE < kTile ? 256 : (TILE * (8 + ND * (int)sizeof(T)) > 65536 ? 1024 : 512);
+    return TILE < kTile ? 256 : (TILE == kTile ? 512 : 1024);
 }
 
 // SRC: 0 reads keys and payload; 1 computes them from the points (src, a
 // plain plan); 2 the same for a batch (transform by binary search of pt_off).
 // offs holds the scanned counts or, with `sums`, the counts themselves.
-template <typename T, int ND, int SRC, int TILE, int NT = scatter_threads<T, ND, TILE>()>
+template <typename T, int ND, int SRC, int TILE, int NT = scatter_threads<TILE>()>
 __global__ void __launch_bounds__(NT)
 k_radix_scatter(const uint32_t *__restrict__ kin, const uint32_t *__restrict__ vin, int M,
                 int shift, int dbits, int pitch, bool sums, const uint32_t *__restrict__ offs,
@@ -268,55 +287,56 @@ k_radix_scatter(const uint32_t *__restrict__ kin, const uint32_t *__restrict__ v
     __shared__ uint32_t tstart[256];         // tile-local start of each digit run
     __shared__ uint32_t gbase[256];          // global start of each digit run
     __shared__ uint32_t wsum[4], asum[4];
-    extern __shared__ __align__(16) unsigned char stage_raw[];
-    uint32_t *skey = reinterpret_cast<uint32_t *>(stage_raw);
-    uint32_t *sval = skey + TILE;
-    T *spay = reinterpret_cast<T *>(sval + TILE);
+    __shared__ __align__(16) unsigned char stage_raw[TILE * sizeof(T)];
+    uint32_t *sU = reinterpret_cast<uint32_t *>(stage_raw);
+    T *sT = reinterpret_cast<T *>(stage_raw);
 
     const int tid = threadIdx.x;
     const int wave = tid >> 6;
     const int lane = tid & 63;
     for (int e = tid; e < kSWaves * 256; e += NT) (&cnt[0][0])[e] = 0;
-    __syncthreads();
 
     const int64_t tbase = (int64_t)blockIdx.x * TILE;
     const int64_t base = tbase + (int64_t)wave * (64 * kSItems);
     const int tcount = (int)std::min<int64_t>(TILE, (int64_t)M - tbase);
+    if constexpr (SRC == 2)
+        src.tg = tile_transforms(src.tg, src.T, tbase, tbase + tcount - 1);
     const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     const uint32_t dmask = (1u << dbits) - 1u;
-    uint32_t kk[kSItems], vv[kSItems], rk[kSItems];
-    T pu[SRC ? kSItems : 1][ND];  // payload computed from the points (SRC)
-    if constexpr (SRC) {
-        // every coordinate load first, so that their latencies overlap
-        const T *cs[3] = {(const T *)src.x, (const T *)src.y, (const T *)src.z};
+    uint32_t kk[kSItems], vv[kSItems], lp[kSItems];
+    T pu[kSItems][ND];  // payload (SRC: the coordinates it is computed from, first)
+    // every load first, so that their latencies overlap
+    {
+        const T *cs[3] = {(const T *)(SRC ? src.x : pl.in[0]), (const T *)(SRC ? src.y : pl.in[1]),
+                          (const T *)(SRC ? src.z : pl.in[2])};
 #pragma unroll
         for (int r = 0; r < kSItems; ++r) {
             const int64_t jc = std::min<int64_t>(base + r * 64 + lane, (int64_t)M - 1);
+            if constexpr (!SRC) kk[r] = kin[jc];
+            vv[r] = vin ? vin[jc] : (uint32_t)jc;
 #pragma unroll
             for (int q = 0; q < ND; ++q) pu[r][q] = cs[q][jc];
         }
     }
+    __syncthreads();
 #pragma unroll
     for (int r = 0; r < kSItems; ++r) {
         const int64_t idx = base + r * 64 + lane;
         const bool valid = idx < M;
-        uint32_t key = 0u;
         if constexpr (SRC) {
+            kk[r] = 0u;
             if (valid) {
                 T xc[3] = {pu[r][0], ND >= 2 ? pu[r][ND >= 2 ? 1 : 0] : (T)0,
                            ND == 3 ? pu[r][ND == 3 ? 2 : 0] : (T)0};
                 T u[3];
                 int bad = 0;
-                key = point_key_of<T, SRC == 2>(src.g, xc, src.map, src.tg, src.T, nullptr,
-                                                false, (int)idx, u, bad);
+                kk[r] = point_key_of<T, SRC == 2>(src.g, xc, src.map, src.tg, src.T, nullptr,
+                                                  false, (int)idx, u, bad);
 #pragma unroll
                 for (int q = 0; q < ND; ++q) pu[r][q] = u[q];
             }
-        } else {
-            key = valid ? kin[idx] : 0u;
         }
-        const uint32_t val = valid ? (vin ? vin[idx] : (uint32_t)idx) : 0u;
-        const uint32_t d = (key >> shift) & dmask;
+        const uint32_t d = (kk[r] >> shift) & dmask;
         uint64_t mask = __ballot(valid);
         for (int b = 0; b < dbits; ++b) {
             const bool bit = (d >> b) & 1u;
@@ -329,9 +349,7 @@ k_radix_scatter(const uint32_t *__restrict__ kin, const uint32_t *__restrict__ v
             old = cnt[wave][d];
             if (rank == 0) cnt[wave][d] = old + (uint32_t)__popcll(mask);
         }
-        kk[r] = key;
-        vv[r] = val;
-        rk[r] = old + rank;
+        lp[r] = old + rank;  // within the wave's digit
     }
     __syncthreads();
     if (tid < 256) {
@@ -344,7 +362,7 @@ k_radix_scatter(const uint32_t *__restrict__ kin, const uint32_t *__restrict__ v
             run += c;
         }
         const uint32_t inc = wave_incl_scan(run, lane);
-        uint32_t base = 0, all = 0;
+        uint32_t base_d = 0, all = 0;
         if (sums) {
             // this digit's points in earlier blocks, and in all of them
             const uint4 *row = reinterpret_cast<const uint4 *>(offs + (int64_t)d * pitch);
@@ -352,20 +370,20 @@ k_radix_scatter(const uint32_t *__restrict__ kin, const uint32_t *__restrict__ v
 #pragma unroll 16
             for (uint32_t q = 0; q < (uint32_t)pitch / 4; ++q) {
                 const uint4 v = row[q];
-                base += (4 * q < me ? v.x : 0u) + (4 * q + 1 < me ? v.y : 0u) +
-                        (4 * q + 2 < me ? v.z : 0u) + (4 * q + 3 < me ? v.w : 0u);
+                base_d += (4 * q < me ? v.x : 0u) + (4 * q + 1 < me ? v.y : 0u) +
+                          (4 * q + 2 < me ? v.z : 0u) + (4 * q + 3 < me ? v.w : 0u);
                 all += v.x + v.y + v.z + v.w;
             }
         } else {
-            base = offs[(int64_t)d * pitch + blockIdx.x];
+            base_d = offs[(int64_t)d * pitch + blockIdx.x];
         }
         const uint32_t ainc = wave_incl_scan(all, lane);
         if (lane == 63) {
             wsum[wave] = inc;
             asum[wave] = ainc;
         }
-        tstart[d] = inc;  // within the wave's digits; completed below
-        gbase[d] = base + (sums ? ainc - all : 0u);
+        tstart[d] = inc - run;  // within the wave's digits; completed below
+        gbase[d] = base_d + (sums ? ainc - all : 0u);
     }
     __syncthreads();
     if (tid < 256) {
@@ -375,36 +393,48 @@ k_radix_scatter(const uint32_t *__restrict__ kin, const uint32_t *__restrict__ v
         }
     }
     __syncthreads();
-    // tstart[d] now holds the inclusive sum of the digit totals, so digit d's
-    // run in the tile starts at tstart[d - 1] (0 for d = 0).
+    // position in the tile's digit order (none past the input's end)
 #pragma unroll
     for (int r = 0; r < kSItems; ++r) {
-        const int64_t idx = base + r * 64 + lane;
-        if (idx < M) {
-            const uint32_t d = (kk[r] >> shift) & dmask;
-            const uint32_t start = d == 0 ? 0u : tstart[d - 1];
-            const uint32_t lpos = start + cnt[wave][d] + rk[r];
-            if (lpos >= (uint32_t)TILE) continue;  // cannot happen when the counts agree
-            skey[lpos] = kk[r];
-            sval[lpos] = vv[r];
+        const uint32_t d = (kk[r] >> shift) & dmask;
+        lp[r] += tstart[d] + cnt[wave][d];
+        if (base + r * 64 + lane >= M || lp[r] >= (uint32_t)TILE) lp[r] = ~0u;
+    }
+    // each array in turn: scattered LDS writes, then contiguous runs to memory
+    uint32_t gp[kSItems];
 #pragma unroll
-            for (int q = 0; q < ND; ++q) {
-                if constexpr (SRC) spay[q * TILE + lpos] = pu[r][q];
-                else spay[q * TILE + lpos] = static_cast<const T *>(pl.in[q])[idx];
-            }
+    for (int r = 0; r < kSItems; ++r)
+        if (lp[r] != ~0u) sU[lp[r]] = kk[r];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kSItems; ++k) {
+        const int e = tid + k * NT;
+        gp[k] = ~0u;
+        if (e < tcount) {
+            const uint32_t key = sU[e], d = (key >> shift) & dmask;
+            gp[k] = gbase[d] + (uint32_t)e - tstart[d];
+            if (gp[k] >= (uint32_t)M) gp[k] = ~0u;  // cannot happen when the counts agree
+            else kout[gp[k]] = key;
         }
     }
     __syncthreads();
-    for (int e = tid; e < tcount; e += NT) {
-        const uint32_t key = skey[e];
-        const uint32_t d = (key >> shift) & dmask;
-        const uint32_t start = d == 0 ? 0u : tstart[d - 1];
-        const uint32_t gpos = gbase[d] + (uint32_t)e - start;
-        if (gpos >= (uint32_t)M) continue;  // cannot happen when the counts agree
-        kout[gpos] = key;
-        vout[gpos] = sval[e];
 #pragma unroll
-        for (int q = 0; q < ND; ++q) static_cast<T *>(pl.out[q])[gpos] = spay[q * TILE + e];
+    for (int r = 0; r < kSItems; ++r)
+        if (lp[r] != ~0u) sU[lp[r]] = vv[r];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kSItems; ++k)
+        if (gp[k] != ~0u) vout[gp[k]] = sU[tid + k * NT];
+#pragma unroll
+    for (int q = 0; q < ND; ++q) {
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kSItems; ++r)
+            if (lp[r] != ~0u) sT[lp[r]] = pu[r][q];
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kSItems; ++k)
+            if (gp[k] != ~0u) static_cast<T *>(pl.out[q])[gp[k]] = sT[tid + k * NT];
     }
 }
 
@@ -542,8 +572,10 @@ __global__ void k_subcount(int nbins, int msub, const int32_t *__restrict__ bins
     cnt[b] = (uint32_t)((c + ms - 1) / ms);
 }
 
-// k_subcount and the scan of its counts in one block, for up to kWaveBins
-// bins; also clears the merge list's count.
+// k_subcount and the scan of its counts in one block, for up to kScanBins bins
+// (18225: 21 us, the separate launches about 10; 4096: 5.5 us); also clears
+// the merge list's count.
+constexpr int kScanBins = 8192;
 __global__ void __launch_bounds__(1024)
 k_subscan(int nbins, int msub, const int32_t *__restrict__ binstart, uint32_t *__restrict__ off,
           const TGeom *__restrict__ tg, const int32_t *__restrict__ bin_t,
@@ -662,9 +694,6 @@ hipError_t radix_sort(int M, int bits, int prec, int dim, uint32_t *keysA, uint3
     const int passes = radix_passes(bits);
     const int dbits = std::max(1, (bits + passes - 1) / passes);
     const uint32_t dmask = (1u << dbits) - 1u;
-    const int tile = tile_of(M), nblk = std::max(1, nblocks(M, tile));
-    const int pitch = hist_pitch(nblk);
-    const bool sums = nblk <= kFusedBlocks;  // the scatter sums the counts itself
     uint32_t *kb[2] = {keysA, keysB}, *vb[2] = {valsA, valsB};
     int cur = 0;
     for (int p = 0; p < passes; ++p) {
@@ -672,6 +701,9 @@ hipError_t radix_sort(int M, int bits, int prec, int dim, uint32_t *keysA, uint3
             const int shift = dbits * p;
             // pass 0 from the points themselves when a source is given
             const int from = (p == 0 && src) ? (src->tg ? 2 : 1) : 0;
+            const int tile = tile_of(M, !from && dim == 3 && prec == 0);
+            const int nblk = std::max(1, nblocks(M, tile)), pitch = hist_pitch(nblk);
+            const bool sums = nblk <= kFusedBlocks;  // the scatter sums the counts itself
             const KeySrc ks = src ? *src : KeySrc{};
             const uint32_t *vin = p == 0 ? nullptr : (const uint32_t *)vb[cur];
             const auto pass = [&](auto tag) -> hipError_t {
@@ -679,13 +711,19 @@ hipError_t radix_sort(int M, int bits, int prec, int dim, uint32_t *keysA, uint3
 #define MN_HSRC(TT, BB)                                                                       \
     hipLaunchKernelGGL((k_radix_hist_src<TT, BB, TILE>), dim3(nblk), dim3(kSrcThreads), 0, s,  \
                        ks, M, shift, dmask, pitch, hist)
-                if (from == 0)
+                constexpr bool wide = TILE == kTileWide;
+                if (from == 0 || wide)
                     hipLaunchKernelGGL((k_radix_hist<TILE>), dim3(nblk), dim3(kThreads), 0, s,
                                        (const uint32_t *)kb[cur], M, shift, dmask, pitch, hist);
-                else if (prec == 0 && from == 2) MN_HSRC(float, true);
-                else if (prec == 0) MN_HSRC(float, false);
-                else if (from == 2) MN_HSRC(double, true);
-                else MN_HSRC(double, false);
+                if constexpr (!wide) {
+                    if (from == 2) {
+                        if (prec == 0) MN_HSRC(float, true);
+                        else MN_HSRC(double, true);
+                    } else if (from == 1) {
+                        if (prec == 0) MN_HSRC(float, false);
+                        else MN_HSRC(double, false);
+                    }
+                }
 #undef MN_HSRC
                 // digits above dmask are empty: only the first dmask + 1 rows are scanned
                 if (!sums) {
@@ -695,12 +733,8 @@ hipError_t radix_sort(int M, int bits, int prec, int dim, uint32_t *keysA, uint3
                 }
 #define MN_SCATTER1(TT, DD, SS)                                                             \
     do {                                                                                    \
-        const size_t lds = (size_t)TILE * (8 + DD * sizeof(TT));                            \
-        if (lds > 65536)                                                                    \
-            (void)hipFuncSetAttribute((const void *)k_radix_scatter<TT, DD, SS, TILE>,      \
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); \
         hipLaunchKernelGGL((k_radix_scatter<TT, DD, SS, TILE>), dim3(nblk),                 \
-                           dim3(scatter_threads<TT, DD, TILE>()), lds, s,                   \
+                           dim3(scatter_threads<TILE>()), 0, s,                             \
                            (const uint32_t *)kb[cur], vin, M, shift, dbits, pitch, sums,    \
                            (const uint32_t *)hist, kb[1 - cur], vb[1 - cur], pays[p], ks);  \
     } while (0)
@@ -710,7 +744,9 @@ hipError_t radix_sort(int M, int bits, int prec, int dim, uint32_t *keysA, uint3
         else if (from == 1) MN_SCATTER1(TT, DD, 1);                                         \
         else MN_SCATTER1(TT, DD, 0);                                                        \
     } while (0)
-                if (prec == 0) {
+                if constexpr (wide) {
+                    MN_SCATTER1(float, 3, 0);
+                } else if (prec == 0) {
                     if (dim == 1) MN_SCATTER(float, 1);
                     else if (dim == 2) MN_SCATTER(float, 2);
                     else MN_SCATTER(float, 3);
@@ -723,8 +759,10 @@ hipError_t radix_sort(int M, int bits, int prec, int dim, uint32_t *keysA, uint3
 #undef MN_SCATTER1
                 return hipSuccess;
             };
-            const hipError_t e = tile == kTile ? pass(std::integral_constant<int, kTile>())
-                                               : pass(std::integral_constant<int, kTileSmall>());
+            const hipError_t e =
+                tile == kTileWide ? pass(std::integral_constant<int, kTileWide>())
+                : tile == kTile   ? pass(std::integral_constant<int, kTile>())
+                                  : pass(std::integral_constant<int, kTileSmall>());
             if (e != hipSuccess) return e;
         }
         cur = 1 - cur;
@@ -1048,7 +1086,7 @@ hipError_t launch_subproblems(int nbins, int msub, int nsub_max, const int32_t *
     if (tg && !bin_t) return hipErrorInvalidValue;
     (void)T;
     uint32_t *cnt = reinterpret_cast<uint32_t *>(subcount);
-    if (nbins <= kWaveBins) {
+    if (nbins <= kScanBins) {
         hipLaunchKernelGGL(k_subscan, dim3(1), dim3(1024), 0, s, nbins, msub, binstart, cnt, tg,
                            bin_t, nmerge);
     } else {

@@ -101,7 +101,7 @@ struct mnufft_plan_s {
     int64_t t3Mcap = -1, t3Kcap = -1;
     void *t3pre = nullptr, *t3post = nullptr, *t3cp = nullptr;
     mn::PtMap ptmap{};                 // map applied before binning (type 3 sub-plans)
-    double *t3part = nullptr;          // bounds partials, 2 x 1024 blocks x 3 dims x 3
+    double *t3part = nullptr;          // bounds partials, 2 x 1024 blocks x 3 dims x 3, and 18
     double *t3quad = nullptr;          // ximax and the Chebyshev terms of log phi_hat
     int t3nq = 0;
     double C[3] = {0, 0, 0}, D[3] = {0, 0, 0}, gam[3] = {1, 1, 1}, hstep[3] = {1, 1, 1};
@@ -643,6 +643,7 @@ int plan_geometry(mnufft_plan p, const int64_t nf[3], int w, double beta, const 
     int64_t nbins = 1;
     for (int d = 0; d < 3; ++d) {
         g.B[d] = (g.n[d] + g.m[d] - 1) / g.m[d];
+        g.im[d] = 1.0 / (double)g.m[d];
         nbins *= g.B[d];
     }
     if (nbins > ((int64_t)1 << 30)) return MNUFFT_ERR_ARG;
@@ -762,7 +763,7 @@ int make_type3(int dim, int iflag, int64_t ntransf, double eps, int prec, const 
     if (!rc) rc = dalloc(p, (void **)&p->t3quad, zz.size() * 8);
     if (!rc && hipMemcpy(p->t3quad, zz.data(), zz.size() * 8, hipMemcpyHostToDevice))
         rc = MNUFFT_ERR_HIP;
-    if (!rc) rc = dalloc(p, (void **)&p->t3part, 2 * 1024 * 3 * 3 * 8);
+    if (!rc) rc = dalloc(p, (void **)&p->t3part, (2 * 1024 * 3 * 3 + 18) * 8);
     if (rc) {
         mnufft_destroy(p);
         return rc;
@@ -784,21 +785,15 @@ int64_t smooth_even(int64_t n)
     }
 }
 
-// (min, max) per dimension of n values from the partials of launch_t3_bounds;
-// false if a value is non-finite.  n = 0 gives (0, 0).
-bool reduce_bounds(const double *part, int nb, int dim, int n, double lo[3], double hi[3])
+// (min, max) per dimension of n values as launch_t3_final leaves them; false
+// if a value is non-finite.  n = 0 gives (0, 0).
+bool read_bounds(const double *fin, int dim, int n, double lo[3], double hi[3])
 {
     bool ok = true;
     for (int d = 0; d < dim; ++d) {
-        lo[d] = INFINITY;
-        hi[d] = -INFINITY;
-        for (int b = 0; b < nb; ++b) {
-            const double *q = part + 3 * ((size_t)b * dim + d);
-            lo[d] = std::min(lo[d], q[0]);
-            hi[d] = std::max(hi[d], q[1]);
-            if (q[2] != 0.0) ok = false;
-        }
-        if (n == 0) lo[d] = hi[d] = 0.0;
+        lo[d] = n == 0 ? 0.0 : fin[3 * d];
+        hi[d] = n == 0 ? 0.0 : fin[3 * d + 1];
+        if (fin[3 * d + 2] != 0.0) ok = false;
     }
     return ok;
 }
@@ -1063,12 +1058,13 @@ int mnufft_setpts3(mnufft_plan p, int64_t M, const void *x, const void *y, const
     double *partx = p->t3part, *parts = p->t3part + 1024 * 3 * 3;
     MN_HIP(mn::launch_t3_bounds(p->prec, (int)M, dim, xs, partx, st));
     MN_HIP(mn::launch_t3_bounds(p->prec, (int)K, dim, ss, parts, st));
-    std::vector<double> hp(2 * 1024 * 3 * 3);
-    MN_HIP(hipMemcpyAsync(hp.data(), p->t3part, hp.size() * 8, hipMemcpyDeviceToHost, st));
+    double hp[18], *fin = p->t3part + 2 * 1024 * 3 * 3;
+    MN_HIP(mn::launch_t3_final(dim, partx, nbx, parts, nbs, fin, st));
+    MN_HIP(hipMemcpyAsync(hp, fin, sizeof(hp), hipMemcpyDeviceToHost, st));
     MN_HIP(hipStreamSynchronize(st));
     double xl[3], xh[3], sl[3], sh[3];
-    const bool okx = reduce_bounds(hp.data(), nbx, dim, (int)M, xl, xh);
-    const bool oks = reduce_bounds(hp.data() + 1024 * 3 * 3, nbs, dim, (int)K, sl, sh);
+    const bool okx = read_bounds(hp, dim, (int)M, xl, xh);
+    const bool oks = read_bounds(hp + 9, dim, (int)K, sl, sh);
     if (!okx || !oks) return MNUFFT_ERR_PTS;
     // rescaling: gamma = nf / (2 sigma S) puts the rescaled frequencies within
     // pi / sigma, and nf >= 2 sigma S X / pi + w + 1 keeps every point's taps

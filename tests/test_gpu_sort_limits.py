@@ -27,3 +27,17 @@ def test_permutation_bins_and_subproblems(M):
         assert np.array_equal(start.cpu().numpy(), binsort.bin_starts(keys, inf["nbins"]))
         assert np.array_equal(sub[:, :3].cpu().numpy(),
                               binsort.subproblems(keys, inf["nbins"], inf["msub"]))
+
+
+@pytest.mark.parametrize("M", [(1 << 20) + 1, 1 << 21, (1 << 21) + 5000])
+def test_permutation_3d_wide_tiles(M):
+    from paper_2102_08463_amd import Plan
+    note(f"sort 3d {M}")
+    pts64, pts = make_points("uniform", M, 3, "f32", seed=6)
+    with Plan(1, (64, 60, 50), eps=1e-4) as p:
+        p.setpts(*pts)
+        inf = p.info()
+        perm, start = p.get_sort()
+    keys = binsort.bin_keys(pts64, inf["nfine"], inf["binsize"])
+    assert np.array_equal(perm.cpu().numpy(), binsort.permutation(keys))
+    assert np.array_equal(start.cpu().numpy(), binsort.bin_starts(keys, inf["nbins"]))
