@@ -39,6 +39,8 @@ UNITS = [
     ("kernels_fft.hip", [], "kernels_fft.o"),
     ("fft_inst.hip", ["-DMN_T=float", "-DMN_V=16", "-DMN_TAB=false"], "fft_f16.o"),
     ("fft_inst.hip", ["-DMN_T=float", "-DMN_V=16", "-DMN_TAB=true"], "fft_f16t.o"),
+    ("fft_inst.hip", ["-DMN_T=float", "-DMN_V=4", "-DMN_TAB=false"], "fft_f4.o"),
+    ("fft_inst.hip", ["-DMN_T=float", "-DMN_V=8", "-DMN_TAB=false"], "fft_f8.o"),
     ("fft_inst.hip", ["-DMN_T=float", "-DMN_V=24", "-DMN_TAB=false"], "fft_f24.o"),
     ("fft_inst.hip", ["-DMN_T=double", "-DMN_V=8", "-DMN_TAB=false"], "fft_d8.o"),
     ("fft_inst.hip", ["-DMN_T=double", "-DMN_V=8", "-DMN_TAB=true"], "fft_d8t.o"),

@@ -200,8 +200,8 @@ __device__ __forceinline__ int mode_of(int l, int N, int n)
     return l <= N - 1 - N / 2 ? l + N / 2 : l - n + N / 2;
 }
 
-// Radices up to this one (the larger ones spill registers in double precision).
-template <typename T> constexpr int max_radix() { return sizeof(T) == 4 ? 16 : 8; }
+// Radices up to this one (a butterfly takes one thread's values).
+constexpr int max_radix(int V) { return V < 16 ? V : 16; }
 
 // The lines a block works on and where this thread stands in them.
 struct Where {
@@ -215,22 +215,39 @@ struct Where {
 // (type 1), or of the inputs only (type 2).
 enum { kWhole = 0, kCutOut = 1, kPadIn = 2 };
 
+// What the stages need of a pass, loaded together when a block starts (the
+// arguments are cold then; fetched where they are used, each stage waited for
+// another line of them: 5.2-7.6 us a pass over a 128 x 128 grid after 6.4-8.4).
+template <typename C>
+struct Args {
+    int n, np, T, pitch, inv, cut, scale, pe, pa, full;
+    long long s_e, d_e;
+    const void *fe;
+    const C *tw, *tw4;
+    unsigned long long radices;
+    // The state of the stage loop: values per butterfly group so far, the
+    // stage's first factor.
+    int Ns, tw0;
+};
+
 template <typename T, int V, int FORM, typename C = typename Cplx<T>::type>
 struct Stage {
     // One radix stage: B butterflies of R values per thread.
     template <int R>
-    static __device__ __forceinline__ void go(const FftPass &p, int q, Where &w, const Where &w2,
-                                              T sab, const C *src, C *dst, const C *tw, C *lds)
+    static __device__ __forceinline__ void go(const Args<C> &p, int q, Where &w, const Where &w2,
+                                              T sab, const C *src, C *dst, C *lds)
     {
         constexpr int B = V / R;
         const bool first = q == 0, last = q == p.np - 1;
-        const int nbf = p.n / R, Ns = p.Ns[q];
+        const int nbf = p.n / R, Ns = p.Ns;
+        // (j + 1/2) / Ns is at least 1 / (2 Ns) from an integer, j < 2^16
+        const float rNs = 1.0f / (float)Ns;
         C x[B][R];
         int jm[B], jq[B];
 #pragma unroll
         for (int b = 0; b < B; ++b) {
             const int j = w.t + b * p.T;
-            jq[b] = first ? j : (int)__umulhi((unsigned)j, p.mNs[q]);  // j / Ns
+            jq[b] = first ? j : (int)(((float)j + 0.5f) * rNs);  // j / Ns
             jm[b] = j - jq[b] * Ns;
             if (j >= nbf || !w.on) continue;
             if (first) {
@@ -273,7 +290,7 @@ struct Stage {
                 }
             } else {
                 // exp(-2 pi i jm k / (Ns R)), k = 1 .. R - 1, rows of Ns
-                const C *f = tw + p.tw0[q] + jm[b];
+                const C *f = p.tw + p.tw0 + jm[b];
 #pragma unroll
                 for (int k = 0; k < R; ++k) x[b][k] = lds[w.c * p.pitch + skew(j + k * nbf)];
 #pragma unroll
@@ -309,8 +326,8 @@ struct Stage {
                     int m = w.a * base;
 #pragma unroll
                     for (int k = 0; k < R; ++k) {
-                        const C f = static_cast<const C *>(p.tw4)[m & (kTw4 - 1)];
-                        const C g = static_cast<const C *>(p.tw4)[kTw4 + m / kTw4];
+                        const C f = p.tw4[m & (kTw4 - 1)];
+                        const C g = p.tw4[kTw4 + m / kTw4];
                         const T fx = f.x * g.x - f.y * g.y, fy = f.x * g.y + f.y * g.x;
                         const T xr = x[b][k].x * fx - x[b][k].y * fy;
                         x[b][k].y = x[b][k].x * fy + x[b][k].y * fx;
@@ -401,21 +418,38 @@ k_fft_lines(FftPass p0, const FftPass *__restrict__ tab, int ntab,
         if (p.fa) sab = static_cast<const T *>(p.fa)[w.a];
         if (p.fb) sab *= static_cast<const T *>(p.fb)[b_idx];
     }
-    const C *tw = static_cast<const C *>(p.tw);
-    for (int q = 0; q < p.np; ++q) {
-        switch (p.R[q]) {
-#define MN_R(RR)                                                                       \
+    Args<C> g{p.n, p.np, p.T, p.pitch, p.inv, p.cut, p.scale, p.pe, p.pa, p.full, p.s_e, p.d_e,
+              p.fe, static_cast<const C *>(p.tw), static_cast<const C *>(p.tw4), p.radices, 1, 0};
+    // (keeps the loads here)
+    asm volatile("" ::"s"(g.n), "s"(g.np), "s"(g.T), "s"(g.pitch), "s"(g.inv), "s"(g.cut),
+                 "s"(g.scale), "s"(g.pe), "s"(g.pa), "s"(g.full), "s"(g.s_e), "s"(g.d_e),
+                 "s"(g.fe), "s"(g.tw), "s"(g.tw4), "s"(g.radices));
+    // The first stage's factors are ones and the last stage's come from memory
+    // too: their lines are fetched beside the first loads, a line per thread,
+    // so that the later stages find them in the cache.
+    C warm = {0, 0};
+    T warmf = (T)0;
+    if (p.tw_len > 0) warm = g.tw[min((int)threadIdx.x * (128 / (int)sizeof(C)), p.tw_len - 1)];
+    if (FORM == kCutOut && g.scale)
+        warmf = static_cast<const T *>(
+            g.fe)[min((int)threadIdx.x * (128 / (int)sizeof(T)), g.cut - 1)];
+    for (int q = 0; q < g.np; ++q) {
+        if (q == 1) asm volatile("" ::"v"(warm.x), "v"(warmf));
+        const int R = (int)(g.radices >> (8 * q)) & 255;
+        switch (R) {
+#define MN_R(RR)                                                                           \
     case RR:                                                                               \
-        if constexpr (RR <= max_radix<T>())                                                \
-            Stage<T, V, FORM>::template go<RR>(p, q, w, w2, sab, src, dst, tw, lds);             \
+        if constexpr (RR <= max_radix(V))                                                  \
+            Stage<T, V, FORM>::template go<RR>(g, q, w, w2, sab, src, dst, lds);           \
         break;
             MN_R(2) MN_R(3) MN_R(4) MN_R(5) MN_R(6) MN_R(8) MN_R(9) MN_R(10) MN_R(12) MN_R(15)
             MN_R(16)
 #undef MN_R
         }
+        if (q) g.tw0 += (R - 1) * g.Ns;
+        g.Ns *= R;
     }
 }
-
 
 }  // namespace fft
 }  // namespace mn

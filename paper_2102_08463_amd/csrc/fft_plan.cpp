@@ -175,7 +175,7 @@ int four_step(int64_t n)
 // Passes with the same radix stages share a table of stage factors.
 bool same_stages(const FftPass &a, const FftPass &b)
 {
-    return a.n == b.n && a.np == b.np && std::equal(a.R, a.R + a.np, b.R);
+    return a.n == b.n && a.radices == b.radices;
 }
 void add_length(std::vector<FftPass> &lens, const FftPass &p, size_t &vals)
 {
@@ -185,13 +185,28 @@ void add_length(std::vector<FftPass> &lens, const FftPass &p, size_t &vals)
     vals += (size_t)p.tw_len;
 }
 
+// A pass this small (a line and all values) is bound by the latency of one
+// block: the wait for its code and arguments, then stages one after another.
+// Four values a thread have a third of the code and four times the waves of
+// sixteen: 4.5-5.8 us a pass over 128 x 128 and 256 x 256 grids against
+// 5.2-7.4 with 8 values and 5.6-9.7 with 16.  Over 512 x 512 the extra stages
+// cost more (5.9-7.4 us against 5.6-6.8 with 8 values).
+constexpr long long kSmallPass = 1LL << 17;
+constexpr int kSmallLine = 256;
+
 // Radix stages and block shape; fewer values per thread unless the block then
-// holds too few lines.
+// holds too few lines or the line needs more stages.
 bool shape(Pass &q, int prec, bool table, int &V)
 {
-    for (int v : {fft_values(prec), 24}) {
-        if (v == 24 && (prec != 0 || table)) break;
-        if (!fft_line(q.p.n, prec, v, q.p)) return false;
+    const int norm = fft_values(prec);
+    FftPass base = q.p;
+    if (!fft_line(q.p.n, norm, base)) return false;
+    const bool small = q.p.n <= kSmallLine &&
+                       (long long)q.p.n * q.p.na * q.p.nb * q.nt <= kSmallPass;
+    for (int v : {4, 8, norm, 24}) {
+        if (v != norm && (prec != 0 || table)) continue;
+        if (v == 4 && !small) continue;
+        if (!fft_line(q.p.n, v, q.p) || (v == 8 && q.p.np > base.np && v < norm)) continue;
         if (fft_tile(q.p, prec, q.rows, (long long)q.p.nb * q.nt)) {
             V = v;
             return true;

@@ -377,14 +377,13 @@ hipError_t launch_precorrect_batch(const TGeom *tg, int T, long long ncells, int
 constexpr int kFftStages = 8;
 struct FftPass {
     int n, np, T, C, logC;   // length, radix stages, threads per line, lines per block
-    int R[kFftStages], Ns[kFftStages];
-    unsigned mNs[kFftStages];  // ceil(2^32 / Ns)
+    unsigned long long radices;  // a byte per stage, first lowest
     int pitch, lds, threads;   // LDS pitch of a line (values), bytes, block size
     int col0, col1;          // thread order of the first load / of the rest: lines fastest
     int inv;                 // exponent sign +1
     int na, nb, ta;          // lines, tiles over a
     int cut, scale;          // kept modes (forms 1, 2); multiply by the factors
-    int tw0[kFftStages], tw_len;  // each stage's factors in tw, their count
+    int tw_len;              // the stages' factors in tw
     int pe, pa, full;
     int tile0;               // batches: first tile of this entry
     long long s0, s_e, s_a, s_b, s_t, d0, d_e, d_a, d_b, d_t;
@@ -399,9 +398,12 @@ constexpr int kFftThreads = 1024;
 // radices up to 8 (16 values and radix 10 took 256 registers, half the waves:
 // 162^3 forward passes 117 -> 71 us, 2000 x 1998 98 -> 82 us).
 constexpr int fft_values(int prec) { return prec == 0 ? 16 : 8; }
+// Single precision takes 8 too where that needs no further stage (n = 512:
+// twice the waves, 14.7 and 12.4 -> 10.1 and 8.4 us a pass of 8 grids), and 24
+// where 16 leave a block too few lines.
 // Radix stages and threads per line for length n with V values per thread;
 // false when n does not factor into them.
-bool fft_line(int n, int prec, int V, FftPass &p);
+bool fft_line(int n, int V, FftPass &p);
 // Lines per block, LDS and block size of a pass whose n, na are set, over
 // `outer` groups of na lines; rows: the source line is contiguous.
 bool fft_tile(FftPass &p, int prec, bool rows, long long outer);

@@ -14,6 +14,7 @@ hipError_t launch(int form, const FftPass &p, const FftPass *tab, int ntab, long
                                                   long long, int, int, const void *, void *,  \
                                                   hipStream_t);
 MN_EXTERN(float, 16, false) MN_EXTERN(float, 16, true) MN_EXTERN(float, 24, false)
+MN_EXTERN(float, 8, false) MN_EXTERN(float, 4, false)
 MN_EXTERN(double, 8, false) MN_EXTERN(double, 8, true)
 #undef MN_EXTERN
 }  // namespace fft
@@ -41,21 +42,24 @@ __global__ void k_twiddle(int cnt, long long step, double n, typename Cplx<T>::t
 }
 
 // The factors of every stage after the first: stage q holds, for k = 1 ..
-// R - 1, a row of Ns values exp(-2 pi i j k / (Ns R)), at tw0[q].
+// R - 1, a row of Ns values exp(-2 pi i j k / (Ns R)).
 template <typename T>
 __global__ void k_stage_twiddle(FftPass p, typename Cplx<T>::type *__restrict__ out)
 {
     const int m = blockIdx.x * blockDim.x + threadIdx.x;
-    for (int q = 1; q < p.np; ++q) {
-        const int Ns = p.Ns[q], R = p.R[q], e = m - p.tw0[q];
-        if (e < 0 || e >= (R - 1) * Ns) continue;
-        const int k = e / Ns + 1, j = e % Ns;
-        double sn, cs;
-        sincospi(2.0 * ((double)j * k) / ((double)Ns * R), &sn, &cs);
-        typename Cplx<T>::type v;
-        v.x = (T)cs;
-        v.y = (T)-sn;
-        out[m] = v;
+    for (int q = 0, Ns = 1, at = 0; q < p.np; ++q) {
+        const int R = (int)(p.radices >> (8 * q)) & 255, e = m - at, len = q ? (R - 1) * Ns : 0;
+        if (e >= 0 && e < len) {
+            const int k = e / Ns + 1, j = e % Ns;
+            double sn, cs;
+            sincospi(2.0 * ((double)j * k) / ((double)Ns * R), &sn, &cs);
+            typename Cplx<T>::type v;
+            v.x = (T)cs;
+            v.y = (T)-sn;
+            out[m] = v;
+        }
+        at += len;
+        Ns *= R;
     }
 }
 
@@ -92,23 +96,20 @@ void search(int n, int rest, int maxr, int np, int *R, int V, int *best, int &bn
 
 }  // namespace
 
-bool fft_line(int n, int prec, int V, FftPass &p)
+bool fft_line(int n, int V, FftPass &p)
 {
     int R[kFftStages] = {}, best[kFftStages] = {}, np = 0, T = 0;
     if (n < 2) return false;
-    search(n, n, prec == 0 ? 16 : 8, 0, R, V, best, np, T);
+    search(n, n, std::min(V, 16), 0, R, V, best, np, T);
     if (np == 0) return false;
     p.n = n;
     p.np = np;
     p.T = T;
-    int Ns = 1;
+    p.radices = 0;
     p.tw_len = 0;
-    for (int q = 0; q < np; ++q) {
-        p.tw0[q] = p.tw_len;
+    for (int q = 0, Ns = 1; q < np; ++q) {
+        p.radices |= (unsigned long long)best[q] << (8 * q);
         if (q) p.tw_len += (best[q] - 1) * Ns;
-        p.R[q] = best[q];
-        p.Ns[q] = Ns;
-        p.mNs[q] = (unsigned)((0x100000000ull + Ns - 1) / Ns);  // exact for j < 65536
         Ns *= best[q];
     }
     return true;
@@ -187,6 +188,8 @@ hipError_t launch_fft_lines(int prec, int V, int form, const FftPass &p, const F
 #define MN_GO(TT, VV, BB) fft::launch<TT, VV, BB>(form, p, tab, ntab, tiles, threads, lds, src, dst, s)
     if (prec == 0) {
         if (V == 24) return MN_GO(float, 24, false);
+        if (V == 4) return MN_GO(float, 4, false);
+        if (V == 8) return MN_GO(float, 8, false);
         return tab ? MN_GO(float, 16, true) : MN_GO(float, 16, false);
     }
     return tab ? MN_GO(double, 8, true) : MN_GO(double, 8, false);

@@ -16,7 +16,8 @@ pytestmark = pytest.mark.gpu
 # thread) / 3D odd sizes / 1D one line, then two passes (8640, 2^17)
 CASES = [((5, 7), 1), ((45, 1080), 1), ((1024, 2), 3), ((2160, 3), 1), ((300, 243), 1),
          ((9, 10, 32), 1), ((27, 8, 5), 2), ((64, 40, 50), 1),
-         ((6,), 3), ((2048,), 1), ((4099,), 2), ((65536,), 1)]
+         ((6,), 3), ((2048,), 1), ((4099,), 2), ((65536,), 1),
+         ((128, 12), 1), ((32, 8, 16), 2), ((3, 5000), 1)]
 
 
 def _factors(info, d):
