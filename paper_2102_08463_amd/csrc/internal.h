@@ -273,7 +273,7 @@ hipError_t launch_subproblems(int nbins, int msub, int nsub_max, const int32_t *
 // point processed at each position.
 // out[i] = i for i < n.
 hipError_t launch_iota(int32_t *out, int n, hipStream_t s);
-hipError_t launch_balance(const Geom &g, int prec, int nsub_max, const int32_t *sub,
+hipError_t launch_balance(const Geom &g, int prec, int nsub_max, int msub, const int32_t *sub,
                           const int32_t *nsub, const void *const u[3], const int32_t *perm,
                           void *const v[3], int32_t *vperm, int32_t *spos, uint16_t *hslot,
                           hipStream_t s);

@@ -1023,7 +1023,7 @@ hipError_t launch_iota(int32_t *out, int n, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_balance(const Geom &g, int prec, int nsub_max, const int32_t *sub,
+hipError_t launch_balance(const Geom &g, int prec, int nsub_max, int msub, const int32_t *sub,
                           const int32_t *nsub, const void *const u[3], const int32_t *perm,
                           void *const v[3], int32_t *vperm, int32_t *spos, uint16_t *hslot,
                           hipStream_t s)
@@ -1037,7 +1037,7 @@ hipError_t launch_balance(const Geom &g, int prec, int nsub_max, const int32_t *
 #define MN_BAL(TT, DD)                                                                         \
     do {                                                                                       \
         MN_BAL1(TT, DD, 8);                                                                    \
-        MN_BAL1(TT, DD, 16);                                                                   \
+        if (msub > 8 * kBalThreads) MN_BAL1(TT, DD, 16);                                       \
     } while (0)
     if (prec == 0) {
         if (g.dim == 1) MN_BAL(float, 1);

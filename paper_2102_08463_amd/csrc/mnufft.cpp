@@ -70,6 +70,12 @@ struct mnufft_plan_s {
     uint16_t *hslot_proc = nullptr;
     int32_t *binstart = nullptr, *subcount = nullptr, *sub = nullptr, *nsub = nullptr;
     int nsub_max = 0, nsub_cap = 0;
+    // The kernels cut bins into subproblems of msub_k points, msub unless the
+    // library chose it (see kernel_msub); nsub_k is their list's bound.
+    bool msub_given = false;
+    int msub_k = 0, nsub_k = 0;
+    int32_t *publist = nullptr;  // get_subproblems' list of msub and its bin offsets
+    size_t publist_bytes = 0;
     uint32_t *hist = nullptr, *partials = nullptr;
     size_t hist_cap = 0, partials_cap = 0;
     int *flag = nullptr;
@@ -173,6 +179,8 @@ void free_points(mnufft_plan p)
     dfree(p, (void **)&p->partials, p->partials_cap * 4);
     dfree(p, &p->scratch, p->scratch_bytes);
     dfree(p, (void **)&p->mergelist, (size_t)p->nsub_cap * 4);
+    dfree(p, (void **)&p->publist, p->publist_bytes);
+    p->publist_bytes = 0;
     p->scratch_bytes = 0;
     p->Mcap = -1;
     p->nsub_cap = 0;
@@ -185,6 +193,32 @@ void free_points(mnufft_plan p)
 // one of k_group (kept in the *_proc arrays); 1D tiles are a single row,
 // where the sorted order does as well.
 bool balanced(const mnufft_plan_s *p) { return p->method == MNUFFT_METHOD_SM && p->dim >= 2; }
+
+// Points per subproblem of the kernels for M points, where msub is the
+// library's default: one block works on a subproblem, and a full one of 4096
+// points takes about 100 us whatever the rest, so sets that fill the GPU less
+// than that are cut finer, into about 2048 when every bin is full, 8 per CU
+// (131072 radial points on 512^2: type 1 + adjoint of 8 vectors 224 -> 184
+// us).  Not below 512 points, and a quarter above the mean of a bin: bins of
+// uniform points stay whole (1e6 points in 1024 bins cut in two: 71 -> 105
+// us), and 64 points more for the spread of small counts.  The matrix-core
+// kernels share their work by a queue and want full groups.
+int kernel_msub(const mnufft_plan_s *p, int64_t M)
+{
+    if (p->msub_given || p->method != MNUFFT_METHOD_SM || p->mf) return p->msub;
+    const int64_t mean = M / p->g.nbins;
+    const int64_t k = std::max<int64_t>({512, (M + 2047) / 2048, mean + mean / 4 + 64});
+    return (int)std::min<int64_t>((k + 63) / 64 * 64, p->msub);
+}
+
+// Subproblems of up to M points at most: nbins and one per msub_k points.
+int64_t subproblem_bound(const mnufft_plan_s *p, int64_t M)
+{
+    const int64_t full = (M + p->msub - 1) / p->msub;
+    // (kernel_msub of any count up to M: at most 2048, and one per 512 points)
+    const int64_t fine = p->msub_given ? 0 : std::min<int64_t>(2048, (M + 511) / 512);
+    return p->g.nbins + std::max(full, fine);
+}
 
 int alloc_points(mnufft_plan p, int64_t M)
 {
@@ -201,7 +235,7 @@ int alloc_points(mnufft_plan p, int64_t M)
     if ((rc = dalloc(p, (void **)&p->keyB, Ma * 4))) return rc;
     if ((rc = dalloc(p, (void **)&p->valB, Ma * 4))) return rc;
     if (p->method == MNUFFT_METHOD_GM && (rc = dalloc(p, (void **)&p->key_in, Ma * 4))) return rc;
-    p->nsub_cap = (int)(p->g.nbins + (M + p->msub - 1) / p->msub);
+    p->nsub_cap = (int)subproblem_bound(p, M);
     if ((rc = dalloc(p, (void **)&p->sub, (size_t)std::max(p->nsub_cap, 1) * 16))) return rc;
     if (p->method == MNUFFT_METHOD_SM) {
         // (spos_proc: each processed point's sorted position, the identity
@@ -221,6 +255,11 @@ int alloc_points(mnufft_plan p, int64_t M)
         if ((rc = dalloc(p, &p->scratch, p->scratch_bytes))) return rc;
         if ((rc = dalloc(p, (void **)&p->mergelist, (size_t)std::max(p->nsub_cap, 1) * 4)))
             return rc;
+        if (!p->msub_given && !p->mf) {
+            const size_t most = (size_t)(p->g.nbins + (M + p->msub - 1) / p->msub);
+            p->publist_bytes = (4 * most + (size_t)p->g.nbins + 2) * 4;
+            if ((rc = dalloc(p, (void **)&p->publist, p->publist_bytes))) return rc;
+        }
     }
     p->hist_cap = mn::radix_hist_elems((int)M);
     if ((rc = dalloc(p, (void **)&p->hist, p->hist_cap * 4))) return rc;
@@ -325,7 +364,7 @@ mn::Pts points_of(mnufft_plan p)
     P.binstart = p->binstart;
     P.sub = p->sub;
     P.nsub = p->nsub;
-    P.nsub_max = p->nsub_max;
+    P.nsub_max = p->nsub_k;
     P.key_in = p->key_in;
     P.suboff = p->subcount;
     P.scratch = p->scratch;
@@ -336,7 +375,7 @@ mn::Pts points_of(mnufft_plan p)
     // the heavy-bin list of the add-back follows the nbins + 1 subproblem offsets
     P.heavy = p->method == MNUFFT_METHOD_SM ? p->subcount + p->g.nbins + 1 : nullptr;
     P.cmax = p->cmax;
-    P.msub = p->msub;
+    P.msub = p->msub_k;
     P.sm = p->method == MNUFFT_METHOD_SM;
     P.nt = 1;
     P.tile_stride = (size_t)std::max(p->nsub_cap, 1) * p->ts2;
@@ -426,7 +465,7 @@ int exec_type2(mnufft_plan p, int sign, const void *f, void *c, bool sorted = fa
     int rc = modes_to_grid(p, sign, f);
     if (rc) return rc;
     // (their work items are counted in 32 bits)
-    const int64_t fit = std::max<int64_t>(1, ((int64_t)1 << 28) / std::max(p->nsub_max, 1));
+    const int64_t fit = std::max<int64_t>(1, ((int64_t)1 << 28) / std::max(p->nsub_k, 1));
     const int64_t chunk = p->method == MNUFFT_METHOD_SM ? std::min(kMaxStack, fit) : 1;
     for (int64_t t = 0; t < p->ntransf; t += chunk) {
         char *ct = (char *)c + (size_t)t * p->M * 2 * p->rsz;
@@ -461,6 +500,8 @@ int enqueue_setpts(mnufft_plan p, int64_t M, const void *x, const void *y, const
     const mn::Geom &g = p->g;
     hipStream_t s = p->stream;
     p->nsub_max = (int)(g.nbins + (M + p->msub - 1) / p->msub);
+    p->msub_k = kernel_msub(p, M);
+    p->nsub_k = (int)(g.nbins + (M + p->msub_k - 1) / p->msub_k);
     if (p->validate) MN_HIP(mn::launch_zero(p->flag, 16, s));
     // The bin-relative coordinates ride along with the keys through the radix
     // passes and must end in su.  Going backwards from the last pass the
@@ -495,7 +536,7 @@ int enqueue_setpts(mnufft_plan p, int64_t M, const void *x, const void *y, const
     p->perm = reinterpret_cast<int32_t *>(sv);
     MN_HIP(mn::launch_binstart((int)M, g.nbins, p->skey, p->binstart, s));
     const bool sm = p->method == MNUFFT_METHOD_SM;
-    MN_HIP(mn::launch_subproblems(g.nbins, p->msub, p->nsub_max, p->binstart, p->subcount,
+    MN_HIP(mn::launch_subproblems(g.nbins, p->msub_k, p->nsub_k, p->binstart, p->subcount,
                                   p->partials, p->sub, p->nsub, kMergeGroup,
                                   sm ? p->mergelist : nullptr, sm ? p->nmerge : nullptr, s));
     if (p->method == MNUFFT_METHOD_SM && !balanced(p))
@@ -503,10 +544,10 @@ int enqueue_setpts(mnufft_plan p, int64_t M, const void *x, const void *y, const
     if (balanced(p)) {
         const void *su[3] = {p->su[0], p->su[1], p->su[2]};
         if (p->mf)
-            MN_HIP(mn::launch_group(g, p->prec, p->mf, p->nsub_max, p->sub, p->nsub, su, p->perm,
+            MN_HIP(mn::launch_group(g, p->prec, p->mf, p->nsub_k, p->sub, p->nsub, su, p->perm,
                                     p->su_proc, p->perm_proc, p->spos_proc, s));
         else
-            MN_HIP(mn::launch_balance(g, p->prec, p->nsub_max, p->sub, p->nsub, su, p->perm,
+            MN_HIP(mn::launch_balance(g, p->prec, p->nsub_k, p->msub_k, p->sub, p->nsub, su, p->perm,
                                       p->su_proc, p->perm_proc, p->spos_proc, p->hslot_proc, s));
     }
     return MNUFFT_OK;
@@ -536,6 +577,7 @@ int replan(mnufft_plan p, const mnufft_opts &c)
     o.msub = c.msub;
     o.tune = MNUFFT_TUNE_OFF;
     p->msub = o.msub > 0 ? o.msub : 4096;
+    p->msub_given = o.msub > 0;
     int64_t nf[3] = {p->g.n[0], p->g.n[1], p->g.n[2]};
     int rc = plan_geometry(p, nf, p->g.w, p->g.beta, o);
     if (!rc) rc = plan_bins_device(p);
@@ -591,6 +633,7 @@ mnufft_plan new_plan(int type, int dim, const int64_t *nmodes, int iflag, int64_
     p->validate = o.validate_pts;
     p->stream = (hipStream_t)o.stream;
     p->msub = o.msub > 0 ? o.msub : 4096;
+    p->msub_given = o.msub > 0;
     p->sigma = sigma;
     p->opts = o;
     for (int d = 0; d < 3; ++d) p->N[d] = (nmodes && d < dim) ? nmodes[d] : 1;
@@ -1016,7 +1059,7 @@ int mnufft_setpts(mnufft_plan p, int64_t M, const void *x, const void *y, const 
     int rc = use_device(p);
     if (rc) return rc;
     if (p->opts.tune != MNUFFT_TUNE_OFF && (rc = tune_for_points(p, M, x, y, z)) < 0) return rc;
-    if (p->g.nbins + (M + p->msub - 1) / p->msub > 2147483647LL) return MNUFFT_ERR_ARG;
+    if (subproblem_bound(p, M) > 2147483647LL) return MNUFFT_ERR_ARG;
     p->M = -1;  // invalid until the whole setup has been enqueued
     if (M > p->Mcap && (rc = alloc_points(p, M))) {
         free_points(p);
@@ -1216,6 +1259,20 @@ int mnufft_get_subproblems(mnufft_plan p, int32_t *sub, int32_t *nsub)
     if (rc) return rc;
     if (p->type == 3) return MNUFFT_ERR_UNSUPPORTED;
     if ((rc = use_device(p))) return rc;
+    if (p->msub_k != p->msub) {
+        // the list of msub, which the kernels cut finer: made here for the caller
+        int32_t *list = p->publist, *off = list + 4 * (size_t)p->nsub_max;
+        MN_HIP(mn::launch_subproblems(p->g.nbins, p->msub, p->nsub_max, p->binstart, off,
+                                      p->partials, list, off + p->g.nbins + 1, kMergeGroup,
+                                      nullptr, nullptr, p->stream));
+        if (sub && p->nsub_max > 0)
+            MN_HIP(hipMemcpyAsync(sub, list, (size_t)p->nsub_max * 16, hipMemcpyDeviceToDevice,
+                                  p->stream));
+        if (nsub)
+            MN_HIP(hipMemcpyAsync(nsub, off + p->g.nbins + 1, 4, hipMemcpyDeviceToDevice,
+                                  p->stream));
+        return MNUFFT_OK;
+    }
     if (sub && p->nsub_max > 0)
         MN_HIP(hipMemcpyAsync(sub, p->sub, (size_t)p->nsub_max * 16, hipMemcpyDeviceToDevice,
                               p->stream));

@@ -41,3 +41,30 @@ def test_permutation_3d_wide_tiles(M):
     keys = binsort.bin_keys(pts64, inf["nfine"], inf["binsize"])
     assert np.array_equal(perm.cpu().numpy(), binsort.permutation(keys))
     assert np.array_equal(start.cpu().numpy(), binsort.bin_starts(keys, inf["nbins"]))
+
+
+@pytest.mark.parametrize("M", [600, 300000, 2048 * 576 + 2047])
+def test_kernels_cut_crowded_bins_finer(M):
+    """Without an msub the kernels cut bins finer than the list they report;
+    all points in one bin, in more pieces than one merge group."""
+    import torch
+    import workloads
+    from paper_2102_08463_amd import Plan
+    note(f"crowded {M}")
+    pts = [np.random.default_rng(7 + d).uniform(0.1, 0.2, M).astype(np.float32) for d in range(2)]
+    c = workloads.strengths(M, seed=8).astype(np.complex64)
+    eps = 1e-4
+    with Plan(1, (24, 20), eps=eps, isign=-1, binsize=(32, 32)) as p:
+        p.setpts(*[torch.from_numpy(a).cuda() for a in pts])
+        inf = p.info()
+        sub, _ = p.get_subproblems()
+        f = p.execute(torch.from_numpy(c).cuda()).cpu().numpy()
+    pts64 = [a.astype(np.float64) for a in pts]
+    keys = binsort.bin_keys(pts64, inf["nfine"][:2], inf["binsize"][:2])
+    assert np.array_equal(sub[:, :3].cpu().numpy(),
+                          binsort.subproblems(keys, inf["nbins"], inf["msub"]))
+    e1 = np.exp(-1j * np.outer(np.arange(24) - 12, pts64[0]))
+    e2 = np.exp(-1j * np.outer(np.arange(20) - 10, pts64[1]))
+    want = (e2 * c) @ e1.T
+    # the requested accuracy, with the factor the kernel's error constant takes
+    assert np.linalg.norm(f - want) <= 10 * eps * np.linalg.norm(want)
