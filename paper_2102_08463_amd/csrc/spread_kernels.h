@@ -1576,25 +1576,31 @@ k_grad_sm(Geom g, const int32_t *__restrict__ sub, const int32_t *__restrict__ n
         const int end = rec.y + rec.z;
         for (int i = rec.y + threadIdx.x; i < end; i += kThreads) {
             T kx[W], ky[W], dkx[W], dky[W];
-            const int sx = taps_der<T, W>(u0[i] + (T)P, bk, beta, kx, dkx);
+            // (not of u + P, as the interpolation does: P would round u, and the
+            // derivative has a pole at |z| = 1)
+            const int sx = taps_der<T, W>(u0[i], bk, beta, kx, dkx) + P;
             int sy = 0;
             if constexpr (DIM >= 2) {
-                sy = taps_der<T, W>(u1[i] + (T)P, bk, beta, ky, dky);
+                sy = taps_der<T, W>(u1[i], bk, beta, ky, dky) + P;
             } else {
                 ky[0] = 1;  // one row, weight one
                 dky[0] = 0;
             }
             const int j = idx[i];
             const C w = wts[j];
-            T z0 = 0;
+            T dz = 0;  // from the point to its first tap
             int sz = 0;
-            if constexpr (DIM == 3) sz = tap_start<T, W>(u2[i] + (T)P, z0);
+            if constexpr (DIM == 3) {
+                const T s = ceil(u2[i] - (T)(0.5 * W));
+                dz = s - u2[i];
+                sz = (int)s + P;
+            }
             T dr[3] = {0, 0, 0}, di[3] = {0, 0, 0};
 #pragma unroll 1
             for (int a3 = 0; a3 < (DIM == 3 ? W : 1); ++a3) {
                 T wz = 1, dwz = 0;
                 if constexpr (DIM == 3)
-                    es_val_der(z0 + (T)a3 * (T)(2.0 / W), bk, beta, wz, dwz);
+                    es_val_der(fma(dz, (T)(2.0 / W), (T)a3 * (T)(2.0 / W)), bk, beta, wz, dwz);
                 // sums over the plane with the x-derivative, the y-derivative, none
                 T xr = 0, xi = 0, yr = 0, yi = 0, pr = 0, pi = 0;
 #pragma unroll

@@ -135,3 +135,34 @@ def test_diff_3d_spiral_64cubed():
         cm = direct.type2(tuple(pm), f64, iflag=+1)
         fd = np.real(np.conj(g64[idx]) * (cp - cm) / (2 * h))
         assert rel_l2(got, fd) <= 1e-3
+
+
+@pytest.mark.parametrize("dim", [1, 2, 3])
+def test_position_gradient_at_the_window_edge(dim):
+    """Points within a few units in the last place of a grid line, where the
+    derivative of the outermost tap is large and changes fast: the LDS-staged
+    kernel takes the same window and the same tap positions as the direct one."""
+    import torch
+    from paper_2102_08463_amd import Plan
+    note(f"grad window edge {dim}d")
+    N = (64, 60, 50)[:dim]
+    M = 5000
+    R = np.random.default_rng(51)
+    out = {}
+    for method in ("sm", "gmsort"):
+        with Plan(2, N, eps=1e-5, method=method) as p:
+            if method == "sm":
+                nf = p.info()["nfine"]
+                pts = []
+                for d in range(dim):
+                    x = (2 * np.pi * (R.integers(0, nf[d], M) / nf[d] - 0.5)).astype(np.float32)
+                    x += R.integers(-3, 4, M).astype(np.float32) * np.spacing(np.abs(x))
+                    pts.append(torch.from_numpy(x).cuda())
+                _, f = make_complex(tuple(N[::-1]), "f32", seed=52)
+                _, g = make_complex(M, "f32", seed=53)
+            p.setpts(*pts)
+            out[method] = [a.cpu().numpy() for a in p.interp_grad(f, g)]
+    # same taps: what differs is the order of about 3 w sums, whose terms exceed
+    # the result by a factor of up to about 20 (30 * 20 * 2^-24)
+    for a, b in zip(out["sm"], out["gmsort"]):
+        assert np.max(np.abs(a - b)) <= 4e-5 * np.max(np.abs(b))
