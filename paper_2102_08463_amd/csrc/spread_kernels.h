@@ -647,10 +647,17 @@ k_spread_sm(Geom g, const int32_t *__restrict__ sub, const int32_t *__restrict__
 // HBM traffic, so it is done once.  The same pass loads the coordinates and
 // keeps each point's histogram slot (16 bits) in LDS, so the histogram pass
 // reads LDS only.
-// (LDS use, the tile plus the staged strengths, allows about three
-// workgroups per CU, i.e. three waves per SIMD; the register budget follows.)
+// In 3D a bin holds few points, so each thread keeps the strengths and slots
+// of its first kHold points in registers instead: the LDS is the tile alone
+// (34 KB at w = 6 with 16 x 8 x 8 bins) and four workgroups fit a CU where the
+// stage left room for three: 1e-5, 2^24 points on 256^3 cells 1041 -> 929 us,
+// 1e6 points on 128^3 91 -> 80.  2D bins hold about ten points a thread, too
+// many for registers, and tile and stage fit four times anyway.  (Batches
+// look their slots up from the coordinates and keep the stage.)
+constexpr int hold_points(int dim, bool batch) { return dim == 3 && !batch ? 6 : 0; }
 template <typename T, int DIM, int W, bool BATCH>
-__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3)))
+__global__ void __launch_bounds__(kThreads)
+__attribute__((amdgpu_waves_per_eu(hold_points(DIM, BATCH) ? 4 : 3)))
 k_spread_smp(Geom g, const int32_t *__restrict__ sub, const int32_t *__restrict__ nsubp,
              const float *__restrict__ u0, const float *__restrict__ u1,
              const float *__restrict__ u2, const int32_t *__restrict__ idx,
@@ -694,8 +701,30 @@ k_spread_smp(Geom g, const int32_t *__restrict__ sub, const int32_t *__restrict_
         // staged points (the loads are issued kPre at a time so that their
         // latencies overlap)
         constexpr int kPre = 8;
+        constexpr int kHold = hold_points(DIM, BATCH);
+        const int past = rec.y + tid + kHold * kThreads;  // first point not held
         float am = 0.f;
-        for (int i0 = rec.y + tid; i0 < end; i0 += kPre * kThreads) {
+        float2 hc[kHold > 0 ? kHold : 1];
+        int hh[kHold > 0 ? kHold : 1];
+        if constexpr (kHold > 0) {
+            int pj[kHold];
+#pragma unroll
+            for (int k = 0; k < kHold; ++k) {
+                const int i = rec.y + tid + k * kThreads;
+                const bool in = i < end;
+                pj[k] = in ? idx[i] : -1;
+                hh[k] = in ? (int)hslot[i] : 0;
+            }
+#pragma unroll
+            for (int k = 0; k < kHold; ++k) {
+                hc[k] = make_float2(0.f, 0.f);
+                if (pj[k] >= 0) hc[k] = c[pj[k]];
+            }
+#pragma unroll
+            for (int k = 0; k < kHold; ++k)
+                am = fmaxf(am, fmaxf(fabsf(hc[k].x), fabsf(hc[k].y)));
+        }
+        for (int i0 = past; i0 < end; i0 += kPre * kThreads) {
             int pj[kPre], hs[kPre];
 #pragma unroll
             for (int k = 0; k < kPre; ++k) {
@@ -743,7 +772,15 @@ k_spread_smp(Geom g, const int32_t *__restrict__ sub, const int32_t *__restrict_
             return ii - rec.y < stage_cap ? cs[ii - rec.y] : c[idx[ii]];
         };
         // histogram of ceil(a_j 2^hu) over the start cells
-        for (int i = rec.y + tid; i < end; i += kThreads) {
+        const auto entry = [&](float2 cv) {
+            return (unsigned)ceilf(ldexpf(fmaxf(fabsf(cv.x), fabsf(cv.y)), hu));
+        };
+        if constexpr (kHold > 0) {
+#pragma unroll
+            for (int k = 0; k < kHold; ++k)
+                if (rec.y + tid + k * kThreads < end) atomicAdd(H + hh[k], entry(hc[k]));
+        }
+        for (int i = past; i < end; i += kThreads) {
             const int j = i - rec.y;
             int hs;
             float2 cv;
@@ -757,8 +794,7 @@ k_spread_smp(Geom g, const int32_t *__restrict__ sub, const int32_t *__restrict_
                                             DIM == 3 ? start_cell<float, W>(u2[i]) : 0);
                 cv = c[idx[i]];
             }
-            const unsigned hv = (unsigned)ceilf(ldexpf(fmaxf(fabsf(cv.x), fabsf(cv.y)), hu));
-            atomicAdd(H + hs, hv);
+            atomicAdd(H + hs, entry(cv));
         }
         __syncthreads();
         const unsigned B = tile_bound<DIM, W>(H, hg, redu);
@@ -787,16 +823,22 @@ k_spread_smp(Geom g, const int32_t *__restrict__ sub, const int32_t *__restrict_
             nu0 = u0[i];
             if constexpr (DIM >= 2) nu1 = u1[i];
             if constexpr (DIM == 3) nu2 = u2[i];
-            ncv = strength(i);
+            if constexpr (kHold == 0) ncv = strength(i);
         }
         for (; i < end; i += kThreads) {
             const float x0 = nu0, x1 = nu1, x2 = nu2;
-            const float2 cv = ncv;
+            const float2 cv = kHold > 0 ? hc[0] : ncv;
+            if constexpr (kHold > 0) {
+                // the held strengths move up; points past them are gathered again
+#pragma unroll
+                for (int k = 0; k + 1 < kHold; ++k) hc[k] = hc[k + 1];
+                if (i + kHold * kThreads < end) hc[kHold - 1] = c[idx[i + kHold * kThreads]];
+            }
             if (i + kThreads < end) {
                 nu0 = u0[i + kThreads];
                 if constexpr (DIM >= 2) nu1 = u1[i + kThreads];
                 if constexpr (DIM == 3) nu2 = u2[i + kThreads];
-                ncv = strength(i + kThreads);
+                if constexpr (kHold == 0) ncv = strength(i + kThreads);
             }
             float kx[W], ky[W];
             const int sx = taps<float, W>(x0 + (float)P, bk, kx);
@@ -1722,15 +1764,19 @@ hipError_t spread_wb(const Geom &g, int method, const Pts &P, const void *c, voi
         }
         if ((part & 1) && !done) {
             if constexpr (packed) {
+                // (bins are accepted by the size with the stage, whatever is staged)
+                const bool held = hold_points(DIM, BATCH) > 0;
+                if (held && !P.hslot) return hipErrorInvalidValue;
+                const size_t need = held ? (size_t)sm_tile_stride(g) * 4 : lds;
                 auto pk = k_spread_smp<T, DIM, W, BATCH>;
-                if (lds > 65536)
+                if (need > 65536)
                     (void)hipFuncSetAttribute((const void *)pk,
-                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-                hipLaunchKernelGGL(pk, dim3(sm_grid(P), P.nt), dim3(kThreads), lds, s, g, P.sub,
+                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)need);
+                hipLaunchKernelGGL(pk, dim3(sm_grid(P), P.nt), dim3(kThreads), need, s, g, P.sub,
                                    P.nsub, (const float *)P.u[0], (const float *)P.u[1],
                                    (const float *)P.u[2], sm_index(P), P.hslot, (const float2 *)c,
                                    (float *)P.scratch, P.ts2, sm_tile_stride(g), (float)bk,
-                                   smp_stage(DIM, P.msub), P.tg, P.bin_t, P.q0, tst);
+                                   held ? 0 : smp_stage(DIM, P.msub), P.tg, P.bin_t, P.q0, tst);
             } else {
                 auto kern = k_spread_sm<T, DIM, W, BATCH>;
                 if (lds > 65536)

@@ -68,3 +68,30 @@ def test_kernels_cut_crowded_bins_finer(M):
     want = (e2 * c) @ e1.T
     # the requested accuracy, with the factor the kernel's error constant takes
     assert np.linalg.norm(f - want) <= 10 * eps * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("M", [1, 255, 1536, 1537, 4096, 9000])
+@pytest.mark.parametrize("sorted_order", [False, True])
+def test_3d_bin_with_points_past_the_held_ones(M, sorted_order):
+    """3D spreading keeps six points a thread (1536 a subproblem) and gathers
+    the strengths of the rest again; all points in one bin, against the sums."""
+    import torch
+    import workloads
+    from paper_2102_08463_amd import Plan
+    note(f"held points {M} {sorted_order}")
+    eps, N = 1e-5, (12, 10, 9)
+    pts = [np.random.default_rng(9 + d).uniform(0.05, 0.2, M).astype(np.float32) for d in range(3)]
+    c = workloads.strengths(M, seed=10).astype(np.complex64)
+    with Plan(1, N, eps=eps, isign=-1, binsize=(16, 8, 8), msub=4096) as p:
+        p.setpts(*[torch.from_numpy(a).cuda() for a in pts])
+        ct = torch.from_numpy(c).cuda()
+        if sorted_order:
+            perm, _ = p.get_sort()
+            f = p.execute_sorted(ct[perm.long()].contiguous())
+        else:
+            f = p.execute(ct)
+        f = f.cpu().numpy()
+    e = [np.exp(-1j * np.outer(np.arange(n) - n // 2, a.astype(np.float64)))
+         for n, a in zip(N, pts)]
+    want = np.einsum("zj,yj,xj->zyx", e[2], e[1], e[0] * c, optimize=True)
+    assert np.linalg.norm(f - want) <= 10 * eps * np.linalg.norm(want)
