@@ -493,7 +493,8 @@ typedef struct mnufft_batch_s *mnufft_batch;
  *   nmodes    host array ntr x 3: N_1, N_2 (, N_3) of transform t at 3t ..
  *   npts      host array ntr: points of each transform (>= 0, total <= 2^31 - 1)
  *   binsize   host array ntr x 3 of bin extents, or NULL; 0 entries take
- *             opts->binsize or the plan default
+ *             opts->binsize or the default: in 3D the plan's, in 2D one size
+ *             for all transforms that gives the batch enough bins
  *   msub      host array ntr of subproblem sizes, or NULL; 0 entries take
  *             opts->msub or the plan default
  *   opts      NULL or options; method must be AUTO or SM

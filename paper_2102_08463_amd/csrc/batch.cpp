@@ -317,6 +317,32 @@ int mnufft_batch_makeplan(int type, int dim, int ntr, const int64_t *nmodes, con
     b->geo.resize(ntr);
     int64_t pf[3] = {0, 0, 0};  // correction factors per dimension
     std::vector<int2> cv[3];
+    // A plan's default bins are halved until its grid alone has kMinBins of
+    // them.  The transforms of a 2D batch fill the GPU together and take the
+    // same bins, halved until the batch has that many: wider bins have less
+    // halo to clear, store and sum per cell and shorter keys to sort, and one
+    // class of bins is one launch instead of several forked ones.  64 grids of
+    // 128^2 to 1024^2 with 200000 points each (type 1): 2900 -> 2395 us, 5000
+    // points each: 1266 -> 815; 4 such grids 197 -> 109 (twice kMinBins: 116,
+    // four times: 124); small radial sets at 16 grids of 48^2 to 256^2, whose
+    // crowded bins grow, 1016 -> 1046.  (3D bins stay the plan's: larger ones
+    // may not fit in LDS.)
+    int batch_m[2] = {32, 32};
+    for (; dim == 2;) {
+        int64_t nb = 0;
+        for (int t = 0; t < ntr; ++t) {
+            int64_t own = 1;
+            for (int d = 0; d < 2; ++d) {
+                const int64_t n = mn::host::fine_size(nmodes[3 * t + d], w, sigma);
+                const int64_t m = std::min<int64_t>(batch_m[d], n);
+                own *= (n + m - 1) / m;
+            }
+            nb += own;
+        }
+        const int dl = batch_m[1] > batch_m[0] ? 1 : 0;
+        if (nb >= mn::host::kMinBins || batch_m[dl] <= mn::host::kMinSide) break;
+        batch_m[dl] /= 2;
+    }
     int64_t bin_off = 0, pt_off = 0, grid_off = 0, mode_off = 0, nsub_max = 0;
     int mmax[3] = {1, 1, 1};
     for (int t = 0; t < ntr; ++t) {
@@ -328,6 +354,7 @@ int mnufft_batch_makeplan(int type, int dim, int ntr, const int64_t *nmodes, con
             nf[d] = d < dim ? mn::host::fine_size(nmodes[3 * t + d], w, sigma) : 1;
         int defm[3];
         mn::host::default_bins(dim, nf, defm);
+        for (int d = 0; d < 2 && dim == 2 && ntr > 1; ++d) defm[d] = batch_m[d];
         for (int d = 0; d < 3; ++d) {
             const int64_t N = d < dim ? nmodes[3 * t + d] : 1;
             const int64_t n = nf[d];

@@ -150,3 +150,39 @@ def test_small_mixed_batch_3d(prec, eps, ntype):
                                fm[t].astype(np.complex128), iflag=+1)
             assert rel_l2(got, ref) <= 10 * eps, t
     b.destroy()
+
+
+@pytest.mark.parametrize("typ", [1, 2])
+@pytest.mark.parametrize("modes", [
+    [(20, 12)],                                        # one transform: the plan's bins
+    [(5, 7), (300, 243), (64, 64), (16, 16)],          # bins wider than a grid
+    [(500, 400), (512, 512), (24, 30)],                # 32 x 32 throughout
+    [(24, 20), (30, 26)],                              # halved to the narrowest
+])
+def test_default_bins_shared_by_the_batch(typ, modes):
+    """Whatever default bins a batch takes, each transform is what its own plan
+    computes, up to the rounding of either (both within 10 eps of the sums)."""
+    import torch
+    import workloads
+    from paper_2102_08463_amd import Batch, Plan
+    note(f"batch default bins {typ} {modes}")
+    eps = 1e-5
+    M = [3000 + 977 * t for t in range(len(modes))]
+    pts = [workloads.uniform(m, 2, seed=60 + t) for t, m in enumerate(M)]
+    x = [torch.from_numpy(np.concatenate([p[d] for p in pts]).astype(np.float32)).cuda()
+         for d in range(2)]
+    n_in = sum(M) if typ == 1 else sum(a * b for a, b in modes)
+    data = torch.from_numpy(workloads.strengths(n_in, seed=61).astype(np.complex64)).cuda()
+    with Batch(typ, modes, M, eps=eps) as b:
+        b.setpts(*x)
+        out = b.execute(data)
+    at = kat = 0
+    for md, m in zip(modes, M):
+        k = md[0] * md[1]
+        d = data[at:at + m] if typ == 1 else data[kat:kat + k]
+        with Plan(typ, md, eps=eps) as p:
+            p.setpts(*[v[at:at + m].contiguous() for v in x])
+            got = p.execute(d.contiguous()).reshape(-1)
+        want = out[kat:kat + k] if typ == 1 else out[at:at + m]
+        assert float(torch.linalg.norm(got - want) / torch.linalg.norm(got)) <= 20 * eps
+        at, kat = at + m, kat + k
