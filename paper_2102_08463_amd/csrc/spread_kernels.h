@@ -1767,7 +1767,15 @@ hipError_t spread_wb(const Geom &g, int method, const Pts &P, const void *c, voi
                 // (bins are accepted by the size with the stage, whatever is staged)
                 const bool held = hold_points(DIM, BATCH) > 0;
                 if (held && !P.hslot) return hipErrorInvalidValue;
-                const size_t need = held ? (size_t)sm_tile_stride(g) * 4 : lds;
+                const size_t tile = (size_t)sm_tile_stride(g) * 4;
+                // (w = 7 and 8: the 32 x 32 tile is 1.2 KB larger than at w = 6
+                // and the full stage would leave room for three workgroups, not
+                // four: 64 grids with 32 x 32 bins 2396 -> 2250 us, 1e7 points
+                // type 1 + adjoint on 2048^2 cells 580 -> 560)
+                const int cap = smp_stage(DIM, P.msub);
+                const int fit = (int)((40960 - 512 - (int64_t)tile) / 10 / 8 * 8);
+                const int stage = held ? 0 : DIM == 2 && fit >= 2560 ? std::min(cap, fit) : cap;
+                const size_t need = tile + (size_t)8 * stage + ((size_t)2 * stage + 15) / 16 * 16;
                 auto pk = k_spread_smp<T, DIM, W, BATCH>;
                 if (need > 65536)
                     (void)hipFuncSetAttribute((const void *)pk,
@@ -1776,7 +1784,7 @@ hipError_t spread_wb(const Geom &g, int method, const Pts &P, const void *c, voi
                                    P.nsub, (const float *)P.u[0], (const float *)P.u[1],
                                    (const float *)P.u[2], sm_index(P), P.hslot, (const float2 *)c,
                                    (float *)P.scratch, P.ts2, sm_tile_stride(g), (float)bk,
-                                   held ? 0 : smp_stage(DIM, P.msub), P.tg, P.bin_t, P.q0, tst);
+                                   stage, P.tg, P.bin_t, P.q0, tst);
             } else {
                 auto kern = k_spread_sm<T, DIM, W, BATCH>;
                 if (lds > 65536)
