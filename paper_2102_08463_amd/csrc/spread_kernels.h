@@ -936,81 +936,84 @@ k_tile_merge(int32_t *__restrict__ nmergep, const int32_t *__restrict__ mergelis
     }
 }
 
-// Each fine-grid cell is the sum of the tile cells that cover it (the wrapped
+// el = q n + r; in 32 bits where el allows (a 64-bit division is about a
+// hundred instructions).
+__device__ __forceinline__ long long divmod(long long el, int n, int &r)
+{
+    if (el <= 0xffffffffLL) {
+        const unsigned e = (unsigned)el, q = e / (unsigned)n;
+        r = (int)(e - q * (unsigned)n);
+        return q;
+    }
+    r = (int)(el % n);
+    return el / n;
+}
+
+// One fine-grid cell as the sum of the tile cells that cover it (the wrapped
 // add-back of eq. addtoglobal, computed as a gather): per dimension, cov_i
 // lists for grid index l the pairs (bin index, offset in that bin's padded
-// tile) that land on l, up to kmax_i of them (unused entries have bin -1).
+// tile) that land on l, up to k_i of them (unused entries have bin -1).
 // Bins with more than G tiles are read through their merged leaders.
-template <typename T, int DIM, bool BATCH>
-__global__ void __launch_bounds__(kThreads)
-k_tile_gather(Geom g, const int32_t *__restrict__ suboff, const T *__restrict__ scratch,
-              int ts2, int G, const int2 *__restrict__ cov0_, const int2 *__restrict__ cov1_,
-              const int2 *__restrict__ cov2_, int k0_, int k1_, int k2_, int P,
-              typename Cplx<T>::type *__restrict__ grid, long long ncell_all,
-              const TGeom *__restrict__ tg, int T_, TStride tst)
+template <typename T, int DIM>
+__device__ __forceinline__ typename Cplx<T>::type
+gather_cell(const Geom &gg, const int32_t *__restrict__ suboff, const T *__restrict__ scratch,
+            int ts2, int G, const int2 *__restrict__ cov0, const int2 *__restrict__ cov1,
+            const int2 *__restrict__ cov2, int k0, int k1, int k2, int p1, int p2, int boff,
+            int l1, int l2, int l3)
 {
-    scratch += blockIdx.y * tst.tiles;
-    grid += blockIdx.y * tst.grid;
-    __shared__ long long soff[BATCH ? kTCache : 1];
-    const auto fld = [](const TGeom &a) { return a.grid_off; };
-    bool cached = false;
-    if constexpr (BATCH) cached = cache_offsets(soff, tg, T_, fld);
-    for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < ncell_all;
-         e += (long long)gridDim.x * blockDim.x) {
-        Geom gg = g;
-        const int2 *cov0 = cov0_, *cov1 = cov1_, *cov2 = cov2_;
-        int k0 = k0_, k1 = k1_, k2 = k2_, boff = 0;
-        long long el = e;
-        if constexpr (BATCH) {
-            const TGeom &tt =
-                tg[cached ? find_cached(soff, T_, e) : find_transform(tg, T_, e, fld)];
-            gg = geom_of(g, tt);
-            cov0 = cov0_ + tt.cov_off[0];
-            cov1 = cov1_ + tt.cov_off[1];
-            cov2 = DIM == 3 ? cov2_ + tt.cov_off[2] : cov2_;
-            k0 = tt.kmax[0];
-            k1 = tt.kmax[1];
-            k2 = tt.kmax[2];
-            boff = tt.bin_off;
-            el = e - tt.grid_off;
+    T ar = 0, ai = 0;
+    for (int j3 = 0; j3 < (DIM == 3 ? k2 : 1); ++j3) {
+        int nb3 = 0, s3 = 0;
+        if constexpr (DIM == 3) {
+            const int2 c3 = cov2[(size_t)l3 * k2 + j3];
+            if (c3.x < 0) break;
+            nb3 = c3.x;
+            s3 = c3.y;
         }
-        const int p1 = gg.m[0] + 2 * P, p2 = gg.m[1] + 2 * P;
-        const int l1 = (int)(el % gg.n[0]);
-        const long long r = el / gg.n[0];
-        const int l2 = (int)(r % gg.n[1]);
-        const int l3 = DIM == 3 ? (int)(r / gg.n[1]) : 0;
-        if constexpr (DIM == 1) k1 = 1;  // one row: the single entry (bin 0, offset 0)
-        T ar = 0, ai = 0;
-        for (int j3 = 0; j3 < (DIM == 3 ? k2 : 1); ++j3) {
-            int nb3 = 0, s3 = 0;
-            if constexpr (DIM == 3) {
-                const int2 c3 = cov2[(size_t)l3 * k2 + j3];
-                if (c3.x < 0) break;
-                nb3 = c3.x;
-                s3 = c3.y;
-            }
-            for (int j2 = 0; j2 < k1; ++j2) {
-                const int2 c2 = DIM >= 2 ? cov1[(size_t)l2 * k1 + j2] : make_int2(0, 0);
-                if (c2.x < 0) break;
-                for (int j1 = 0; j1 < k0; ++j1) {
-                    const int2 c1 = cov0[(size_t)l1 * k0 + j1];
-                    if (c1.x < 0) break;
-                    const int b = boff + c1.x + gg.B[0] * (c2.x + gg.B[1] * nb3);
-                    const int first = suboff[b], k = suboff[b + 1] - first;
-                    const int step = k > G ? G : 1;
-                    const size_t off = 2 * ((size_t)c1.y + (size_t)p1 * (c2.y + (size_t)p2 * s3));
-                    for (int q = first; q < first + k; q += step) {
-                        const T *t = scratch + (size_t)q * ts2 + off;
-                        ar += t[0];
-                        ai += t[1];
-                    }
+        for (int j2 = 0; j2 < (DIM >= 2 ? k1 : 1); ++j2) {
+            // (1D: one row, the single entry bin 0, offset 0)
+            const int2 c2 = DIM >= 2 ? cov1[(size_t)l2 * k1 + j2] : make_int2(0, 0);
+            if (c2.x < 0) break;
+            for (int j1 = 0; j1 < k0; ++j1) {
+                const int2 c1 = cov0[(size_t)l1 * k0 + j1];
+                if (c1.x < 0) break;
+                const int b = boff + c1.x + gg.B[0] * (c2.x + gg.B[1] * nb3);
+                const int first = suboff[b], k = suboff[b + 1] - first;
+                const int step = k > G ? G : 1;
+                const size_t off = 2 * ((size_t)c1.y + (size_t)p1 * (c2.y + (size_t)p2 * s3));
+                for (int q = first; q < first + k; q += step) {
+                    const T *t = scratch + (size_t)q * ts2 + off;
+                    ar += t[0];
+                    ai += t[1];
                 }
             }
         }
-        typename Cplx<T>::type out;
-        out.x = ar;
-        out.y = ai;
-        grid[e] = out;
+    }
+    typename Cplx<T>::type out;
+    out.x = ar;
+    out.y = ai;
+    return out;
+}
+
+// Cell-wise add-back of a plan with a cover table of more than two entries
+// per grid index.
+template <typename T, int DIM>
+__global__ void __launch_bounds__(kThreads)
+k_tile_gather(Geom g, const int32_t *__restrict__ suboff, const T *__restrict__ scratch,
+              int ts2, int G, const int2 *__restrict__ cov0, const int2 *__restrict__ cov1,
+              const int2 *__restrict__ cov2, int k0, int k1, int k2, int P,
+              typename Cplx<T>::type *__restrict__ grid, long long ncell, TStride tst)
+{
+    scratch += blockIdx.y * tst.tiles;
+    grid += blockIdx.y * tst.grid;
+    const int p1 = g.m[0] + 2 * P, p2 = g.m[1] + 2 * P;
+    for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < ncell;
+         e += (long long)gridDim.x * blockDim.x) {
+        int l1, l2;
+        const long long r = divmod(e, g.n[0], l1);
+        const int l3 = (int)divmod(r, g.n[1], l2);
+        grid[e] = gather_cell<T, DIM>(g, suboff, scratch, ts2, G, cov0, cov1, cov2, k0, k1, k2, p1,
+                                      p2, 0, l1, l2, l3);
     }
 }
 
@@ -1019,6 +1022,10 @@ k_tile_gather(Geom g, const int32_t *__restrict__ suboff, const T *__restrict__ 
 // every cell's cover entries, the first tile of each covering bin and those
 // tiles' values are loaded in three rounds of independent loads, not one
 // dependent chain per covering bin.  The sum is taken in the same order.
+// Bound by the latency of those rounds.  A batch always comes here: few of its
+// cells have a third entry, next to a last bin narrower than the halos, and
+// those take the chain (64 grids, 2.1e7 cells in all: 5000 points each 817 ->
+// 760 us a pass, 200000 each 2250 -> 2192).
 template <typename T, int DIM, bool BATCH>
 __global__ void __launch_bounds__(kThreads)
 k_tile_gather2(Geom g, const int32_t *__restrict__ suboff, const T *__restrict__ scratch,
@@ -1034,15 +1041,13 @@ k_tile_gather2(Geom g, const int32_t *__restrict__ suboff, const T *__restrict__
     const auto fld = [](const TGeom &a) { return a.grid_off; };
     bool cached = false;
     if constexpr (BATCH) cached = cache_offsets(soff, tg, T_, fld);
-    for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < ncell;
-         e += (long long)gridDim.x * blockDim.x) {
+    const auto cell = [&](long long e, int tr) {
         Geom gg = g;
         const int2 *cov0 = cov0_, *cov1 = cov1_, *cov2 = cov2_;
         int k0 = k0_, k1 = k1_, k2 = k2_, boff = 0;
         long long el = e;
         if constexpr (BATCH) {
-            const TGeom &tt =
-                tg[cached ? find_cached(soff, T_, e) : find_transform(tg, T_, e, fld)];
+            const TGeom &tt = tg[tr];
             gg = geom_of(g, tt);
             cov0 = cov0_ + tt.cov_off[0];
             cov1 = cov1_ + tt.cov_off[1];
@@ -1054,10 +1059,18 @@ k_tile_gather2(Geom g, const int32_t *__restrict__ suboff, const T *__restrict__
             el = e - tt.grid_off;
         }
         const int p1 = gg.m[0] + 2 * P, p2 = gg.m[1] + 2 * P;
-        const int l1 = (int)(el % gg.n[0]);
-        const long long r = el / gg.n[0];
-        const int l2 = (int)(r % gg.n[1]);
-        const int l3 = DIM == 3 ? (int)(r / gg.n[1]) : 0;
+        int l1, l2;
+        const long long r = divmod(el, gg.n[0], l1);
+        const int l3 = (int)divmod(r, gg.n[1], l2);
+        if constexpr (BATCH) {
+            if ((k0 > 2 && cov0[(size_t)l1 * k0 + 2].x >= 0) ||
+                (k1 > 2 && cov1[(size_t)l2 * k1 + 2].x >= 0) ||
+                (DIM == 3 && k2 > 2 && cov2[(size_t)l3 * k2 + 2].x >= 0)) {
+                grid[e] = gather_cell<T, DIM>(gg, suboff, scratch, ts2, G, cov0, cov1, cov2, k0,
+                                              k1, k2, p1, p2, boff, l1, l2, l3);
+                return;
+            }
+        }
         int2 c1[2], c2[2], c3[2];
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
@@ -1105,6 +1118,19 @@ k_tile_gather2(Geom g, const int32_t *__restrict__ suboff, const T *__restrict__
         out.x = ar;
         out.y = ai;
         grid[e] = out;
+    };
+    for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < ncell;
+         e += (long long)gridDim.x * blockDim.x) {
+        if constexpr (BATCH) {
+            // a wave's cells are mostly one transform's, whose geometry then
+            // takes scalar loads instead of some fifteen per cell
+            const int tr = cached ? find_cached(soff, T_, e) : find_transform(tg, T_, e, fld);
+            const int tr0 = __builtin_amdgcn_readfirstlane(tr);
+            if (__all(tr == tr0)) cell(e, tr0);
+            else cell(e, tr);
+        } else {
+            cell(e, 0);
+        }
     }
 }
 
@@ -1819,18 +1845,17 @@ hipError_t spread_wb(const Geom &g, int method, const Pts &P, const void *c, voi
         }
         const long long ncell = P.ncells;
         const int ggrid = (int)std::min<long long>((ncell + kThreads - 1) / kThreads, 16384);
-        // (for a batch, P.kmax holds the largest table width over its transforms)
-        if (P.kmax[0] <= 2 && (DIM == 1 || P.kmax[1] <= 2) && (DIM <= 2 || P.kmax[2] <= 2)) {
+        if (BATCH || (P.kmax[0] <= 2 && (DIM == 1 || P.kmax[1] <= 2) && (DIM <= 2 || P.kmax[2] <= 2))) {
             hipLaunchKernelGGL((k_tile_gather2<T, DIM, BATCH>), dim3(std::max(ggrid, 1), P.nt),
                                dim3(kThreads), 0, s, g, P.suboff, (const T *)P.scratch, P.ts2,
                                P.G, P.cov[0], P.cov[1], P.cov[2], P.kmax[0], P.kmax[1],
                                P.kmax[2], (W + 1) / 2, (C *)grid, ncell, P.tg, P.T, tst);
             return hipGetLastError();
         }
-        hipLaunchKernelGGL((k_tile_gather<T, DIM, BATCH>), dim3(std::max(ggrid, 1), P.nt), dim3(kThreads),
+        hipLaunchKernelGGL((k_tile_gather<T, DIM>), dim3(std::max(ggrid, 1), P.nt), dim3(kThreads),
                            0, s, g, P.suboff, (const T *)P.scratch, P.ts2, P.G, P.cov[0], P.cov[1],
                            P.cov[2], P.kmax[0], P.kmax[1], P.kmax[2], (W + 1) / 2, (C *)grid, ncell,
-                           P.tg, P.T, tst);
+                           tst);
     } else if (part & 1) {
         const bool gm = method == 1;
         hipLaunchKernelGGL((k_spread_gm<T, DIM, W>), dim3(cdiv(P.M, kThreads)), dim3(kThreads),
