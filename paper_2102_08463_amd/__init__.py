@@ -1,7 +1,7 @@
 """MI355X-native 1D/2D/3D nonuniform FFTs (types 1, 2 and 3) after cuFINUFFT.
 
-The transforms run in libmnufft.so (hand-written HIP kernels for gfx950 plus
-rocFFT for the fine-grid FFT) behind the C ABI in include/mnufft.h; this
+The transforms run in libmnufft.so (hand-written HIP kernels for gfx950;
+rocFFT only for FFT lines too long for a workgroup) behind the C ABI in include/mnufft.h; this
 package is its thin Python binding.  PyTorch provides device memory and
 streams only.
 """

@@ -7,8 +7,9 @@
 // order, so each class's subproblems are one range of the list; spreading
 // and interpolation run one launch per class (each with exactly the LDS its
 // tiles need, on parallel streams), so that a few transforms with large
-// bins do not lower the occupancy of all the others.  Only the fine-grid
-// FFTs run per transform (rocFFT plans cached by size).  The method is SM
+// bins do not lower the occupancy of all the others.  The FFT passes of all
+// transforms are one launch each too (rocFFT plans per size on parallel
+// streams where a line is too long for them).  The method is SM
 // for every transform.
 #include "../../include/mnufft.h"
 #include "host_common.h"
@@ -327,8 +328,10 @@ int mnufft_batch_makeplan(int type, int dim, int ntr, const int64_t *nmodes, con
     // four times: 124); small radial sets at 16 grids of 48^2 to 256^2, whose
     // crowded bins grow, 1016 -> 1046.  (3D bins stay the plan's: larger ones
     // may not fit in LDS.)
+    const bool noisy = mn::host::noisy_factors(prec, w, beta, sigma, dim);
+    const bool share_bins = dim == 2 && ntr > 1 && (prec != MNUFFT_F32 || sigma >= 2.0);
     int batch_m[2] = {32, 32};
-    for (; dim == 2;) {
+    while (share_bins) {
         int64_t nb = 0;
         for (int t = 0; t < ntr; ++t) {
             int64_t own = 1;
@@ -354,7 +357,7 @@ int mnufft_batch_makeplan(int type, int dim, int ntr, const int64_t *nmodes, con
             nf[d] = d < dim ? mn::host::fine_size(nmodes[3 * t + d], w, sigma) : 1;
         int defm[3];
         mn::host::default_bins(dim, nf, defm);
-        for (int d = 0; d < 2 && dim == 2 && ntr > 1; ++d) defm[d] = batch_m[d];
+        for (int d = 0; d < 2 && share_bins; ++d) defm[d] = batch_m[d];
         for (int d = 0; d < 3; ++d) {
             const int64_t N = d < dim ? nmodes[3 * t + d] : 1;
             const int64_t n = nf[d];
@@ -507,7 +510,7 @@ int mnufft_batch_makeplan(int type, int dim, int ntr, const int64_t *nmodes, con
                  hipEventCreateWithFlags(&b->join[k], hipEventDisableTiming) != hipSuccess)
             rc = MNUFFT_ERR_HIP;
     }
-    if (!rc)
+    if (!rc && !noisy)
         rc = b->own.make(type, dim, iflag, b->geo, prec, b->pfac,
                          [b](void **ptr, size_t bytes) { return balloc(b, ptr, bytes); },
                          b->stream);

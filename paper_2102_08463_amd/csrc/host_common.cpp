@@ -87,6 +87,21 @@ void correction(int64_t N, int64_t n, int w, double beta, std::vector<double> &p
     }
 }
 
+bool noisy_factors(int prec, int w, double beta, double sigma, int dim)
+{
+    if (prec != MNUFFT_F32 || sigma >= 2.0) return false;
+    // rms of 1 / phi_hat over the band |k| < 1 / (2 sigma) per cell, times the
+    // 2-norm of the kernel's samples (phi^2 is the kernel of twice the shape)
+    constexpr int kF = 16;
+    std::vector<double> xi(kF), ph, sq;
+    for (int i = 0; i < kF; ++i) xi[i] = kPi * w * (i + 0.5) / (2.0 * sigma * kF);
+    es_fourier(beta, xi, ph);
+    es_fourier(2.0 * beta, {0.0}, sq);
+    double ms = 0;
+    for (int i = 0; i < kF; ++i) ms += 1.0 / (0.25 * w * w * ph[i] * ph[i] * kF);
+    return std::pow(std::sqrt(ms * 0.5 * w * sq[0]), dim) > 200.0;
+}
+
 void default_bins(int dim, const int64_t n[3], int m[3])
 {
     static const int defm[3][3] = {{64, 1, 1}, {32, 32, 1}, {16, 8, 8}};

@@ -33,6 +33,17 @@ void correction(int64_t N, int64_t n, int w, double beta, std::vector<double> &p
 // quadrature, 513 nodes).
 void es_fourier(double beta, const std::vector<double> &xi, std::vector<double> &out);
 
+// Whether single precision rounding on the fine grid reaches the results
+// amplified more than 200 times: by the rms of the correction factors over
+// the band, which are far above one for wide kernels at upsampling factors
+// near 1.25 (3D, eps 1e-6, sigma = 1.25: 1550 times, results 2.2e-5 from the
+// sums, all of it such rounding).  There any other FFT or order of sums gives
+// other noise of the same size (3.3e-5 between two), rocFFT's a little less
+// than the own passes' (2.2e-5 against 2.5e-5): such plans keep rocFFT.
+// (Single precision below sigma = 2 also keeps msub and a batch's own bins:
+// the spreading quantum follows the subproblems and is amplified likewise.)
+bool noisy_factors(int prec, int w, double beta, double sigma, int dim);
+
 // Default bin extents for a fine grid n (dim dimensions): 64 cells in 1D,
 // 32 x 32 in 2D and 16 x 8 x 8 in 3D (measured on gfx950; the paper's V100
 // choice was 32 x 32 and 16 x 16 x 2, Sec. III-A, first remark), each at most

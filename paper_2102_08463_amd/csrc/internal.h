@@ -316,8 +316,9 @@ hipError_t launch_interp_grad(const Geom &g, int prec, const Pts &P, int ntransf
 // Dynamic LDS bytes the SM kernels need for these bins and subproblem size.
 size_t sm_lds_bytes(const Geom &g, int prec, bool interp, int msub);
 // Single-precision SM spreading keeps up to this many gathered strengths of
-// a subproblem in LDS, so the strengths are read from HBM once (fewer in 3D,
-// where bins hold fewer points and LDS occupancy matters more).
+// a subproblem in LDS, so the strengths are read from HBM once.  Bins are
+// accepted by this size; the launch may stage fewer (2D, w = 7 and 8) or keep
+// them in registers (3D plans).
 // (2D: 2816 keeps the default 32 x 32 tile plus the stage within 40 KB, four
 // workgroups per CU; a uniform 2D bin of the default workload holds about
 // 2440 points, and the few strengths past the stage are gathered again:

@@ -1,8 +1,9 @@
 // Host side of libmnufft: plan construction, parameter choice, correction
-// factors, the rocFFT fine-grid transform and the C ABI declared in
+// factors, the fine-grid transform and the C ABI declared in
 // include/mnufft.h.  The stages follow the paper's plan / setup / execute /
 // destroy interface (Sec. I-A) and three-step algorithm (Sec. II); every
-// step on the device runs in the kernels of kernels_*.hip except the FFT.
+// step on the device runs in the library's kernels except the FFT of lines
+// too long for a workgroup (rocFFT).
 #include "../../include/mnufft.h"
 #include "host_common.h"
 #include "internal.h"
@@ -70,9 +71,9 @@ struct mnufft_plan_s {
     uint16_t *hslot_proc = nullptr;
     int32_t *binstart = nullptr, *subcount = nullptr, *sub = nullptr, *nsub = nullptr;
     int nsub_max = 0, nsub_cap = 0;
-    // The kernels cut bins into subproblems of msub_k points, msub unless the
-    // library chose it (see kernel_msub); nsub_k is their list's bound.
-    bool msub_given = false;
+    // The kernels cut bins into subproblems of msub_k points, msub or fewer
+    // (see kernel_msub); nsub_k is their list's bound.
+    bool noisy = false;  // see noisy_factors
     int msub_k = 0, nsub_k = 0;
     int32_t *publist = nullptr;  // get_subproblems' list of msub and its bin offsets
     size_t publist_bytes = 0;
@@ -194,8 +195,7 @@ void free_points(mnufft_plan p)
 // where the sorted order does as well.
 bool balanced(const mnufft_plan_s *p) { return p->method == MNUFFT_METHOD_SM && p->dim >= 2; }
 
-// Points per subproblem of the kernels for M points, where msub is the
-// library's default: one block works on a subproblem, and a full one of 4096
+// Points per subproblem of the kernels for M points, at most msub: one block works on a subproblem, and a full one of 4096
 // points takes about 100 us whatever the rest, so sets that fill the GPU less
 // than that are cut finer, into about 2048 when every bin is full, 8 per CU
 // (131072 radial points on 512^2: type 1 + adjoint of 8 vectors 224 -> 184
@@ -205,7 +205,13 @@ bool balanced(const mnufft_plan_s *p) { return p->method == MNUFFT_METHOD_SM && 
 // kernels share their work by a queue and want full groups.
 int kernel_msub(const mnufft_plan_s *p, int64_t M)
 {
-    if (p->msub_given || p->method != MNUFFT_METHOD_SM || p->mf) return p->msub;
+    if (p->method != MNUFFT_METHOD_SM || p->mf) return p->msub;
+    if (p->prec == MNUFFT_F32 && p->sigma < 2.0) return p->msub;  // see noisy_factors
+    // (a full subproblem's points share few cells of the smallest 3D grids, and
+    // the spreading quantum, up to 2e-5 of the results there, follows its cut)
+    if (p->prec == MNUFFT_F32 && p->dim == 3 &&
+        (int64_t)p->g.n[0] * p->g.n[1] * p->g.n[2] < 65536)
+        return p->msub;
     const int64_t mean = M / p->g.nbins;
     const int64_t k = std::max<int64_t>({512, (M + 2047) / 2048, mean + mean / 4 + 64});
     return (int)std::min<int64_t>((k + 63) / 64 * 64, p->msub);
@@ -216,7 +222,7 @@ int64_t subproblem_bound(const mnufft_plan_s *p, int64_t M)
 {
     const int64_t full = (M + p->msub - 1) / p->msub;
     // (kernel_msub of any count up to M: at most 2048, and one per 512 points)
-    const int64_t fine = p->msub_given ? 0 : std::min<int64_t>(2048, (M + 511) / 512);
+    const int64_t fine = std::min<int64_t>(2048, (M + 511) / 512);
     return p->g.nbins + std::max(full, fine);
 }
 
@@ -255,7 +261,7 @@ int alloc_points(mnufft_plan p, int64_t M)
         if ((rc = dalloc(p, &p->scratch, p->scratch_bytes))) return rc;
         if ((rc = dalloc(p, (void **)&p->mergelist, (size_t)std::max(p->nsub_cap, 1) * 4)))
             return rc;
-        if (!p->msub_given && !p->mf) {
+        if (!p->mf) {
             const size_t most = (size_t)(p->g.nbins + (M + p->msub - 1) / p->msub);
             p->publist_bytes = (4 * most + (size_t)p->g.nbins + 2) * 4;
             if ((rc = dalloc(p, (void **)&p->publist, p->publist_bytes))) return rc;
@@ -577,7 +583,6 @@ int replan(mnufft_plan p, const mnufft_opts &c)
     o.msub = c.msub;
     o.tune = MNUFFT_TUNE_OFF;
     p->msub = o.msub > 0 ? o.msub : 4096;
-    p->msub_given = o.msub > 0;
     int64_t nf[3] = {p->g.n[0], p->g.n[1], p->g.n[2]};
     int rc = plan_geometry(p, nf, p->g.w, p->g.beta, o);
     if (!rc) rc = plan_bins_device(p);
@@ -633,7 +638,6 @@ mnufft_plan new_plan(int type, int dim, const int64_t *nmodes, int iflag, int64_
     p->validate = o.validate_pts;
     p->stream = (hipStream_t)o.stream;
     p->msub = o.msub > 0 ? o.msub : 4096;
-    p->msub_given = o.msub > 0;
     p->sigma = sigma;
     p->opts = o;
     for (int d = 0; d < 3; ++d) p->N[d] = (nmodes && d < dim) ? nmodes[d] : 1;
@@ -700,6 +704,7 @@ int plan_geometry(mnufft_plan p, const int64_t nf[3], int w, double beta, const 
         p->method = o.method;
     if (p->method == MNUFFT_METHOD_SM && lds > kLdsMax) return MNUFFT_ERR_ARG;
     p->mf = p->method == MNUFFT_METHOD_SM ? mn::mf_span(g, p->prec, p->msub) : 0;
+    p->noisy = mn::host::noisy_factors(p->prec, g.w, g.beta, p->sigma, p->dim);
     return MNUFFT_OK;
 }
 
@@ -750,7 +755,7 @@ int plan_device(mnufft_plan p, bool with_fft)
             p->owntab = *ptr;
             return r;
         };
-        if (!rc) rc = p->own.make(dim, p->N, g.n, p->ntransf, p->prec, p->pfac, alloc, p->stream);
+        if (!rc && !p->noisy) rc = p->own.make(dim, p->N, g.n, p->ntransf, p->prec, p->pfac, alloc, p->stream);
         if (!rc) rc = make_fft(p, p->type, p->iflag);
     }
     // the tables filled above serve whatever stream the plan is moved to

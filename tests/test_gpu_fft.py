@@ -99,3 +99,20 @@ def test_batch_passes_match_plans(typ):
         err = torch.linalg.norm(got - want) / torch.linalg.norm(want)
         assert err <= 2 * _tol(torch.complex64, 4 * k), (md, float(err))
         at, kat = at + m, kat + k
+
+
+@pytest.mark.parametrize("sigma,eps,own", [(2.0, 1e-6, True), (1.25, 1e-4, True),
+                                           (1.25, 1e-6, False)])
+def test_plans_that_amplify_rounding_keep_the_library_fft(sigma, eps, own):
+    """3D single precision at 43 and 1550 times amplified rounding: the own
+    passes apply the factors themselves, the library's FFT needs the kernel."""
+    modes, M = (20, 18, 16), 2000
+    pts = [torch.from_numpy(a.astype(np.float32)).cuda()
+           for a in workloads.uniform(M, 3, seed=11)]
+    f = torch.from_numpy(workloads.strengths(modes[::-1], seed=12).astype(np.complex64)).cuda()
+    with Plan(2, modes, 1, eps, -1, upsampfac=sigma) as p:
+        p.setpts(*pts)
+        p.set_timing(True)
+        p.execute(f)
+        _, launches = p.timing()["precorrect"]
+    assert (launches == 0) == own

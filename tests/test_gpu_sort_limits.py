@@ -45,7 +45,7 @@ def test_permutation_3d_wide_tiles(M):
 
 @pytest.mark.parametrize("M", [600, 300000, 2048 * 576 + 2047])
 def test_kernels_cut_crowded_bins_finer(M):
-    """Without an msub the kernels cut bins finer than the list they report;
+    """The kernels cut bins finer than the list they report;
     all points in one bin, in more pieces than one merge group."""
     import torch
     import workloads
