@@ -39,7 +39,7 @@ extern "C" {
 #define MNUFFT_ERR_ARG          (-1)  /* invalid argument; nothing was done */
 #define MNUFFT_ERR_ALLOC        (-2)  /* device or host allocation failed */
 #define MNUFFT_ERR_HIP          (-3)  /* a HIP runtime call failed */
-#define MNUFFT_ERR_FFT          (-4)  /* rocFFT plan creation or execution failed */
+#define MNUFFT_ERR_FFT          (-4)  /* rocFFT (lines too long for the own FFT) failed */
 #define MNUFFT_ERR_STATE        (-5)  /* call out of order (e.g. execute before setpts) */
 #define MNUFFT_ERR_PTS          (-6)  /* a point is non-finite or outside [-3pi, 3pi) (validate_pts) */
 #define MNUFFT_ERR_UNSUPPORTED  (-7)  /* valid request the library does not provide */
@@ -134,8 +134,8 @@ int mnufft_default_opts(mnufft_opts *o);
  *   opts     NULL for defaults
  *   out      receives the plan handle, owned by the caller until mnufft_destroy
  * Picks w, beta and the fine grid, computes the correction factors
- * p_k = (2/w) / phi_hat(alpha k) (Sec. II-A step 3) once, creates the rocFFT
- * plan and allocates the fine grid.  All arguments are validated before any
+ * p_k = (2/w) / phi_hat(alpha k) (Sec. II-A step 3) once, makes the FFT
+ * passes and allocates the fine grid.  All arguments are validated before any
  * device call.  Returns MNUFFT_WARN_EPS_CLAMPED if eps needs w > 8 in F32 or
  * w > 16 in F64 (the plan then runs at the capped width).  Errors: ERR_ARG,
  * ERR_ALLOC, ERR_HIP, ERR_FFT; *out is NULL on error. */
@@ -276,7 +276,11 @@ int mnufft_destroy(mnufft_plan p);
 #define MNUFFT_STAGE_SETPTS     0  /* the whole bin-sort of mnufft_setpts */
 #define MNUFFT_STAGE_ZERO       1  /* clearing the fine grid before spreading */
 #define MNUFFT_STAGE_SPREAD     2  /* type 1 step 1 (Sec. II-A); for SM the LDS tile kernel */
-#define MNUFFT_STAGE_FFT        3  /* rocFFT of the fine grid (either sign) */
+#define MNUFFT_STAGE_FFT        3  /* FFT of the fine grid (either sign); where the library's own
+                                      passes do it (every dimension whose lines fit a
+                                      workgroup), truncation, padding and the correction
+                                      factors are part of them and DECONV / PRECORRECT
+                                      stay zero */
 #define MNUFFT_STAGE_DECONV     4  /* type 1 step 3 (Sec. II-A) */
 #define MNUFFT_STAGE_PRECORRECT 5  /* type 2 step 1 (Sec. II-B) */
 #define MNUFFT_STAGE_INTERP     6  /* type 2 step 3 (Sec. II-B) */
