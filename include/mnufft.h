@@ -486,9 +486,9 @@ int mnufft_batch_select(int type, int dim, int ntr, const int64_t *nmodes, const
  * tolerance and precision, each with its own modes and points, as one
  * workload: one bin-sort over all points (the transforms' bins numbered
  * consecutively), one subproblem list, and one persistent launch each for
- * spreading, the add-back of the padded bins, interpolation and the
- * corrections (method SM, Sec. III-A); only the fine-grid FFTs run per
- * transform.  Inputs and outputs are concatenated in transform order. */
+ * spreading, the add-back of the padded bins, interpolation and each pass of
+ * the FFT with the corrections (method SM, Sec. III-A); the FFTs run per
+ * transform only where a dimension is too long for the library's own passes.  Inputs and outputs are concatenated in transform order. */
 typedef struct mnufft_batch_s *mnufft_batch;
 
 /* Create a batch.
