@@ -327,7 +327,8 @@ int mnufft_batch_makeplan(int type, int dim, int ntr, const int64_t *nmodes, con
     // points each: 1266 -> 815; 4 such grids 197 -> 109 (twice kMinBins: 116,
     // four times: 124); small radial sets at 16 grids of 48^2 to 256^2, whose
     // crowded bins grow, 1016 -> 1046.  (3D bins stay the plan's: larger ones
-    // may not fit in LDS.)
+    // may not fit in LDS.)  Windows and kernel values stay those of the plan's
+    // bins (fix_coord).
     const bool noisy = mn::host::noisy_factors(prec, w, beta, sigma, dim);
     const bool share_bins = dim == 2 && ntr > 1 && (prec != MNUFFT_F32 || sigma >= 2.0);
     int batch_m[2] = {32, 32};
@@ -357,7 +358,18 @@ int mnufft_batch_makeplan(int type, int dim, int ntr, const int64_t *nmodes, con
             nf[d] = d < dim ? mn::host::fine_size(nmodes[3 * t + d], w, sigma) : 1;
         int defm[3];
         mn::host::default_bins(dim, nf, defm);
-        for (int d = 0; d < 2 && share_bins; ++d) defm[d] = batch_m[d];
+        // (a transform with an extent of its own keeps its plan's others: next to
+        // a given long side the batch's might not fit in LDS)
+        bool given = false;
+        for (int d = 0; d < dim; ++d)
+            given = given || o.binsize[d] > 0 || (binsize && binsize[3 * t + d] > 0);
+        for (int d = 0; d < 2 && share_bins && !given; ++d) {
+            if (prec == MNUFFT_F32) {
+                tg.own[d] = (int)std::min<int64_t>(defm[d], nf[d]);
+                tg.own_im[d] = 1.0 / (double)tg.own[d];
+            }
+            defm[d] = batch_m[d];
+        }
         for (int d = 0; d < 3; ++d) {
             const int64_t N = d < dim ? nmodes[3 * t + d] : 1;
             const int64_t n = nf[d];

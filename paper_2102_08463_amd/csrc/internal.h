@@ -31,6 +31,10 @@ struct TGeom {
     int bin_off, nbins;
     int pt_off, M;
     int msub;
+    // Shared 2D single precision bins: extents of the bins the transform's own
+    // plan would have (0: coordinates are relative to m, see Window)
+    int own[2];
+    double own_im[2];
     int p_off[3];    // offsets into the concatenated correction factors, per dimension
     int cov_off[3];  // offsets (entries) into the concatenated cover tables, per dimension
     int kmax[3];
@@ -111,6 +115,30 @@ __host__ __device__ inline int start_cell_rt(T u, int w)
 {
     const T v = u + (T)((w + 1) / 2);
     return (int)ceil(v - (T)(0.5 * w));
+}
+
+// Coordinates of a batch whose 2D bins are shared (TGeom::own).  A point's
+// window and kernel values follow fl(u + P), u its single precision coordinate
+// in a bin of the plan's own size; relative to a wider bin that sum has fewer
+// fractional bits, and a point next to the edge of a window then drops one
+// outermost tap for the opposite one (weight exp(-beta): 1e-3 at w = 3).  The
+// four bytes hold that sum instead, a multiple of 2^-23 (it is at least P >= 1),
+// plus the whole cells from the shared bin's start to the own bin's, in units
+// of 2^-23: with extents up to 32 and P <= 4 below 2^29.
+constexpr int kFixBits = 23;
+
+__host__ __device__ inline int fix_coord(float u, int pad, int cells)
+{
+    return (int)((u + (float)pad) * (float)(1 << kFixBits)) + cells * (1 << kFixBits);
+}
+
+// Start cell of that coordinate, as start_cell_rt, and first tap minus point
+// (exact, as the difference of the floats is).
+__host__ __device__ inline int fix_start(int q, int w, float &d)
+{
+    const int s = (q - w * (1 << (kFixBits - 1)) + (1 << kFixBits) - 1) >> kFixBits;
+    d = (float)(s * (1 << kFixBits) - q) * (1.0f / (float)(1 << kFixBits));
+    return s;
 }
 
 // Layout of the start-cell histogram of a tile with bin extents m: start

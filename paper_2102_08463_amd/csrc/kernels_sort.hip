@@ -73,11 +73,18 @@ __device__ __forceinline__ uint32_t point_key_of(const Geom &g, const T xc[3], c
 {
     uint32_t k = 0, stride = 1;
     Geom gg = g;
+    [[maybe_unused]] int own[2] = {0, 0};
+    [[maybe_unused]] double own_im[2] = {0, 0};
     if constexpr (BATCH) {
         const auto fld = [](const TGeom &a) { return a.pt_off; };
         const int t = cached ? find_cached(soff, T_, j) : find_transform(tg, T_, j, fld);
         gg = geom_of(g, tg[t]);
         k = (uint32_t)tg[t].bin_off;
+        if constexpr (std::is_same<T, float>::value)
+            for (int d = 0; d < 2; ++d) {
+                own[d] = tg[t].own[d];
+                own_im[d] = tg[t].own_im[d];
+            }
     }
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
@@ -92,6 +99,13 @@ __device__ __forceinline__ uint32_t point_key_of(const Geom &g, const T xc[3], c
         k += (uint32_t)b * stride;
         stride *= (uint32_t)gg.B[d];
         u[d] = (T)(gc - (double)b * (double)gg.m[d]);
+        if constexpr (BATCH && std::is_same<T, float>::value) {
+            if (d < 2 && own[d] > 0) {
+                const int c = (int)(((double)l + 0.5) * own_im[d]) * own[d];  // own bin's first cell
+                u[d] = __int_as_float(
+                    fix_coord((float)(gc - (double)c), gg.pad, c - b * gg.m[d]));
+            }
+        }
     }
     return k;
 }

@@ -110,6 +110,26 @@ __device__ __forceinline__ int taps(T v, T bk, T (&k)[W])
     return (int)s;
 }
 
+// The same of a batch point's coordinate u in a bin with halo P: as fixed point
+// with `fix` (fix_coord), else at u + P.
+template <int W>
+__device__ __forceinline__ int taps_batch(float u, bool fix, float bk, float (&k)[W])
+{
+    float d;
+    int s;
+    if (fix) {
+        s = fix_start(__float_as_int(u), W, d);
+    } else {
+        const float v = u + (float)((W + 1) / 2), f = ceil(v - (float)(0.5 * W));
+        s = (int)f;
+        d = f - v;
+    }
+    const float z0 = d * (float)(2.0 / W);
+#pragma unroll
+    for (int a = 0; a < W; ++a) k[a] = es_val(z0 + (float)a * (float)(2.0 / W), bk);
+    return s;
+}
+
 // First tap of a point at v, with z0 = 2 (first tap - v) / W; the weight of
 // tap a is es_val(z0 + 2a/W).  Used for the outermost dimension, whose taps
 // are produced inside a rolled loop.
@@ -685,13 +705,22 @@ k_spread_smp(Geom g, const int32_t *__restrict__ sub, const int32_t *__restrict_
     for (int q = q0 + (int)blockIdx.x; q < nsub; q += gridDim.x) {
         const int4 rec = reinterpret_cast<const int4 *>(sub)[q];
         int m1 = g.m[0], m2 = g.m[1], m3 = g.m[2];
+        [[maybe_unused]] bool fix = false;  // (2D batches: fixed-point coordinates)
         if constexpr (BATCH) {
             const TGeom &tt =
                 tg[bin_t[rec.x]];
             m1 = tt.m[0];
             m2 = tt.m[1];
             m3 = tt.m[2];
+            if constexpr (DIM == 2) fix = tt.own[0] > 0;
         }
+        const auto first = [&](float u) {
+            if constexpr (BATCH && DIM == 2) {
+                float d;
+                if (fix) return fix_start(__float_as_int(u), W, d);
+            }
+            return start_cell<float, W>(u);
+        };
         const int p1 = m1 + 2 * P, p2 = m2 + 2 * P;
         // this tile's own words (a batch's ts2 fits its largest bins)
         const int tsz = BATCH ? tile_words<DIM>(p1, p2, m3 + 2 * P) : ts2;
@@ -735,9 +764,8 @@ k_spread_smp(Geom g, const int32_t *__restrict__ sub, const int32_t *__restrict_
                 if (hslot) {
                     hs[k] = st ? (int)hslot[i] : 0;
                 } else if (st) {
-                    hs[k] = hist_slot<DIM>(hg, start_cell<float, W>(u0[i]),
-                                           start_cell<float, W>(u1[i]),
-                                           DIM == 3 ? start_cell<float, W>(u2[i]) : 0);
+                    hs[k] = hist_slot<DIM>(hg, first(u0[i]), first(u1[i]),
+                                           DIM == 3 ? first(u2[i]) : 0);
                 } else {
                     hs[k] = 0;
                 }
@@ -789,9 +817,8 @@ k_spread_smp(Geom g, const int32_t *__restrict__ sub, const int32_t *__restrict_
                 cv = cs[j];
             } else {
                 hs = hslot ? (int)hslot[i]
-                           : hist_slot<DIM>(hg, start_cell<float, W>(u0[i]),
-                                            start_cell<float, W>(u1[i]),
-                                            DIM == 3 ? start_cell<float, W>(u2[i]) : 0);
+                           : hist_slot<DIM>(hg, first(u0[i]), first(u1[i]),
+                                            DIM == 3 ? first(u2[i]) : 0);
                 cv = c[idx[i]];
             }
             atomicAdd(H + hs, entry(cv));
@@ -841,9 +868,14 @@ k_spread_smp(Geom g, const int32_t *__restrict__ sub, const int32_t *__restrict_
                 if constexpr (kHold == 0) ncv = strength(i + kThreads);
             }
             float kx[W], ky[W];
-            const int sx = taps<float, W>(x0 + (float)P, bk, kx);
-            int sy = 0;
-            if constexpr (DIM >= 2) sy = taps<float, W>(x1 + (float)P, bk, ky);
+            int sx, sy;
+            if constexpr (BATCH && DIM == 2) {
+                sx = taps_batch<W>(x0, fix, bk, kx);
+                sy = taps_batch<W>(x1, fix, bk, ky);
+            } else {
+                sx = taps<float, W>(x0 + (float)P, bk, kx);
+                sy = taps<float, W>(x1 + (float)P, bk, ky);
+            }
             const float cr0 = ldexpf(cv.x, sh), ci0 = ldexpf(cv.y, sh);
             // contributions are rounded to nearest (ties to even): truncation,
             // or ties away from zero, would bias the terms, and ties are
@@ -1336,12 +1368,15 @@ k_interp_sm(Geom g, const int32_t *__restrict__ sub, const int32_t *__restrict__
         int b = rec.x;
         Geom gg = g;
         const C *grid = grid_;
+        constexpr bool kFix = BATCH && DIM == 2 && std::is_same<T, float>::value;
+        [[maybe_unused]] bool fix = false;
         if constexpr (BATCH) {
             const TGeom &tt =
                 tg[bin_t[rec.x]];
             gg = geom_of(g, tt);
             grid = grid_ + tt.grid_off;
             b -= tt.bin_off;
+            if constexpr (kFix) fix = tt.own[0] > 0;
         }
         const int p1 = gg.m[0] + 2 * P, p2 = DIM >= 2 ? gg.m[1] + 2 * P : 1;
         const int p3 = DIM == 3 ? gg.m[2] + 2 * P : 1;
@@ -1411,9 +1446,14 @@ k_interp_sm(Geom g, const int32_t *__restrict__ sub, const int32_t *__restrict__
             const int pj = ap[k];
             load_round(r0 + k + kAhead, k);
             T kx[W], ky[W];
-            const int sx = taps<T, W>(x0 + (T)P, bk, kx);
-            int sy = 0;
-            if constexpr (DIM >= 2) sy = taps<T, W>(x1 + (T)P, bk, ky);
+            int sx, sy = 0;
+            if constexpr (kFix) {
+                sx = taps_batch<W>(x0, fix, bk, kx);
+                sy = taps_batch<W>(x1, fix, bk, ky);
+            } else {
+                sx = taps<T, W>(x0 + (T)P, bk, kx);
+                if constexpr (DIM >= 2) sy = taps<T, W>(x1 + (T)P, bk, ky);
+            }
             T ar = 0, ai = 0;
             if constexpr (DIM == 1) {
                 const C *row = tile + sx;
