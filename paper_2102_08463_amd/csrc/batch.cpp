@@ -558,7 +558,8 @@ int mnufft_batch_setpts(mnufft_batch b, const void *x, const void *y, const void
         const mn::KeySrc ks{b->g, x, y, z, b->flag, b->d_geo, b->T, mn::PtMap{}};
         uint32_t *sk = nullptr, *sv = nullptr;
         if (mn::radix_sort(M, mn::host::bits_for(b->nbins), b->prec, b->dim, b->keyA, b->valA,
-                           b->keyB, b->valB, pays.data(), b->hist, b->partials, &sk, &sv, s, &ks))
+                           b->keyB, b->valB, pays.data(), b->hist, mn::radix_hist_elems(M),
+                           b->partials, &sk, &sv, s, &ks))
             return MNUFFT_ERR_HIP;
         b->skey = sk;
         b->perm = reinterpret_cast<int32_t *>(sv);

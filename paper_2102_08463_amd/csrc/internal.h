@@ -224,7 +224,7 @@ struct Pts {
 };
 
 // ---- bin sort (kernels_sort.hip) ------------------------------------------
-// Scratch needed by the radix sort for M keys.
+// Scratch needed by the radix sort for up to M keys.
 size_t radix_hist_elems(int M);
 size_t scan_partial_elems(size_t n);
 
@@ -273,11 +273,12 @@ int radix_passes(int bits);
 // dim payload planes of the plan precision; pass p reads pays[p].in and
 // writes pays[p].out.  Returns in *keys_out / *vals_out the buffers (among
 // the two ping-pong pairs) that hold the sorted keys and the permutation.
-// With src, pass 0 takes keys and payload from the points (keysA and
+// hist holds hist_elems counts and partials those of a scan over them; an error
+// when they are too few for M.  With src, pass 0 takes keys and payload from the points (keysA and
 // pays[0].in are not read).
 hipError_t radix_sort(int M, int bits, int prec, int dim, uint32_t *keysA, uint32_t *valsA,
                       uint32_t *keysB, uint32_t *valsB, const Payload *pays, uint32_t *hist,
-                      uint32_t *partials, uint32_t **keys_out, uint32_t **vals_out, hipStream_t s,
+                      size_t hist_elems, uint32_t *partials, uint32_t **keys_out, uint32_t **vals_out, hipStream_t s,
                       const KeySrc *src = nullptr);
 
 // binstart[b] = first sorted position with key >= b, b = 0..nbins.

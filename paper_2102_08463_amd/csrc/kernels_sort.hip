@@ -652,9 +652,13 @@ inline int nblocks(int64_t n, int t) { return (int)((n + t - 1) / t); }
 
 }  // namespace
 
+// (A plan's buffers serve smaller point sets too, and the count does not grow with
+// M: 2^20 keys are 1024 small tiles, 2^20 + 1 are 257 large ones.)
 size_t radix_hist_elems(int M)
 {
-    return (size_t)256 * hist_pitch(std::max(1, nblocks(M, tile_of(M))));
+    const int small = std::min(M, kSmallKeys);
+    return (size_t)256 * std::max(hist_pitch(std::max(1, nblocks(small, tile_of(small)))),
+                                  hist_pitch(std::max(1, nblocks(M, tile_of(M)))));
 }
 
 size_t scan_partial_elems(size_t n) { return (n + kScanChunk - 1) / kScanChunk + 1; }
@@ -698,7 +702,7 @@ int radix_passes(int bits) { return std::max(1, (bits + 7) / 8); }
 
 hipError_t radix_sort(int M, int bits, int prec, int dim, uint32_t *keysA, uint32_t *valsA,
                       uint32_t *keysB, uint32_t *valsB, const Payload *pays, uint32_t *hist,
-                      uint32_t *partials, uint32_t **keys_out, uint32_t **vals_out, hipStream_t s,
+                      size_t hist_elems, uint32_t *partials, uint32_t **keys_out, uint32_t **vals_out, hipStream_t s,
                       const KeySrc *src)
 {
     // Keys start in keysA with implicit values 0..M-1; each pass moves the
@@ -717,6 +721,7 @@ hipError_t radix_sort(int M, int bits, int prec, int dim, uint32_t *keysA, uint3
             const int from = (p == 0 && src) ? (src->tg ? 2 : 1) : 0;
             const int tile = tile_of(M, !from && dim == 3 && prec == 0);
             const int nblk = std::max(1, nblocks(M, tile)), pitch = hist_pitch(nblk);
+            if ((size_t)256 * pitch > hist_elems) return hipErrorInvalidValue;
             const bool sums = nblk <= kFusedBlocks;  // the scatter sums the counts itself
             const KeySrc ks = src ? *src : KeySrc{};
             const uint32_t *vin = p == 0 ? nullptr : (const uint32_t *)vb[cur];

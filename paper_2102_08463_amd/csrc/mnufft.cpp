@@ -536,7 +536,7 @@ int enqueue_setpts(mnufft_plan p, int64_t M, const void *x, const void *y, const
     const mn::KeySrc ks{g, x, y, z, p->flag, nullptr, 1, p->ptmap};
     uint32_t *sk = nullptr, *sv = nullptr;
     MN_HIP(mn::radix_sort((int)M, bits_for(g.nbins), p->prec, p->dim, p->keyA, p->valA, p->keyB,
-                          p->valB, pays.data(), p->hist, p->partials, &sk, &sv, s,
+                          p->valB, pays.data(), p->hist, p->hist_cap, p->partials, &sk, &sv, s,
                           gm ? nullptr : &ks));
     p->skey = sk;
     p->perm = reinterpret_cast<int32_t *>(sv);
