@@ -36,6 +36,7 @@ struct mnufft_batch_s {
     double eps = 1e-6;
     int device = -1;
     hipStream_t stream = nullptr;
+    mn::host::InUse use;  // where work on the batch's buffers may be pending
     size_t rsz = 4;
     mn::Geom g{};  // shared fields; m holds the largest bin extents of the batch
     std::vector<mn::TGeom> geo;
@@ -259,8 +260,10 @@ int mnufft_batch_destroy(mnufft_batch b)
     }
     if (b->fork) (void)hipEventDestroy(b->fork);
     b->tm.destroy();
-    if (rc != MNUFFT_OK) (void)hipDeviceSynchronize();  // nothing in use goes to the pool
-    for (void *p : b->allocs) mn::host::pool_free(p);
+    if (rc != MNUFFT_OK) b->use.elsewhere = true;  // (a wait above failed)
+    const bool idle = b->use.wait(b->stream);
+    if (!idle) rc = MNUFFT_ERR_HIP;
+    for (void *p : b->allocs) mn::host::pool_free(p, idle);
     delete b;
     return rc;
 }
@@ -469,6 +472,7 @@ int mnufft_batch_makeplan(int type, int dim, int ntr, const int64_t *nmodes, con
     // ---- device state ----
     int rc = MNUFFT_OK;
     if (b->device >= 0 && hipSetDevice(b->device) != hipSuccess) rc = MNUFFT_ERR_HIP;
+    if (!rc && hipGetDevice(&b->use.device) != hipSuccess) rc = MNUFFT_ERR_HIP;
     if (!rc) rc = balloc(b, (void **)&b->d_geo, sizeof(mn::TGeom) * ntr);
     if (!rc) rc = upload(b->d_geo, b->geo.data(), sizeof(mn::TGeom) * ntr);
     if (!rc) {
@@ -542,6 +546,7 @@ int mnufft_batch_setpts(mnufft_batch b, const void *x, const void *y, const void
     if (b->device >= 0 && hipSetDevice(b->device) != hipSuccess) return MNUFFT_ERR_HIP;
     b->pts_set = false;
     hipStream_t s = b->stream;
+    b->use.note(s);
     const int M = (int)b->Mtot;
     {
         StageTimer tm(b->tm, MNUFFT_STAGE_SETPTS, s);
@@ -580,6 +585,7 @@ int mnufft_batch_execute(mnufft_batch b, void *c, void *f)
     if (!f || (b->Mtot > 0 && !c)) return MNUFFT_ERR_ARG;
     if (b->device >= 0 && hipSetDevice(b->device) != hipSuccess) return MNUFFT_ERR_HIP;
     hipStream_t s = b->stream;
+    b->use.note(s);
     const mn::Pts P = batch_points(b);
     int rc;
     if (b->type == 1) {

@@ -119,6 +119,32 @@ void default_bins(int dim, const int64_t n[3], int m[3])
     }
 }
 
+void InUse::note(hipStream_t s)
+{
+    if (elsewhere || !s) return;  // (the null stream cannot be captured)
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (s == hipStreamPerThread) {
+        elsewhere = true;  // another stream in another thread
+    } else if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        elsewhere = true;
+    } else if (st != hipStreamCaptureStatusNone) {
+        elsewhere = true;
+    }
+}
+
+bool InUse::wait(hipStream_t s) const
+{
+    // (the null stream and the device's wait go to the current device)
+    int cur = -1;
+    const bool move = device >= 0 && hipGetDevice(&cur) == hipSuccess && cur != device;
+    if (move && hipSetDevice(device) != hipSuccess) return false;
+    const bool ok = (!elsewhere && hipStreamSynchronize(s) == hipSuccess) ||
+                    hipDeviceSynchronize() == hipSuccess;
+    if (move) (void)hipSetDevice(cur);
+    return ok;
+}
+
 int bits_for(int64_t nbins)
 {
     int b = 0;

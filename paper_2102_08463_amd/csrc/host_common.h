@@ -69,10 +69,23 @@ int bits_for(int64_t nbins);
 // periodic wrapping; rows padded to the largest count kmax with bin -1.
 void cover_table(int n, int m, int B, int P, std::vector<int2> &tab, int &kmax);
 
-// Device memory from and to the pool (pool.cpp), on the current device.  The
-// device must no longer use a block that is freed.
+// Device memory from and to the pool (pool.cpp), on the current device.  `idle`:
+// the device is known not to use the block any more; others are freed, which
+// waits for their users.
 hipError_t pool_alloc(void **ptr, size_t bytes);
-void pool_free(void *ptr);
+void pool_free(void *ptr, bool idle);
+
+// Where the work on an owner's buffers may still be pending: on its stream, or,
+// when a call was captured there (a graph may be replayed anywhere) or the
+// stream has been changed, on any stream of its device.
+struct InUse {
+    int device = -1;         // the owner's
+    bool elsewhere = false;
+    // To be called before work is enqueued on s.
+    void note(hipStream_t s);
+    // Waits for that work; false when it could not.
+    bool wait(hipStream_t s) const;
+};
 
 // Per-stage HIP-event timers on one stream.
 struct Timers {

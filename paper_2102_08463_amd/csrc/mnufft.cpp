@@ -49,7 +49,8 @@ struct mnufft_plan_s {
     int device = -1;
     int validate = 0;
     hipStream_t stream = nullptr;
-    bool moved = false;         // work may also be pending on an earlier stream
+    mn::host::InUse use;        // where work on the plan's buffers may be pending
+    bool idle = true;           // it has been waited for (what is freed may be reused)
     size_t rsz = 4;             // bytes per real of the plan precision
     size_t grid_elems = 0;      // complex cells per transform
     void *grid = nullptr;       // ntransf fine grids
@@ -137,22 +138,27 @@ int dalloc(mnufft_plan p, void **ptr, size_t bytes)
 // back to the pool.
 int quiesce(mnufft_plan p)
 {
-    if (!p->moved && hipStreamSynchronize(p->stream) == hipSuccess) return MNUFFT_OK;
-    return hipDeviceSynchronize() == hipSuccess ? MNUFFT_OK : MNUFFT_ERR_HIP;
+    p->idle = p->use.wait(p->stream);
+    return p->idle ? MNUFFT_OK : MNUFFT_ERR_HIP;
 }
 
 void dfree(mnufft_plan p, void **ptr, size_t bytes)
 {
     if (*ptr) {
-        mn::host::pool_free(*ptr);
+        mn::host::pool_free(*ptr, p->idle);
         p->devbytes -= (int64_t)bytes;
     }
     *ptr = nullptr;
 }
 
+// To be called by every entry point before it enqueues work.
 int use_device(mnufft_plan p)
 {
     if (p->device >= 0) MN_HIP(hipSetDevice(p->device));
+    if (p->use.device < 0) MN_HIP(hipGetDevice(&p->use.device));
+    p->use.note(p->stream);
+    for (mnufft_plan q : {p->t3spr, p->t3inner})
+        if (q) q->use.elsewhere = q->use.elsewhere || p->use.elsewhere;
     return MNUFFT_OK;
 }
 
@@ -1301,7 +1307,7 @@ int mnufft_set_stream(mnufft_plan p, void *stream)
     }
     for (mnufft_plan q : {p, p->t3spr, p->t3inner}) {
         if (!q) continue;
-        q->moved = q->moved || q->stream != (hipStream_t)stream;
+        q->use.elsewhere = q->use.elsewhere || q->stream != (hipStream_t)stream;
         q->stream = (hipStream_t)stream;
         q->opts.stream = stream;
     }

@@ -119,7 +119,7 @@ hipError_t pool_alloc(void **ptr, size_t bytes)
     }
 }
 
-void pool_free(void *ptr)
+void pool_free(void *ptr, bool idle)
 {
     if (!ptr) return;
     try {
@@ -129,7 +129,7 @@ void pool_free(void *ptr)
         if (it == p.live.end()) return;
         Block b = it->second;
         p.live.erase(it);
-        if (b.bytes > kKeepBytes / 2) {
+        if (!idle || b.bytes > kKeepBytes / 2) {
             (void)hipFree(ptr);
             return;
         }

@@ -66,8 +66,21 @@ int hipFree(void *p)
 }
 int hipHostMalloc(void **p, size_t n, unsigned f) { (void)f; *p = calloc(1, n); return kOk; }
 int hipHostFree(void *p) { free(p); return kOk; }
-// device to host gives zeros
-int hipMemcpy(void *d, const void *s, size_t n, int kind) { (void)s; if (kind == 2) memset(d, 0, n); return kOk; }
+// device to host gives zeros; type 3 bounds (18 doubles: least, largest and a flag
+// per dimension and set) the ones set here
+static double bounds;
+void fake_bounds(double b) { bounds = b; }
+int hipMemcpy(void *d, const void *s, size_t n, int kind)
+{
+    (void)s;
+    if (kind != 2) return kOk;
+    memset(d, 0, n);
+    for (int k = 0; n == 18 * 8 && k < 6; ++k) {
+        ((double *)d)[3 * k] = -bounds;
+        ((double *)d)[3 * k + 1] = bounds;
+    }
+    return kOk;
+}
 int hipMemcpyAsync(void *d, const void *s, size_t n, int kind, void *st) { (void)st; return hipMemcpy(d, s, n, kind); }
 int hipGetSymbolAddress(void **p, const void *s) { (void)s; return hipMalloc(p, 1 << 20); }
 
@@ -77,8 +90,10 @@ void fake_capture(void *stream) { capturing = stream; }
 int hipGetDevice(int *d) { *d = device; return kOk; }
 int hipSetDevice(int d) { device = d; return kOk; }
 int hipGetLastError(void) { return kOk; }
-int hipDeviceSynchronize(void) { ++counts[C_DEVICE_SYNC]; counts[C_SYNC_DEV] = device; return kOk; }
-int hipStreamSynchronize(void *s) { (void)s; ++counts[C_STREAM_SYNC]; counts[C_SYNC_DEV] = device; return kOk; }
+static int failing;
+void fake_fail_waits(int on) { failing = on; }
+int hipDeviceSynchronize(void) { ++counts[C_DEVICE_SYNC]; counts[C_SYNC_DEV] = device; return failing; }
+int hipStreamSynchronize(void *s) { (void)s; ++counts[C_STREAM_SYNC]; counts[C_SYNC_DEV] = device; return failing; }
 int hipStreamIsCapturing(void *s, int *st) { *st = s && s == capturing; return kOk; }
 int hipStreamCreateWithFlags(void **s, unsigned f) { (void)f; *s = malloc(1); return kOk; }
 int hipStreamDestroy(void *s) { free(s); return kOk; }
