@@ -264,9 +264,18 @@ int mnufft_set_stream(mnufft_plan p, void *stream);
 /* Describe the plan (host memory).  Errors: ERR_ARG. */
 int mnufft_get_info(mnufft_plan p, mnufft_info *info);
 
-/* Synchronise the plan's stream, free everything the plan owns and the plan
- * itself.  NULL is accepted and ignored.  Errors: ERR_HIP. */
+/* Synchronise the plan's stream (the device, once the plan has been moved to
+ * another stream or a call of it captured into a graph), free everything the
+ * plan owns and the plan itself.  NULL is accepted and ignored.  The library keeps up to 1 GiB
+ * per device of the memory of destroyed plans and batches for the next ones;
+ * what is older than ten seconds goes back to the system at the next call that
+ * allocates or frees, all of it when an allocation of the library fails, and
+ * on mnufft_release_memory.  Errors: ERR_HIP. */
 int mnufft_destroy(mnufft_plan p);
+
+/* Give all memory kept from destroyed plans and batches back to the system,
+ * on every device.  Errors: ERR_HIP. */
+int mnufft_release_memory(void);
 
 /* Stage timers.  When enabled, the library brackets each stage it enqueues
  * with a pair of HIP events on the plan's stream, so the figures are device

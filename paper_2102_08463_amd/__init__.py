@@ -9,4 +9,11 @@ from .plan import Plan, nufft_type1, nufft_type2, nufft_type3  # noqa: F401
 from .batch import Batch  # noqa: F401
 from . import lib  # noqa: F401
 
-__all__ = ["Plan", "Batch", "nufft_type1", "nufft_type2", "nufft_type3", "lib"]
+
+def release_memory():
+    """Give the device memory kept from destroyed plans and batches (at most 1 GiB
+    per device) back to the system."""
+    lib.check(lib.load().mnufft_release_memory(), "mnufft_release_memory")
+
+
+__all__ = ["release_memory", "Plan", "Batch", "nufft_type1", "nufft_type2", "nufft_type3", "lib"]

@@ -4,8 +4,8 @@
 // 4.5 ms and making one 0.9 ms, several times the work of a differentiable
 // transform, which makes a plan per call.  Freed blocks are therefore kept
 // for the next plan: at most kKeepBytes per device (oldest returned first),
-// none longer than kKeepSeconds at the next call, all of them when an
-// allocation fails.  A block enters the pool only when the device no longer
+// none longer than kKeepSeconds at the next allocation or free, all of them
+// when an allocation fails or mnufft_release_memory asks.  A block enters the pool only when the device no longer
 // uses it (its owner has waited), so any stream and thread may take it.
 #include "host_common.h"
 
@@ -35,6 +35,17 @@ struct Pool {
     std::unordered_map<void *, Block> live;
     std::vector<Block> idle;  // oldest first
 
+    static bool past(const Block &b, Clock::time_point now)
+    {
+        return std::chrono::duration<double>(now - b.since).count() > kKeepSeconds;
+    }
+
+    // Returns blocks past their time, when there are any.
+    void age()
+    {
+        if (!idle.empty() && past(idle.front(), Clock::now())) trim(-1, SIZE_MAX);
+    }
+
     // Returns idle blocks of dev (all devices if negative) to the system:
     // those past their time, then the oldest until `keep` bytes remain.
     void trim(int dev, size_t keep)
@@ -46,8 +57,7 @@ struct Pool {
         size_t n = 0;
         for (const Block &b : idle) {
             const bool mine = dev < 0 || b.dev == dev;
-            const bool old = std::chrono::duration<double>(now - b.since).count() > kKeepSeconds;
-            if (old || (mine && held > keep)) {
+            if (past(b, now) || (mine && held > keep)) {
                 if (mine) held -= b.bytes;
                 (void)hipFree(b.ptr);
             } else {
@@ -93,8 +103,10 @@ hipError_t pool_alloc(void **ptr, size_t bytes)
             p.live.emplace(b.ptr, b);
             p.idle.erase(p.idle.begin() + i);
             *ptr = b.ptr;
+            p.age();
             return hipSuccess;
         }
+        p.age();
         e = hipMalloc(ptr, size);
         if (e == hipErrorOutOfMemory && !p.idle.empty()) {
             (void)hipGetLastError();
@@ -147,3 +159,15 @@ void pool_free(void *ptr, bool idle)
 
 }  // namespace host
 }  // namespace mn
+
+extern "C" int mnufft_release_memory(void)
+{
+    try {
+        mn::host::Pool &p = mn::host::pool();
+        std::lock_guard<std::mutex> lock(p.m);
+        p.trim(-1, 0);
+    } catch (...) {
+        return MNUFFT_ERR_HIP;
+    }
+    return MNUFFT_OK;
+}

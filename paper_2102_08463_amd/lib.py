@@ -27,7 +27,8 @@ EXPORTS = (
     "mnufft_execute_sorted",
     "mnufft_execute_adjoint", "mnufft_interp_grad", "mnufft_spread", "mnufft_interp",
     "mnufft_get_sort",
-    "mnufft_get_subproblems", "mnufft_get_info", "mnufft_destroy", "mnufft_strerror",
+    "mnufft_get_subproblems", "mnufft_get_info", "mnufft_destroy", "mnufft_release_memory",
+    "mnufft_strerror",
     "mnufft_choose_params", "mnufft_choose_params_sigma", "mnufft_correction_factors",
     "mnufft_type3_grid",
     "mnufft_set_timing", "mnufft_get_timing", "mnufft_set_stream",

@@ -84,6 +84,11 @@ int hipMemcpy(void *d, const void *s, size_t n, int kind)
 int hipMemcpyAsync(void *d, const void *s, size_t n, int kind, void *st) { (void)st; return hipMemcpy(d, s, n, kind); }
 int hipGetSymbolAddress(void **p, const void *s) { (void)s; return hipMalloc(p, 1 << 20); }
 
+// std::chrono::steady_clock::now: the time that the test sets
+static long long clock_ns;
+void fake_time(double seconds) { clock_ns = (long long)(seconds * 1e9); }
+long long _ZNSt6chrono3_V212steady_clock3nowEv(void) { return clock_ns; }
+
 // ---- devices, streams, events --------------------------------------------------
 static void *capturing;
 void fake_capture(void *stream) { capturing = stream; }

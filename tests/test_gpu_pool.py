@@ -59,3 +59,17 @@ def test_kept_memory_is_bounded():
             p.setpts(*pts)
     torch.cuda.synchronize()
     assert free0 - torch.cuda.mem_get_info()[0] <= (1 << 30) + (256 << 20)
+
+
+def test_release_memory():
+    from paper_2102_08463_amd import release_memory
+    with Plan(1, (1024, 1024), eps=1e-5):
+        pass                                 # leaves a 2048^2 grid of 33 MB behind
+    held = torch.cuda.mem_get_info()[0]
+    release_memory()
+    assert torch.cuda.mem_get_info()[0] >= held + (32 << 20)
+    pts = [torch.from_numpy(a).float().cuda() for a in workloads.uniform(5000, 2, 3)]
+    c = torch.from_numpy(workloads.strengths(5000, 3)).to(torch.complex64).cuda()
+    one = _once(pts, c, (64, 64))
+    release_memory()
+    assert torch.equal(torch.view_as_real(one), torch.view_as_real(_once(pts, c, (64, 64))))
