@@ -235,6 +235,7 @@ int64_t subproblem_bound(const mnufft_plan_s *p, int64_t M)
 int alloc_points(mnufft_plan p, int64_t M)
 {
     free_points(p);
+    p->Mcap = M;  // (free_points also takes back a part, when an allocation fails)
     const size_t Ma = (size_t)std::max<int64_t>(M, 1);
     int rc;
     for (int d = 0; d < p->dim; ++d) {
@@ -278,7 +279,6 @@ int alloc_points(mnufft_plan p, int64_t M)
     p->partials_cap = std::max(mn::scan_partial_elems(p->hist_cap),
                                mn::scan_partial_elems((size_t)p->g.nbins + 1));
     if ((rc = dalloc(p, (void **)&p->partials, p->partials_cap * 4))) return rc;
-    p->Mcap = M;
     return MNUFFT_OK;
 }
 
