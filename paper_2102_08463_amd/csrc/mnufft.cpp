@@ -260,12 +260,6 @@ int alloc_points(mnufft_plan p, int64_t M)
             if ((rc = dalloc(p, (void **)&p->perm_proc, Ma * 4))) return rc;
             if (!p->mf && (rc = dalloc(p, (void **)&p->hslot_proc, Ma * 2))) return rc;
         }
-        // tiles of as many stacked transforms as kTileBytes hold, at least one
-        const size_t one = (size_t)std::max(p->nsub_cap, 1) * p->ts2 * p->rsz;
-        p->nt_chunk = (int)std::max<size_t>(
-            1, std::min<size_t>(std::min<int64_t>(p->ntransf, kMaxStack), kTileBytes / one));
-        p->scratch_bytes = one * p->nt_chunk;
-        if ((rc = dalloc(p, &p->scratch, p->scratch_bytes))) return rc;
         if ((rc = dalloc(p, (void **)&p->mergelist, (size_t)std::max(p->nsub_cap, 1) * 4)))
             return rc;
         if (!p->mf) {
@@ -279,7 +273,17 @@ int alloc_points(mnufft_plan p, int64_t M)
     p->partials_cap = std::max(mn::scan_partial_elems(p->hist_cap),
                                mn::scan_partial_elems((size_t)p->g.nbins + 1));
     if ((rc = dalloc(p, (void **)&p->partials, p->partials_cap * 4))) return rc;
-    return MNUFFT_OK;
+    if (p->method != MNUFFT_METHOD_SM) return MNUFFT_OK;
+    // tiles of as many stacked transforms as kTileBytes hold, at least one; last,
+    // and fewer where memory is short
+    const size_t one = (size_t)std::max(p->nsub_cap, 1) * p->ts2 * p->rsz;
+    p->nt_chunk = (int)std::max<size_t>(
+        1, std::min<size_t>(std::min<int64_t>(p->ntransf, kMaxStack), kTileBytes / one));
+    for (;; p->nt_chunk /= 2) {
+        p->scratch_bytes = one * p->nt_chunk;
+        rc = dalloc(p, &p->scratch, p->scratch_bytes);
+        if (rc != MNUFFT_ERR_ALLOC || p->nt_chunk == 1) return rc;
+    }
 }
 
 // What running type `type` (1 or 2) with exponent sign `sign` needs: the

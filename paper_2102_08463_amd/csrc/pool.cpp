@@ -93,7 +93,7 @@ hipError_t pool_alloc(void **ptr, size_t bytes)
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
-    const size_t size = size_class(bytes);
+    size_t size = size_class(bytes);
     try {
         Pool &p = pool();
         std::lock_guard<std::mutex> lock(p.m);
@@ -111,6 +111,11 @@ hipError_t pool_alloc(void **ptr, size_t bytes)
         if (e == hipErrorOutOfMemory && !p.idle.empty()) {
             (void)hipGetLastError();
             p.trim(-1, 0);
+            e = hipMalloc(ptr, size);
+        }
+        if (e == hipErrorOutOfMemory && size > bytes) {  // without the class's rest
+            (void)hipGetLastError();
+            size = bytes;
             e = hipMalloc(ptr, size);
         }
         if (e != hipSuccess) {
