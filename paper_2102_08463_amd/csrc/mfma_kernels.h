@@ -11,7 +11,9 @@
 // with the kernel values placed at the point's taps and exact zeros elsewhere.
 // v_mfma_f64_16x16x4 does 1024 FMAs in 64 cycles of a SIMD; the window has
 // 16^3 / w^3 times the cells (1.9 at w = 13), and a window's sums go to the
-// tile once per group, not once per point.
+// tile once per group, not once per point.  An infinity or NaN times such a zero
+// would reach the whole window: strengths and tiles that hold one take the
+// points tap by tap.
 #pragma once
 #include "spread_kernels.h"
 
@@ -25,6 +27,7 @@ constexpr int kMfPts = 32;        // points whose kernel values are staged at a 
 constexpr int kMfInterp = 1024;   // interpolation: four waves per SIMD
 constexpr int kMfPart = 1024;     // points of a work item of interpolation
 constexpr int kMfBlocks = 256;    // one per CU
+constexpr int kMfOdd = 1 << 30;   // with a point's window origin: strength not finite
 
 // Work items handed out one at a time: a block per CU fits, items differ by a
 // factor of 4096 in size, and a fixed share left a fifth of the CUs idle at
@@ -148,6 +151,10 @@ k_spread_mf(Geom g, const int32_t *__restrict__ sub, const int32_t *__restrict__
                 w[32] = slot_val<W>(z0, slot, st - og, bk);
                 st = start_of<W>(nu2, z0), og = st / S * S, o |= og << 16;
                 w[48] = slot_val<W>(z0, slot, st - og, bk);
+                if (!isfinite(nc.x) || !isfinite(nc.y)) {
+                    o |= kMfOdd;  // (in segments of their own, see below)
+                    if (kx == 0.0) w[0] = w[16] = 0.0;
+                }
                 if (slot == 0) org[pt] = o;
             }
             nu0 = u0[at(i0 + kMfPts)];
@@ -164,6 +171,25 @@ k_spread_mf(Geom g, const int32_t *__restrict__ sub, const int32_t *__restrict__
                 const uint64_t rest = edge & (~0ull << (a + 1));
                 const int b = rest ? (int)__builtin_ctzll(rest) : nv;
                 const int og = __builtin_amdgcn_readlane(mine, a);
+                if (og & kMfOdd) {
+                    // cells of the point's support alone, in this wave's planes
+                    const int ox = og & 255, oy = (og >> 8) & 255, oz = (og >> 16) & 255;
+                    for (int e = a * 2; e < b * 2; ++e) {
+                        const double *w = wts + (e >> 1) * 64;
+                        const int z = (2 * wv + (e & 1) - oz) & 15, Z = oz + z, X = ox + sl;
+                        for (int k = 0; k < 4; ++k) {
+                            const int y = 4 * k + kp, Y = oy + y;
+                            const double f = w[32 + y] * w[48 + z];
+                            if (f != 0.0 && (w[sl] != 0.0 || w[16 + sl] != 0.0)) {
+                                double2 &t = tile[(Z * p2 + Y) * p1 + X];
+                                t.x += f * w[sl];
+                                t.y += f * w[16 + sl];
+                            }
+                        }
+                    }
+                    a = b;
+                    continue;
+                }
                 if (og != cur) {
                     if (cur >= 0) flush();
                     cur = og;
@@ -194,7 +220,7 @@ k_spread_mf(Geom g, const int32_t *__restrict__ sub, const int32_t *__restrict__
             }
             __syncthreads();  // the staged values are no longer read
         }
-        flush();
+        if (cur >= 0) flush();
         __syncthreads();
         double2 *dst = scratch + tr * (tst.tiles / 2) + (size_t)q * tcells;
         for (int e = tid; e < tcells; e += kMfThreads) dst[e] = tile[e];
@@ -227,6 +253,9 @@ k_interp_mf(Geom g, const int32_t *__restrict__ sub, const int32_t *__restrict__
     // work item = kMfPart points of a subproblem (at most 4096 points, so most
     // of the later parts are empty)
     const int items = 4096 / kMfPart * nsub * nt;
+    __shared__ int odd[2];  // the staged tile holds values that are not finite; item by item
+    int turn = 0;
+    if (tid < 2) odd[tid] = 0;  // (the queue's barriers come before their use)
     for (int it = queue.next(items); it < items; it = queue.next(items)) {
         const int pt = it / nsub, part = pt / nt, tr = pt - part * nt;
         const double2 *gt = grid + tr * tst.grid;
@@ -252,11 +281,42 @@ k_interp_mf(Geom g, const int32_t *__restrict__ sub, const int32_t *__restrict__
                                  wrapmod(o2 + s2, g.n[1])) * g.n[0] + l1];
                 }
 #pragma unroll
-                for (int k = 0; k < kRows; ++k)
+                for (int k = 0; k < kRows; ++k) {
                     if (r0 + k * kStep < rows) tile[(r0 + k * kStep) * p1 + s1] = v[k];
+                    if (!isfinite(v[k].x) || !isfinite(v[k].y)) odd[turn] = 1;
+                }
             }
         }
         __syncthreads();
+        const int tap_by_tap = odd[turn];
+        turn ^= 1;
+        if (tid == 0) odd[turn] = 0;
+        if (tap_by_tap) {
+            for (int i = rec.y + tid; i < rec.y + rec.z; i += kMfInterp) {
+                double zy, zz, ar = 0.0, ai = 0.0, kx[W];
+                const int sx = taps<double, W>(u0[i] + (double)P, bk, kx);
+                const int sy = start_of<W>(u1[i], zy), sz = start_of<W>(u2[i], zz);
+#pragma unroll 1
+                for (int a3 = 0; a3 < W; ++a3) {
+                    const double kz = es_val(zz + (double)a3 * (2.0 / W), bk);
+#pragma unroll 1
+                    for (int a2 = 0; a2 < W; ++a2) {
+                        const double f = kz * es_val(zy + (double)a2 * (2.0 / W), bk);
+                        const double2 *row = tile + ((sz + a3) * p2 + sy + a2) * p1 + sx;
+                        double rr = 0.0, ri = 0.0;
+#pragma unroll
+                        for (int a1 = 0; a1 < W; ++a1) {
+                            rr += kx[a1] * row[a1].x;
+                            ri += kx[a1] * row[a1].y;
+                        }
+                        ar += f * rr;
+                        ai += f * ri;
+                    }
+                }
+                ct[idx[i]] = make_double2(ar, ai);
+            }
+            continue;
+        }
         const int share = (rec.z + kMfInterp / 4 - 1) / (kMfInterp / 4) * 16;  // points per wave
         const int w0 = rec.y + wv * share, w1 = min(w0 + share, rec.y + rec.z);
         for (int i0 = w0; i0 < w1; i0 += 64) {
