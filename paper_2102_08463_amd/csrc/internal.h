@@ -210,7 +210,7 @@ struct Pts {
     int mf;                   // start cells per window group of the matrix-core kernels
                               // (the points are in their order; 0: tap by tap)
     int *work;                // their work counters (spreading, interpolation), zero
-                              // between launches
+                              // between launches (null: interpolation without one)
     int sm;                   // method SM: sub, nsub and the kernels' order are set
     int nt;                   // stacked transforms of this launch (SM; at least 1)
     size_t tile_stride;       // reals between their tiles in scratch

@@ -256,7 +256,14 @@ k_interp_mf(Geom g, const int32_t *__restrict__ sub, const int32_t *__restrict__
     __shared__ int odd[2];  // the staged tile holds values that are not finite; item by item
     int turn = 0;
     if (tid < 2) odd[tid] = 0;  // (the queue's barriers come before their use)
-    for (int it = queue.next(items); it < items; it = queue.next(items)) {
+    // A counter serves one launch at a time; one that may run beside another of
+    // its plan has none and takes every gridDim-th item.
+    const auto next = [&](int it) {
+        if (work) return queue.next(items);
+        __syncthreads();
+        return it < 0 ? (int)blockIdx.x : it + (int)gridDim.x;
+    };
+    for (int it = next(-1); it < items; it = next(it)) {
         const int pt = it / nsub, part = pt / nt, tr = pt - part * nt;
         const double2 *gt = grid + tr * tst.grid;
         double2 *ct = c + tr * tst.c;
@@ -409,7 +416,7 @@ hipError_t interp_mf(const Geom &g, const Pts &P, const void *grid, void *c, hip
     hipLaunchKernelGGL(k, dim3(kMfBlocks), dim3(kMfInterp), lds, s, g, P.sub, P.nsub,
                        (const double *)P.u[0], (const double *)P.u[1], (const double *)P.u[2],
                        sm_index(P), (const double2 *)grid, (double2 *)c,
-                       kernel_param<double>(g.beta), P.work + 1, P.nt,
+                       kernel_param<double>(g.beta), P.work ? P.work + 1 : nullptr, P.nt,
                        TStride{(size_t)P.M, (size_t)P.ncells, 0});
     return hipGetLastError();
 }

@@ -1232,7 +1232,12 @@ int mnufft_interp(mnufft_plan p, const void *grid, void *c)
     if (p->type == 3) return MNUFFT_ERR_UNSUPPORTED;
     if (!grid || (p->M > 0 && !c)) return MNUFFT_ERR_ARG;
     if ((rc = use_device(p))) return rc;
-    MN_HIP(mn::launch_interp(p->g, p->prec, p->method, kernel_points(p, false), grid, c, p->stream));
+    mn::Pts P = kernel_points(p, false);
+    // It reads the plan alone, so calls on several streams or in graphs may run
+    // at once: no counter, which they would share (type 2's interpolation has the
+    // plan's grid to itself and keeps it).
+    if (p->use.elsewhere) P.work = nullptr;
+    MN_HIP(mn::launch_interp(p->g, p->prec, p->method, P, grid, c, p->stream));
     return MNUFFT_OK;
 }
 

@@ -18,7 +18,7 @@ for f in (fake.fake_count, fake.fake_live):
     f.restype = ctypes.c_longlong
 fake.fake_capacity.argtypes = [ctypes.c_longlong]
 fake.fake_capture.argtypes = [vp]
-MALLOC, FREE, STREAM_SYNC, DEVICE_SYNC, LAUNCH, OVERRUN, SYNC_DEV = range(7)
+MALLOC, FREE, STREAM_SYNC, DEVICE_SYNC, LAUNCH, OVERRUN, SYNC_DEV, QUEUE = range(8)
 count, live = fake.fake_count, fake.fake_live
 P = [vp((1 << 40) + (k << 36)) for k in range(8)]   # addresses of a caller's buffers
 lib.mnufft_makeplan.argtypes = [ci, ci, vp, ci, i64, dbl, ci, vp, vp]

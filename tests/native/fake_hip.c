@@ -17,7 +17,7 @@ static int nblk, device;
 static uintptr_t next_base = (uintptr_t)1 << 44;
 static long long live_bytes, capacity = -1;
 static long counts[16];
-enum { C_MALLOC, C_FREE, C_STREAM_SYNC, C_DEVICE_SYNC, C_LAUNCH, C_OVERRUN, C_SYNC_DEV };
+enum { C_MALLOC, C_FREE, C_STREAM_SYNC, C_DEVICE_SYNC, C_LAUNCH, C_OVERRUN, C_SYNC_DEV, C_QUEUE };
 
 long fake_count(int what) { return counts[what]; }
 void fake_clear(void) { memset(counts, 0, sizeof(counts)); }
@@ -160,6 +160,8 @@ int hipLaunchKernel(const void *fn, dim3_t g, dim3_t b, void **args, size_t sh, 
     }
     if (strstr(n, "k_scan_reduce")) need(n, PTR(2), (size_t)g.x * 4);  // (in, n, partials)
     if (strstr(n, "k_scan_down")) need(n, PTR(1), *(size_t *)args[2] * 4);  // (in, out, n, partials)
+    // (geometry, sub, nsub, u0, u1, u2, index, grid, c, bk, work, ..)
+    if (strstr(n, "k_interp_mf") && PTR(10)) ++counts[C_QUEUE];
     if (strstr(n, "k_subfill")) {           // (nbins, msub, nsub_max, .., .., sub, .., mergelist)
         need(n, PTR(5), (size_t)I32(2) * 16);
         need(n, PTR(10), (size_t)I32(2) * 4);
