@@ -315,7 +315,7 @@ hipError_t launch_balance(const Geom &g, int prec, int nsub_max, int msub, const
 // Subproblems must fit the grouping pass, the tile and the staged kernel
 // values the LDS.
 int mf_span(const Geom &g, int prec, int msub);
-// Dynamic LDS bytes of the matrix-core spreading kernel.
+// LDS bytes of the matrix-core spreading kernel, 64 of them static.
 size_t mf_lds_bytes(const Geom &g);
 // The processing order of those kernels (k_group), as launch_balance.
 hipError_t launch_group(const Geom &g, int prec, int span, int nsub_max, const int32_t *sub,

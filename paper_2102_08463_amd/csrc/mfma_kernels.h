@@ -397,7 +397,7 @@ template <int W>
 hipError_t spread_mf(const Geom &g, const Pts &P, const void *c, hipStream_t s)
 {
     auto k = k_spread_mf<W>;
-    const size_t lds = mf_lds_bytes(g);
+    const size_t lds = mf_lds_bytes(g) - 64;  // (what is not static)
     (void)hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     hipLaunchKernelGGL(k, dim3(kMfBlocks), dim3(kMfThreads), lds, s, g, P.sub, P.nsub,
                        (const double *)P.u[0], (const double *)P.u[1], (const double *)P.u[2],

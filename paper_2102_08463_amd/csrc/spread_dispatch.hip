@@ -81,8 +81,8 @@ size_t sm_lds_bytes(const Geom &g, int prec, bool interp, int msub)
 size_t mf_lds_bytes(const Geom &g)
 {
     // the tile, then 32 staged points: 4 x 16 products of kernel values and
-    // strength and the window's origin each
-    return (size_t)sm_tile_stride(g) * 8 + 32 * (64 * 8 + 4);
+    // strength and the window's origin each; and the kernels' static LDS
+    return (size_t)sm_tile_stride(g) * 8 + 32 * (64 * 8 + 4) + 64;
 }
 
 int mf_span(const Geom &g, int prec, int msub)

@@ -162,6 +162,8 @@ int hipLaunchKernel(const void *fn, dim3_t g, dim3_t b, void **args, size_t sh, 
     if (strstr(n, "k_scan_down")) need(n, PTR(1), *(size_t *)args[2] * 4);  // (in, out, n, partials)
     // (geometry, sub, nsub, u0, u1, u2, index, grid, c, bk, work, ..)
     if (strstr(n, "k_interp_mf") && PTR(10)) ++counts[C_QUEUE];
+    // 160 KB of LDS, some of it static
+    if (strstr(n, "_mf") && sh + 16 > 160 * 1024) need("LDS of a matrix-core kernel", (void *)1, 1);
     if (strstr(n, "k_subfill")) {           // (nbins, msub, nsub_max, .., .., sub, .., mergelist)
         need(n, PTR(5), (size_t)I32(2) * 16);
         need(n, PTR(10), (size_t)I32(2) * 4);
