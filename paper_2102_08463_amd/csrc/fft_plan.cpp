@@ -19,6 +19,7 @@ struct Pass {
     int64_t nt;      // transforms
     int form = 0;
     bool rows;
+    bool rotate = false;  // scales its outputs by FftPass::tw4
 };
 
 FftPass blank()
@@ -82,7 +83,7 @@ void passes_of(int type, int dim, const int64_t *N, const int *n, int64_t nt,
         c.p.col0 = c.p.col1 = 1;
         r.p.col0 = 0;
         r.p.col1 = 1;
-        c.p.tw4 = &c;  // (the table is set with the others)
+        c.rotate = true;
         c.p.s_e = c.p.d_e = B;
         c.p.s_a = c.p.d_a = 1;
         c.p.s_t = c.p.d_t = n1;
@@ -237,6 +238,7 @@ int FftPlan::make(int dim, const int64_t *N, const int *n, int64_t nt, int prec_
             st.form = q.form;
             st.src = q.src;
             st.dst = q.dst;
+            st.rotate = q.rotate;
             st.tiles = (long long)q.p.ta * q.p.nb * q.nt;
             if (st.tiles > 2147483647LL) return MNUFFT_OK;
             dir[t].push_back(st);
@@ -269,7 +271,7 @@ int FftPlan::make(int dim, const int64_t *N, const int *n, int64_t nt, int prec_
             return MNUFFT_ERR_HIP;
         for (auto &d : dir)
             for (FftStep &st : d)
-                if (st.p.tw4) st.p.tw4 = t;
+                if (st.rotate) st.p.tw4 = t;
     }
     work_cells = fourA ? n[0] * nt : 0;
     ok = true;

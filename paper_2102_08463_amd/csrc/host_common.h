@@ -116,6 +116,7 @@ using FftAlloc = std::function<int(void **, size_t)>;
 struct FftStep {
     FftPass p;
     int V = 16, form = 0, src = 0, dst = 0;
+    bool rotate = false;  // takes the two-step table of a long line
     long long tiles = 0;
 };
 struct FftPlan {
