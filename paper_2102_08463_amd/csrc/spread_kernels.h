@@ -64,6 +64,11 @@ __device__ __forceinline__ float es_val(float z, float bk)
     const float t = fmaxf(1.0f - z * z, 0.0f);
     return __builtin_amdgcn_exp2f(bk * (__builtin_amdgcn_sqrtf(t) - 1.0f));
 }
+// ln 2 in two parts: its first 40 binary places, so that multiples up to 2^13
+// are exact, and the rest (ln 2 less its double is 2.319046813846299615e-17).
+constexpr double kLn2 = 0.693147180559945309417232;
+constexpr double kLn2Hi = (double)(long long)(kLn2 * 1099511627776.0) / 1099511627776.0;
+constexpr double kLn2Lo = (kLn2 - kLn2Hi) + 2.319046813846299615e-17;
 // Double precision without the library calls' special cases, half their
 // instructions: the root by two Goldschmidt steps from the hardware's 24-bit
 // reciprocal root (1e-300 stands for a zero argument), the exponential of an
@@ -79,8 +84,8 @@ __device__ __forceinline__ double es_val(double z, double bk)
     h = fma(h, r0, h);
     g = fma(fma(-g, g, t), h, g);
     const double x = fma(bk, g, -bk);
-    const double n = rint(x * 1.4426950408889634);
-    const double r = fma(-n, 1.90821492927058770002e-10, fma(-n, 6.93147180369123816490e-01, x));
+    const double n = rint(x * (1.0 / kLn2));
+    const double r = fma(-n, kLn2Lo, fma(-n, kLn2Hi, x));
     double p = 1.0 / 6227020800.0;
     p = fma(p, r, 1.0 / 479001600.0);
     p = fma(p, r, 1.0 / 39916800.0);
