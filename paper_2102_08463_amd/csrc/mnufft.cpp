@@ -151,11 +151,13 @@ void dfree(mnufft_plan p, void **ptr, size_t bytes)
     *ptr = nullptr;
 }
 
-// To be called by every entry point before it enqueues work.
-int use_device(mnufft_plan p)
+// To be called by every entry point; `enqueue`: it is about to put work on the
+// plan's stream (others leave a stream alone that its owner may have destroyed).
+int use_device(mnufft_plan p, bool enqueue = true)
 {
     if (p->device >= 0) MN_HIP(hipSetDevice(p->device));
     if (p->use.device < 0) MN_HIP(hipGetDevice(&p->use.device));
+    if (!enqueue) return MNUFFT_OK;
     p->use.note(p->stream);
     for (mnufft_plan q : {p->t3spr, p->t3inner})
         if (q) q->use.elsewhere = q->use.elsewhere || p->use.elsewhere;
@@ -1304,7 +1306,7 @@ int mnufft_get_subproblems(mnufft_plan p, int32_t *sub, int32_t *nsub)
 int mnufft_set_stream(mnufft_plan p, void *stream)
 {
     if (!p) return MNUFFT_ERR_ARG;
-    int rc = use_device(p);
+    int rc = use_device(p, false);
     if (rc) return rc;
     // what both FFT directions need exists from here on, so execute /
     // execute_adjoint allocate nothing and can be captured into a graph

@@ -17,7 +17,7 @@ vp, i64, ci, dbl = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int, ctypes.c_doubl
 for f in (fake.fake_count, fake.fake_live):
     f.restype = ctypes.c_longlong
 fake.fake_capacity.argtypes = [ctypes.c_longlong]
-fake.fake_capture.argtypes = [vp]
+fake.fake_capture.argtypes = fake.fake_stream_gone.argtypes = [vp]
 MALLOC, FREE, STREAM_SYNC, DEVICE_SYNC, LAUNCH, OVERRUN, SYNC_DEV, QUEUE = range(8)
 count, live = fake.fake_count, fake.fake_live
 P = [vp((1 << 40) + (k << 36)) for k in range(8)]   # addresses of a caller's buffers

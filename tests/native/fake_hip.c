@@ -99,7 +99,14 @@ static int failing;
 void fake_fail_waits(int on) { failing = on; }
 int hipDeviceSynchronize(void) { ++counts[C_DEVICE_SYNC]; counts[C_SYNC_DEV] = device; return failing; }
 int hipStreamSynchronize(void *s) { (void)s; ++counts[C_STREAM_SYNC]; counts[C_SYNC_DEV] = device; return failing; }
-int hipStreamIsCapturing(void *s, int *st) { *st = s && s == capturing; return kOk; }
+static void *gone;
+void fake_stream_gone(void *stream) { gone = stream; }  // using it counts as an overrun
+int hipStreamIsCapturing(void *s, int *st)
+{
+    if (s && s == gone) ++counts[C_OVERRUN];
+    *st = s && s == capturing;
+    return kOk;
+}
 int hipStreamCreateWithFlags(void **s, unsigned f) { (void)f; *s = malloc(1); return kOk; }
 int hipStreamDestroy(void *s) { free(s); return kOk; }
 int hipStreamWaitEvent(void *s, void *e, unsigned f) { (void)s; (void)e; (void)f; return kOk; }

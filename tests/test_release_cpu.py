@@ -115,3 +115,16 @@ def test_per_thread_stream(tmp_path):
     lib.mnufft_destroy(h)
     assert count(DEVICE_SYNC) > 0
     """)
+
+
+def test_stream_destroyed_before_the_plan_moves(tmp_path):
+    """Moving a plan does not touch the stream that it leaves."""
+    host_shim.run(tmp_path, f"""
+    h = plan(1, (64, 64), stream={S1})
+    assert setpts(h, 1000, 2) == 0
+    fake.fake_stream_gone({S1})
+    assert lib.mnufft_set_stream(h, {S2}) == 0
+    assert lib.mnufft_execute(h, P[3], P[4]) == 0
+    assert count(OVERRUN) == 0
+    lib.mnufft_destroy(h)
+    """)
