@@ -80,7 +80,7 @@ __device__ __forceinline__ int start_of(double u, double &z0)
 // (evaluating in extra waves beside the products was slower: 11.5 ms for 9.9),
 // so what is left beside the products is kept short: each step of four points
 // reads five operands and multiplies two.  w = 13, 1.6e7 points in caps on
-// 162^3: 33.0 -> 6.95 ms; the products alone would take 3.6 ms.
+// 162^3: 33.0 -> 7.0 ms; the products alone would take 3.6 ms.
 template <int W>
 __global__ void __launch_bounds__(kMfThreads)
 k_spread_mf(Geom g, const int32_t *__restrict__ sub, const int32_t *__restrict__ nsubp,

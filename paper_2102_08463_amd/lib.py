@@ -1,7 +1,7 @@
 """ctypes binding of libmnufft (include/mnufft.h): argument marshalling only.
 
-Every step of the transform runs in the library's HIP kernels (the FFT in
-rocFFT).  PyTorch provides device memory and the stream; torch is imported
+Every step of the transform runs in the library's HIP kernels (FFT lines too
+long for a workgroup in rocFFT).  PyTorch provides device memory and the stream; torch is imported
 before the library is loaded so that both share one HIP runtime.  There is
 no CPU fallback: if the library is missing, loading raises.
 """
