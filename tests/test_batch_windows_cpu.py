@@ -23,7 +23,6 @@ int main()
     for (int w = 2; w <= 8; ++w)
         for (int own : {6, 8, 11, 12, 16, 17, 23, 32})
             for (int m : {8, 16, 29, 32}) {
-                if (own > m) continue;
                 const int P = (w + 1) / 2;
                 for (int it = 0; it < 20000; ++it) {
                     // anywhere, or within units of single precision of a window's edge
